@@ -351,6 +351,8 @@ def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
         if costmodel.is_kf_tile(r["tile"]):       # prisms and hexahedra: factorised along the third coordinate
             r["alg_flops_per_element"] = (costmodel.f_factored_zfirst(n, p + 1, q) if costmodel.is_zfirst_tile(r["tile"])
                                           else costmodel.f_factored(n, p + 1, q))
+        elif costmodel.is_pair_tile(r["tile"]):   # prisms: products of pairs of triangle functions
+            r["alg_flops_per_element"] = costmodel.f_pair(p, rule)
         elif kind == "tet" and costmodel.is_tet_ref_tile(r["tile"]):   # the reference-matrix GEMM
             r["alg_flops_per_element"] = costmodel.f_tet_reference(n)
         else:
@@ -421,7 +423,8 @@ def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
     npad, nqp = (n + 15) // 16 * 16, (q + 7) // 8 * 8
     kf = costmodel.is_kf_tile(h["tile"])
     tref = kind == "tet" and costmodel.is_tet_ref_tile(h["tile"])
-    hw_flops = (products * costmodel.kf_mfma_flops(p, rule, n, q) * ne if kf else
+    hw_flops = (products * costmodel.pair_mfma_flops(p, rule, products == 3) * ne if costmodel.is_pair_tile(h["tile"]) else
+                products * costmodel.kf_mfma_flops(p, rule, n, q) * ne if kf else
                 costmodel.tet_reference_mfma_flops(n) * ne if tref else
                 products * 8.0 * npad * npad * (nqp if products == 3 else q) * ne)
     roofline.update({"traffic": traffic, "kernel_ms": h["kernel_ms_mean"], "flops_per_launch": falg * ne,
@@ -433,6 +436,8 @@ def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
                               if kf and costmodel.is_zfirst_tile(h["tile"]) else
                               "algorithmic flops of the triangle-point contraction per element "
                               "(8 n^2 nij + 8 (p+1)^2 nij n + 24 nq ntri + 12 nq n)" if kf else
+                              "algorithmic flops of the products of pairs of triangle functions per element "
+                              "(costmodel.f_pair)" if costmodel.is_pair_tile(h["tile"]) else
                               "algorithmic flops of the reference-matrix GEMM per element (26 n^2 + n)" if tref else
                               "algorithmic flops 8 n^2 nq per element (one product per entry; "
                               "a split form issues three products)") + "; bytes %d in + (n^2+n) outputs" % in_bytes})
@@ -706,7 +711,7 @@ def bench_laplace(args):
         ms, mn, wall = timed(lambda: F.integrate_laplace_raw(X, p, form, A=A), steps, warm)
         points = F.nq(p, "symmetric")
         paper_ops = costmodel.laplace_paper_ops(p, points)
-        own = ((costmodel.f_factored_zfirst(costmodel.nshp(p), p + 1, costmodel.nq(p, "symmetric"))
+        own = costmodel.f_pair(p, "symmetric") if costmodel.is_pair_tile(tile) else ((costmodel.f_factored_zfirst(costmodel.nshp(p), p + 1, costmodel.nq(p, "symmetric"))
                 if costmodel.is_zfirst_tile(tile) else costmodel.f_kf(p, "symmetric"))
                if costmodel.is_kf_tile(tile) else costmodel.f_dom(p, "symmetric"))
         peak = PEAK_TFLOPS[form]

@@ -266,7 +266,9 @@ feint_status feint_tile_set(int p, feint_form form, int tile);
    their tensor-product factors, no table read: the paper's SC strategy,
    Sec. 4), or "KxTNf" (contraction per triangle point, or per plane point
    for hexahedra: K zeta rows of shape functions by TN column tiles per
-   wave, FP64 and FP32),
+   wave, FP64 and FP32), or "0xWf" (prisms: products of pairs of triangle
+   functions, W waves per workgroup; the default from p = 3, in the split
+   forms from p = 2),
    or "vL" (vector-ALU kernel, L lanes per element); "o2" marks a
    two-waves-per-SIMD register budget. */
 feint_status feint_tile_describe(int p, feint_form form, int tile, char *buf, size_t len);

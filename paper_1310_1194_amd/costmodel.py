@@ -168,12 +168,64 @@ def is_kf_tile(desc: str) -> bool:
     "KxTNfwg", optionally "o" and the waves per SIMD, name the triangle-point
     contraction."""
     import re
-    return re.fullmatch(r"\d+x\d+f(wg?|z)?(o\d)?", desc) is not None
+    return re.fullmatch(r"[1-9]\d*x\d+f(wg?|z)?(o\d)?", desc) is not None
+
+
+def is_pair_tile(desc: str) -> bool:
+    """Tile descriptions "0xWf" (W waves per workgroup), optionally "oK", name the
+    prisms' products of pairs of triangle functions."""
+    import re
+    return re.fullmatch(r"0x\d+f(o\d)?", desc) is not None
+
+
+def pair_sizes(p: int, rule: str = "collapsed"):
+    """(rows, contraction length) of the four classes of the pair products, in the
+    order even symmetric, even antisymmetric, odd symmetric, odd antisymmetric.
+    Rows: orbits of the pairs (t, t') of triangle functions under exchange and
+    under the reflection that swaps two barycentric coordinates.  Contraction:
+    the types 0o 0e 00 oo ee oe (antisymmetric 0o 0e oe), each over the reflected
+    pairs of triangle points and, where the type's parity is the class's, over
+    the fixed points."""
+    nt, fixed = (p + 1) * (p + 2) // 2, p // 2 + 1
+    moved = (nt - fixed) // 2
+    ff = fixed * (fixed - 1) // 2
+    full = (nt * nt - fixed - 2 * (ff + 2 * moved)) // 4
+    nij = nq(p, rule) // (p + 1)
+    if rule == "collapsed":
+        selfs = p + 1 if (p + 1) % 2 else 0
+    else:
+        selfs = {1: 1, 2: 2, 3: 2, 4: 4, 5: 3, 6: 5, 7: 6}[p]
+    pairs = (nij - selfs) // 2
+    return [(full + 2 * moved + ff + fixed, 6 * pairs + 4 * selfs), (full + 2 * moved + ff, 3 * pairs + selfs),
+            (full + moved, 6 * pairs + 2 * selfs), (full + 2 * moved, 3 * pairs + 2 * selfs)]
+
+
+def f_pair(p: int, rule: str = "collapsed") -> int:
+    """Flops per element of the pair products: per class rows x contraction
+    length x (p+1)^2 columns; the zeta sums (13 multiply-adds per triangle point,
+    (k, k') and zeta point) with the sums and differences of the points' W (2 x 13
+    per pair of points and zeta point); four additions per orbit and column for
+    its parity sums and four for its entries; the load vector."""
+    nk, nij = p + 1, nq(p, rule) // (p + 1)
+    sizes = pair_sizes(p, rule)
+    gemm = sum(2 * r * k for r, k in sizes) * nk * nk
+    zeta = 26 * nij * nk ** 3 + 13 * nij * nk
+    load = 2 * nij * nk * nk + 2 * nij * nshp(p)
+    return gemm + zeta + 8 * sizes[0][0] * nk * nk + load
+
+
+def pair_mfma_flops(p: int, rule: str = "collapsed", split: bool = False) -> int:
+    """Issued matrix flops per element of the pair products (one product): tiles
+    of 16 orbits, blocks of 8 (FP64), 4 (FP32; the last block of 16) or 32 (split
+    forms) contraction rows, 16 columns (k, k')."""
+    g = 32 if split else 8
+    cols = -(-(p + 1) ** 2 // 16) * 16
+    return sum(2 * (-(-r // 16) * 16) * (-(-k // g) * g) for r, k in pair_sizes(p, rule)) * cols
 
 
 def f_kernel(p: int, rule: str, desc: str) -> int:
     """Algorithmic flops per element of the algorithm the tile runs."""
-    return f_kf(p, rule) if is_kf_tile(desc) else f_dom(p, rule)
+    return f_pair(p, rule) if is_pair_tile(desc) else f_kf(p, rule) if is_kf_tile(desc) else f_dom(p, rule)
 
 
 def f_full(p: int) -> int:

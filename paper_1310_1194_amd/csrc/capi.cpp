@@ -63,8 +63,10 @@ feint_status prepare_tables(int p, int rule, int type) {
     const size_t s_ycf = align(H.Ycf.size() * 4);
     const size_t s_m64 = align(H.Mref.size() * 8), s_m32 = align(H.Mref32.size() * 4);
     const size_t s_tb = align(H.taub_hi.size() * 2);
+    const size_t s_p64 = align(H.pair64.size() * 8), s_p32 = align(H.pair32.size() * 4), s_pb = align(H.pairb.size() * 2);
+    const size_t s_po = align(H.potab.size() * 4), s_pp = align(H.ppts.size() * 2), s_pt = align(H.pbt64.size() * 8), s_pq = align(H.pqw.size() * 8);
     const size_t total = s_tau + s_tau32 + s_lam + s_lam32 + s_qw + s_gll + 2 * s_b64 + 3 * s_b32 + 4 * s_sp + s_ycf +
-                         s_m64 + s_m32 + 4 * s_tb;
+                         s_m64 + s_m32 + 4 * s_tb + s_p64 + s_p32 + 2 * s_pb + s_po + s_pp + 2 * s_pt + s_pq;
     char *base = nullptr;
     e = hipMalloc((void **)&base, total);
     if (e != hipSuccess) { set_error("hipMalloc(tables)", e); return FEINT_ERR_HIP; }
@@ -104,6 +106,17 @@ feint_status prepare_tables(int p, int rule, int type) {
     T->taubl = (const uint16_t *)put(H.taub_lo.data(), H.taub_lo.size() * 2, s_tb);
     T->tauhh = (const uint16_t *)put(H.tauh_hi.data(), H.tauh_hi.size() * 2, s_tb);
     T->tauhl = (const uint16_t *)put(H.tauh_lo.data(), H.tauh_lo.size() * 2, s_tb);
+    T->pair64 = (const double *)put(H.pair64.data(), H.pair64.size() * 8, s_p64);
+    T->pair32 = (const float *)put(H.pair32.data(), H.pair32.size() * 4, s_p32);
+    T->pairb = (const uint16_t *)put(H.pairb.data(), H.pairb.size() * 2, s_pb);
+    T->pairh = (const uint16_t *)put(H.pairh.data(), H.pairh.size() * 2, s_pb);
+    T->potab = (const uint32_t *)put(H.potab.data(), H.potab.size() * 4, s_po);
+    T->ppts = (const uint16_t *)put(H.ppts.data(), H.ppts.size() * 2, s_pp);
+    T->pbt64 = (const double *)put(H.pbt64.data(), H.pbt64.size() * 8, s_pt);
+    T->pbt32 = (const float *)put(H.pbt32.data(), H.pbt32.size() * 4, s_pt);
+    T->pqw = (const double *)put(H.pqw.data(), H.pqw.size() * 8, s_pq);
+    T->pair_shift = H.pair_shift;
+    T->pair_gz = (float)H.pair_gz;
     T->tau_f16_shift = H.tau_f16_shift;
     T->f16_zc = (float)H.f16_zc;
     T->f16_zb = (float)H.f16_zb;
@@ -154,6 +167,11 @@ void fill_fwd_params(FwdParams &prm, const feint_elements *el, int form, const D
     prm.Mref64 = T->Mref64; prm.Mref32 = T->Mref32;
     prm.taubh = form == FEINT_FP16X3 ? T->tauhh : T->taubh;
     prm.taubl = form == FEINT_FP16X3 ? T->tauhl : T->taubl;
+    prm.pairA = form == FEINT_FP64 ? (const void *)T->pair64 : form == FEINT_FP32 ? (const void *)T->pair32
+                : form == FEINT_FP16X3 ? (const void *)T->pairh : (const void *)T->pairb;
+    prm.potab = T->potab; prm.ppts = T->ppts; prm.pbt64 = T->pbt64; prm.pbt32 = T->pbt32; prm.pqw = T->pqw;
+    prm.pair_shift = T->pair_shift;
+    prm.pair_gz = T->pair_gz;
     prm.tau_f16_shift = T->tau_f16_shift;
     prm.f16_zc = T->f16_zc;
     prm.f16_zb = T->f16_zb;
@@ -296,7 +314,8 @@ feint_status feint_rule_tile_set(int p, feint_form form, feint_rule rule, int ti
 // "TMxTN" plus the kernel kind (s staged, sa A operands staged, p pipelined,
 // c shape functions computed per point, f contraction per triangle or plane
 // point, fw the same with two waves per element sharing its point blocks, y split form with Y formed on
-// the matrix cores; "vL" vector-ALU kernel with L lanes per element)
+// the matrix cores; "0xWf" products of pairs of triangle functions, W waves per workgroup;
+// "vL" vector-ALU kernel with L lanes per element)
 // and "o2" for a two-waves-per-SIMD register budget.
 static void describe_variant(const FwdVariant &v, char *buf, size_t len) {
     if (v.staged == 3)
@@ -304,6 +323,8 @@ static void describe_variant(const FwdVariant &v, char *buf, size_t len) {
     else if (v.staged == 11)
         std::snprintf(buf, len, "ref%d%s%s%s", v.tm, v.tn % 4 == 2 ? "s" : "", v.tn >= 4 ? ("e" + std::to_string(v.tn / 4)).c_str() : "",
                       v.minw > 1 ? ("o" + std::to_string(v.minw)).c_str() : "");
+    else if (v.staged == 17)
+        std::snprintf(buf, len, "0x%df%s", v.tn, v.minw > 1 ? ("o" + std::to_string(v.minw)).c_str() : "");
     else if (v.staged >= 8 && v.staged <= 10)
         std::snprintf(buf, len, "sf%dw%s%s%s", v.tn, v.tm > 1 ? ("x" + std::to_string(v.tm)).c_str() : "",
                       v.staged == 9 ? "r" : v.staged == 10 ? "l" : "",

@@ -7,11 +7,14 @@ namespace {
 const FwdVariant v1[] = {
     FEINT_K32S(1, BF16X3, 1, 1, true, 1)};
 const FwdVariant v2[] = {
+    FEINT_KP(2, BF16X3),
     FEINT_K32S(2, BF16X3, 2, 2, true, 1)};
 const FwdVariant v3[] = {
+    FEINT_KP(3, BF16X3),
     FEINT_K32S(3, BF16X3, 3, 3, true, 1),
     FEINT_K32S(3, BF16X3, 3, 1, true, 2)};
 const FwdVariant v4[] = {
+    FEINT_KP(4, BF16X3),
     FEINT_K32Y(4, BF16X3, 5, 5, 2, 0),
     FEINT_K32Y(4, BF16X3, 5, 3, 3, 0),
     FEINT_K32P(4, BF16X3, 5, 5, 1),
@@ -24,6 +27,7 @@ const FwdVariant v4[] = {
     FEINT_KF2G(4, 5, 3, 2),
     FEINT_KF2G(4, 5, 1, 3)};
 const FwdVariant v5[] = {
+    FEINT_KP(5, BF16X3),
     FEINT_KF2G(5, 3, 2, 2),
     FEINT_K32S(5, BF16X3, 8, 4, false, 1),
     FEINT_K32S(5, BF16X3, 8, 4, true, 1),
@@ -31,6 +35,7 @@ const FwdVariant v5[] = {
     FEINT_K32U(5, BF16X3, 8, 4, 1),
     FEINT_KF2G(5, 3, 3, 2)};
 const FwdVariant v6[] = {
+    FEINT_KP(6, BF16X3),
     FEINT_KF2G(6, 7, 1, 2),
     FEINT_K32S(6, BF16X3, 13, 2, false, 2),
     FEINT_K32S(6, BF16X3, 13, 2, false, 1),
@@ -38,6 +43,7 @@ const FwdVariant v6[] = {
     FEINT_K32U(6, BF16X3, 13, 2, 1)};
 
 const FwdVariant v7[] = {
+    FEINT_KP(7, BF16X3),
     FEINT_KF2G(7, 4, 2, 2),
     FEINT_KF2G(7, 4, 1, 2),
     FEINT_K32Y(7, BF16X3, 3, 3, 2, 1),

@@ -10,6 +10,7 @@
 #include "fwd_ymfma.h"
 #include "fwd_hsf.h"
 #include "fwd_tref.h"
+#include "fwd_pair.h"
 
 namespace feint {
 
@@ -132,6 +133,24 @@ int64_t items_of(int64_t ne) { return items_for<KER>(ne); }
 // is used (fewer registers: two waves per SIMD in FP64 at p >= 5; staged = 10)
 #define FEINT_KHL(P, T, NTH, EPW, W) \
     FwdVariant{EPW, (NTH) / 64, 10, W, &launch_hsf<P, T, NTH, EPW, true, W, true>, &items_hsf<EPW>}
+
+// PP: products of pairs of triangle functions (staged = 17)
+template <class K, int MINW>
+void launch_pair(const FwdParams &prm, hipStream_t s) {
+    // as many workgroups as the device holds at once (256 CUs), each going on to further elements
+    static const int per_cu = [] {
+        int n = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_pair<K, K::NW_, MINW>, K::NW_ * 64, 0) == hipSuccess && n > 0 ? n : 1;
+    }();
+    const int64_t groups = (prm.ne + K::EPB_ - 1) / K::EPB_, most = 256 * (int64_t)per_cu;
+    hipLaunchKernelGGL((fwd_pair<K, K::NW_, MINW>), dim3((unsigned)(groups < most ? groups : most)), dim3(K::NW_ * 64), 0, s, prm);
+}
+template <class K>
+int64_t items_pair(int64_t ne) { return (ne + K::EPB_ - 1) / K::EPB_ * 4; }
+#define FEINT_KPG(P, F, R, GEO)                                                                        \
+    FwdVariant{PairShape<P, F>::EPB, PairShape<P, F>::NW, 17, PairShape<P, F>::W,                      \
+               &launch_pair<KPOf<P, F, R, GEO>, PairShape<P, F>::W>, &items_pair<KPOf<P, F, R, GEO>>}
+#define FEINT_KP(P, F) FEINT_KPG(P, F, 0, PrismGeo)
 
 #define FEINT_K4U(P, T, TM, TN, W) FEINT_K4U_R(P, T, TM, TN, W, 0)
 #define FEINT_KSC(P, T, TM, TN, W) FEINT_KSC_R(P, T, TM, TN, W, 0)

@@ -29,6 +29,15 @@ struct FwdParams {
     const uint16_t *taubl;   //   fp16 of tau * 2^tau_f16_shift for the fp16 form)
     int tau_f16_shift;
     float f16_zc, f16_zb;    // fp16 form: |Z| <= f16_zc max|W|, load-vector zeta sums <= f16_zb max|w det J f|
+    // prisms, products of pairs of triangle functions (pair_dims.h)
+    const void *pairA;       // the form's table
+    const uint32_t *potab;   // [orbits padded to 16] t, t' and their reflections, a byte each (all ones: padding)
+    const uint16_t *ppts;    // [sets][2] triangle points of a reflected pair (equal: a fixed point)
+    const double *pqw;       // [line point][sets][2][4] points of the pairs (xi1, xi2, zeta, w)
+    const double *pbt64;     // load vector: factors of the sums and differences of a pair
+    const float *pbt32;
+    int pair_shift;          // fp16: the table holds values * 2^pair_shift
+    float pair_gz;           // fp16: |G| <= pair_gz max |E|
     float bmax;              // max |B| (fp16 form: used for the per-element scale)
     int f16_shift;           // fp16 tables hold B * 2^f16_shift
     // mixed-degree launches: element ids in bucket order and packed offsets
@@ -51,7 +60,8 @@ struct FwdVariant {
                          // 7: split kernel with Y formed on the matrix cores,
                          // 8: hexahedra by sum factorisation (9: W_q formed in each pass,
                          // 10: and the last pass reading from LDS), 11: tetrahedra from
-                         // reference matrices
+                         // reference matrices, 17: products of pairs of triangle functions
+                         // (tm = elements per workgroup, tn = waves per workgroup)
     int minw;            // waves per SIMD the register allocation allows
     void (*launch)(const FwdParams &, hipStream_t);
     int64_t (*items)(int64_t ne);   // work items (waves) of a launch over ne elements

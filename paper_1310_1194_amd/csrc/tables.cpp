@@ -10,6 +10,7 @@
 //     matrix of a Legendre-product modal basis at the nodes (LU with partial
 //     pivoting in extended precision), then evaluating the modal basis and
 //     its derivatives at each quadrature point.
+#include "pair_dims.h"
 #include "tables.h"
 
 #include <cmath>
@@ -453,6 +454,148 @@ void rule_points(int p, int rule, std::vector<double> &qw) {
     }
 }
 
+// Tables of the products of pairs of triangle functions (tau64 and lam are set).
+void build_pair_tables(HostTables &T) {
+    const int p = T.p, rule = T.rule;
+    const PairDims D = pair_dims(p, rule);
+    const int nt = D.nt, nk = D.nk;
+    if (D.nij != T.nij) throw std::runtime_error("pair tables: point count");
+    // the reflection on lattice nodes (j outer, i inner: i -> p - j - i) and on points
+    std::vector<int> st(nt), sp(T.nij);
+    for (int j = 0, t = 0; j <= p; ++j)
+        for (int i = 0; i + j <= p; ++i, ++t) st[t] = t - i + (p - j - i);
+    T.ppts.clear();
+    std::vector<int> self;
+    for (int q = 0; q < T.nij; ++q) {
+        const double x = T.qw[4 * q], y = T.qw[4 * q + 1];
+        int best = -1;
+        for (int r = 0; r < T.nij; ++r)
+            if (std::fabs(T.qw[4 * r] - (1.0 - x - y)) + std::fabs(T.qw[4 * r + 1] - y) < 1e-10) best = r;
+        if (best < 0) throw std::runtime_error("pair tables: the rule is not symmetric");
+        sp[q] = best;
+        if (best > q) { T.ppts.push_back((uint16_t)q); T.ppts.push_back((uint16_t)best); }
+        if (best == q) self.push_back(q);
+    }
+    for (int q : self) { T.ppts.push_back((uint16_t)q); T.ppts.push_back((uint16_t)q); }
+    if ((int)self.size() != D.nself || (int)T.ppts.size() != 2 * D.sets) throw std::runtime_error("pair tables: fixed points");
+    // orbits of the pairs (t, t'), in the order of pair_dims.h
+    std::vector<std::pair<int, int>> orb[5];
+    std::vector<char> seen((size_t)nt * nt, 0);
+    for (int a = 0; a < nt; ++a)
+        for (int b = 0; b < nt; ++b) {
+            if (seen[a * nt + b]) continue;
+            const int im[4] = {a * nt + b, b * nt + a, st[a] * nt + st[b], st[b] * nt + st[a]};
+            for (int x : im) seen[x] = 1;
+            const bool fa = st[a] == a, fb = st[b] == b;
+            orb[fa && fb ? (a == b ? 4 : 3) : a == b ? 1 : b == st[a] ? 2 : 0].push_back({a, b});
+        }
+    std::vector<std::pair<int, int>> rows;
+    for (auto &o : orb) rows.insert(rows.end(), o.begin(), o.end());
+    if ((int)rows.size() != D.rows || (int)orb[0].size() != D.nfull) throw std::runtime_error("pair tables: orbits");
+    T.potab.assign((size_t)pair_tiles(p, 0) * 16, 0xFFFFFFFFu);
+    for (int o = 0; o < D.rows; ++o) {
+        const uint32_t a = rows[o].first, b = rows[o].second;
+        T.potab[o] = a | b << 8 | (uint32_t)st[a] << 16 | (uint32_t)st[b] << 24;
+    }
+    // operators 0, o = d/dxi1, e = d/dxi2 - d/dxi1 / 2 on function t at point q
+    auto op = [&](int r, int q, int t) {
+        const double *c = &T.tau64[(size_t)q * 4 * T.tpad + t];
+        return r == 0 ? c[0] : r == 1 ? c[T.tpad] : c[2 * T.tpad] - 0.5 * c[T.tpad];
+    };
+    static const int ty[6][2] = {{0, 1}, {0, 2}, {0, 0}, {1, 1}, {2, 2}, {1, 2}};
+    auto eps = [](int y) { return ty[y][0] == 1 || ty[y][1] == 1 ? (ty[y][0] == ty[y][1] ? 1 : -1) : 1; };
+    std::vector<double> cls[4];
+    double big = 0.0;
+    for (int c = 0; c < 4; ++c) {
+        const int par = c < 2 ? 1 : -1, anti = c & 1, K = pair_k(p, rule, c);
+        std::vector<std::pair<int, int>> kap;                       // (type, set) of every contraction row
+        auto enters = [&](int y, int s) { return s < D.npair || eps(y) == par; };
+        for (int y = 0; y < 6; ++y) {
+            if (anti && ty[y][0] == ty[y][1]) continue;
+            for (int x = 0; x < D.sets; ++x)
+                if (enters(y, x)) kap.push_back({y, x});
+        }
+        if ((int)kap.size() != K) throw std::runtime_error("pair tables: contraction length");
+        const int R16 = pair_tiles(p, c) * 16, nrow = pair_rows(p, c);
+        cls[c].assign((size_t)R16 * K, 0.0);
+        for (int o = 0; o < D.rows; ++o)
+            for (int k = 0; k < K; ++k) {
+                const int y = kap[k].first, s = kap[k].second, i = T.ppts[2 * s], j = T.ppts[2 * s + 1];
+                const int r = ty[y][0], q = ty[y][1];
+                auto prod = [&](int at) {
+                    const double u = op(r, at, rows[o].first) * op(q, at, rows[o].second);
+                    if (r == q) return u;
+                    const double v = op(q, at, rows[o].first) * op(r, at, rows[o].second);
+                    return anti ? 0.5 * (u - v) : 0.5 * (u + v);
+                };
+                // half of the sum (odd classes: difference) of the entry and its reflection
+                const double v = i == j ? prod(i) : 0.5 * (prod(i) + par * eps(y) * prod(j));
+                if (o < nrow) cls[c][(size_t)o * K + k] = v;
+                big = std::fmax(big, std::fabs(v));
+            }
+    }
+    T.pair_shift = 13 - (int)std::floor(std::log2(big));
+    const double fs = std::ldexp(1.0, T.pair_shift);
+    // blocks of 16 rows: lane l, value v is row 4 v + l/16 (FP64: values 0, 1 of all lanes,
+    // then 2, 3; FP32: the four values of a lane together); split: two blocks, eight values
+    T.pair64.assign((size_t)pair_off(p, rule, 4, 16) * 256, 0.0);
+    T.pair32.assign(T.pair64.size(), 0.0f);
+    T.pairb.assign((size_t)pair_off(p, rule, 4, 32) * 1024, 0);
+    T.pairh.assign(T.pairb.size(), 0);
+    auto at64 = [](int k, int col) { return (size_t)((k / 8 % 2) * 64 + k % 4 * 16 + col) * 2 + k / 4 % 2; };
+    auto at32 = [](int k, int col) { return (size_t)(k % 4 * 16 + col) * 4 + k / 4 % 4; };
+    for (int c = 0; c < 4; ++c) {
+        const int K = pair_k(p, rule, c);
+        for (int o = 0; o < pair_tiles(p, c) * 16; ++o)
+            for (int k = 0; k < K; ++k) {
+                const double v = cls[c][(size_t)o * K + k];
+                const size_t b16 = pair_off(p, rule, c, 16) + (size_t)(o / 16) * pair_kb(p, rule, c, 16) + k / 16;
+                T.pair64[b16 * 256 + at64(k, o % 16)] = v;
+                T.pair32[b16 * 256 + at32(k, o % 16)] = (float)v;
+                const size_t b32 = pair_off(p, rule, c, 32) + (size_t)(o / 16) * pair_kb(p, rule, c, 32) + k / 32;
+                const size_t at = b32 * 1024 + (size_t)(k % 4 * 16 + o % 16) * 8 + k % 32 / 16 * 4 + k / 4 % 4;
+                const uint16_t h = to_bf16((float)v);
+                T.pairb[at] = h;
+                T.pairb[at + 512] = to_bf16((float)(v - (double)from_bf16(h)));
+                const uint16_t hh = to_f16(v * fs);
+                T.pairh[at] = hh;
+                T.pairh[at + 512] = to_f16(v * fs - from_f16(hh));
+            }
+    }
+    // load vector: rows are the sets (sums, then differences, each padded to blocks of 16)
+    const int hb = (D.sets + 15) / 16, tb = (nt + 15) / 16;
+    T.pbt64.assign((size_t)tb * 2 * hb * 256, 0.0);
+    T.pbt32.assign(T.pbt64.size(), 0.0f);
+    for (int s = 0; s < D.sets; ++s)
+        for (int t = 0; t < nt; ++t) {
+            const int i = T.ppts[2 * s], j = T.ppts[2 * s + 1];
+            for (int par = 0; par < (i == j ? 1 : 2); ++par) {
+                const double v = par ? 0.5 * (op(0, i, t) - op(0, j, t)) : 0.5 * (op(0, i, t) + op(0, j, t));
+                const size_t blk = ((size_t)(t / 16) * 2 * hb + par * hb + s / 16) * 256;
+                T.pbt64[blk + at64(s % 16, t % 16)] = v;
+                T.pbt32[blk + at32(s % 16, t % 16)] = (float)v;
+            }
+        }
+    T.pqw.clear();
+    for (int m = 0; m < nk; ++m)
+        for (int x = 0; x < 2 * D.sets; ++x) {
+            const double *q = &T.qw[4 * ((size_t)m * T.nij + T.ppts[x])];
+            T.pqw.insert(T.pqw.end(), q, q + 4);
+        }
+    // every G is a sum over m of at most one entry times each of L L', L l', l L', l l'
+    T.pair_gz = 0.0;
+    for (int k = 0; k < nk; ++k)
+        for (int q = 0; q < nk; ++q) {
+            double a = 0.0;
+            for (int m = 0; m < nk; ++m) {
+                const double l = std::fabs(T.lam[(size_t)k * nk + m]), dl = std::fabs(T.lam[((size_t)3 * nk + k) * nk + m]);
+                const double u = std::fabs(T.lam[(size_t)q * nk + m]), du = std::fabs(T.lam[((size_t)3 * nk + q) * nk + m]);
+                a += (l + dl) * (u + du);
+            }
+            T.pair_gz = std::fmax(T.pair_gz, a);
+        }
+}
+
 HostTables build_tables(int p, int rule) {
     if (p < 1 || p > kMaxP) throw std::runtime_error("degree out of range");
     if (rule != 0 && rule != 1) throw std::runtime_error("unknown quadrature rule");
@@ -568,6 +711,7 @@ HostTables build_tables(int p, int rule) {
                         T.tauh_lo[o] = to_f16(xs - from_f16(hh));
                     }
     }
+    build_pair_tables(T);
     return T;
 }
 

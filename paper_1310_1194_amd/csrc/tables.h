@@ -47,6 +47,24 @@ struct HostTables {
     // fp16 form's bounds: |Z| <= f16_zc * max |W entry| of the element, and the
     // load vector's zeta sums <= f16_zb * max |w det J f|
     double f16_zc = 0.0, f16_zb = 0.0;
+    // prisms: tables of the products of pairs of triangle functions (classes, orbits
+    // and contraction rows as in pair_dims.h), in blocks of 16 rows x 16 orbits: lane
+    // l, value v holds orbit l%16, row 4 v + l/16.  pair64: [class][tile of 16
+    // orbits][block][values 0 1, 2 3][64][2]; pair32: [class][tile][block][64][4];
+    // pairb / pairh: split into bf16 / fp16 hi and lo, [class][tile][two blocks]
+    // [hi, lo][64][8] (fp16 of the values * 2^pair_shift, the largest in [2^13, 2^14)).
+    std::vector<double> pair64;
+    std::vector<float> pair32;
+    std::vector<uint16_t> pairb, pairh;
+    std::vector<uint32_t> potab;     // [orbits padded to 16]  t, t', reflected t, reflected t', a byte each; all ones past the last
+    std::vector<uint16_t> ppts;      // [sets][2]  triangle points of a reflected pair, twice the same for a fixed point
+    std::vector<double> pqw;         // [line point][sets][2][4]  points of the pairs (xi1, xi2, zeta, w), a fixed point twice
+    // load vector: (T(i) + T(j)) / 2 per set, then (T(i) - T(j)) / 2 (a fixed point: T, 0),
+    // [tile of 16 functions][blocks of 16 sets, sums then differences] as pair64 / pair32
+    std::vector<double> pbt64;
+    std::vector<float> pbt32;
+    int pair_shift = 0;
+    double pair_gz = 0.0;            // |zeta sum G| <= pair_gz * max |entry of the summed point blocks|
     std::vector<double> B64;         // [nqp][4][npad]  rows: phi, d/dxi1, d/dxi2, d/dzeta
     std::vector<float> B32;          // same, rounded to FP32
     std::vector<double> BT64;        // [npad][nqp*4]  transpose of B64 (shape-function major)
