@@ -9,10 +9,20 @@
 //              starts (heaviest degree first), totals of the packed outputs;
 //   k_scatter  per block: stable rank of every element inside its degree,
 //              the permutation into bucket order and the packed offsets;
+// then one of
+//   k_bucket_pair, k_bucket_wave   a launch per degree, heaviest first, over its
+//              bucket (count and start read on the device): the products of
+//              pairs of triangle functions (p = 3..6), the lanes-per-element
+//              kernels below; the default;
 //   k_prep     one lane: work-queue extents for the chosen tile shapes;
 //   k_persist  persistent waves pulling work items (element, tile block)
 //              from an atomic counter, heaviest degree first, each running
 //              the same per-degree device code as the direct kernels.
+// The launches per degree give every kernel its own registers, LDS and workgroup
+// size; k_persist's functions share one budget of a wave per SIMD, and its queue has
+// no workgroup to share G across.  262144 elements: FP32 11.0 ms against 30.4, FP64
+// 19.6 against 65.6; 1024 elements: 0.165 against 0.188, 0.209 against 0.368; at 300
+// elements in FP64 six short launches in a row lose to one (0.195 against 0.161).
 // No memset nodes are used (counters are cleared by kernels), so the whole
 // sequence is safe to capture and replay.
 #include <hip/hip_runtime.h>
@@ -26,6 +36,7 @@
 #include "fwd_kernels.h"
 #include "fwd_valu.h"
 #include "fwd_fact.h"
+#include "fwd_pair.h"
 #include "tables.h"
 
 namespace feint {
@@ -264,7 +275,46 @@ __global__ __launch_bounds__(256, 1) void k_persist(MixedParams mp) {
     }
 }
 
-// One compiled set of per-degree tile shapes.
+// One degree's bucket as a launch of its own.
+__device__ inline bool bucket_params(FwdParams &prm, const MixedHdr *hdr, int d) {
+    prm.ne = hdr->count[d];
+    prm.perm += hdr->bstart[d];
+    return prm.ne > 0;
+}
+template <class K, int MINW>
+__global__ __launch_bounds__(K::NW_ * 64, MINW) void k_bucket_pair(FwdParams prm, const MixedHdr *hdr, int d) {
+    __shared__ typename K::Smem sm;
+    if (bucket_params(prm, hdr, d)) K::run(prm, blockIdx.x, gridDim.x, sm);
+}
+template <class K, int MINW>
+__global__ __launch_bounds__(256, MINW) void k_bucket_wave(FwdParams prm, const MixedHdr *hdr, int d) {
+    __shared__ typename K::Slice sl[4];
+    if (!bucket_params(prm, hdr, d)) return;
+    const int wave = wave_uniform(threadIdx.x >> 6);
+    const int64_t items = items_for<K>(prm.ne);
+    for (int64_t it = (int64_t)blockIdx.x * 4 + wave; it < items; it += (int64_t)gridDim.x * 4)
+        K::run_slice(prm, it / K::NBLK, (int)(it % K::NBLK), sl[wave]);
+}
+struct BucketLaunch {
+    const void *kernel;
+    int threads;
+};
+template <int P, int FORM> BucketLaunch bucket_pair() {
+    typedef PairShape<P, FORM> S;
+    return {(const void *)&k_bucket_pair<KPOf<P, FORM>, S::W>, S::NW * 64};
+}
+template <class K> BucketLaunch bucket_wave() { return {(const void *)&k_bucket_wave<K, 2>, 256}; }
+
+// The launches per degree (index 1..6) of a form.
+const BucketLaunch *bucket_launches(int form) {
+    static const BucketLaunch f64[7] = {{nullptr, 0}, bucket_wave<KV<1, double, 8>>(), bucket_wave<KV<2, double, 18>>(),
+                                        bucket_pair<3, F64>(), bucket_pair<4, F64>(), bucket_pair<5, F64>(), bucket_pair<6, F64>()};
+    static const BucketLaunch f32[7] = {{nullptr, 0}, bucket_wave<KV<1, float, 8>>(), bucket_wave<KV<2, float, 18>>(),
+                                        bucket_pair<3, F32>(), bucket_pair<4, F32>(), bucket_pair<5, F32>(), bucket_pair<6, F32>()};
+    return form == FEINT_FP64 ? f64 : f32;
+}
+
+// One compiled set of per-degree tile shapes (no kernel: the launches per degree).
 struct MixVariant {
     const void *kernel;
     MixSizes sz;
@@ -289,10 +339,11 @@ MixVariant make_variant(const char *desc) {
 }
 
 const MixVariant *mix_variants(int form, int *count) {
-    // p = 1, 2 on the vector ALUs (v8: 8 lanes per element, v18: 18), MFMA tiles above:
+    // first the launches per degree; the persistent sets: p = 1, 2 on the vector ALUs (v8: 8 lanes per element, v18: 18), MFMA tiles above:
     // the contraction per triangle point (KxTNf) or point by point (TMxTN); the last set
     // of each form keeps point-by-point MFMA tiles at every degree for comparison
     static const MixVariant f32[] = {
+        MixVariant{nullptr, MixSizes{}, "v8,v18,0x4f,0x4f,0x4f,0x4f"},
         make_variant<KV<1, float, 8>, KV<2, float, 18>, KF<3, float, 4, 4>, KF<4, float, 5, 3>,
                      KF<5, float, 6, 3>, KF<6, float, 7, 4>>("v8,v18,4x4f,5x3f,6x3f,7x4f"),
         make_variant<KV<1, float, 8>, KV<2, float, 18>, KF<3, float, 4, 4>, KF<4, float, 5, 5>,
@@ -311,6 +362,7 @@ const MixVariant *mix_variants(int form, int *count) {
                      K4<5, float, 8, 2>, K4<6, float, 13, 1>>("1x1,2x2,3x3,5x3,8x2,13x1"),
     };
     static const MixVariant f64[] = {
+        MixVariant{nullptr, MixSizes{}, "v8,v18,0x4f,0x4f,0x4f,0x8f"},
         make_variant<KV<1, double, 8>, KV<2, double, 18>, KF<3, double, 4, 2>, KF<4, double, 5, 5>,
                      KF<5, double, 6, 2>, KF<6, double, 7, 1>>("v8,v18,4x2f,5x5f,6x2f,7x1f"),
         make_variant<KV<1, double, 8>, KV<2, double, 18>, KF<3, double, 4, 2>, KF<4, double, 5, 5>,
@@ -348,6 +400,7 @@ struct feint_mixed_plan {
     int32_t *perm = nullptr;
     int tile = 0;
     int grid[16] = {0};
+    int bgrid[8] = {0};
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -378,6 +431,7 @@ struct MixedWork {
     const DevTables *const *tab;   // [8], degrees 1..6
     int form;
     const int *grid;               // per compiled tile set
+    const int *bgrid;              // [8], of the launches per degree
 };
 
 // Bytes of scratch a batch of ne elements needs: header, block sums, permutation.
@@ -389,7 +443,7 @@ constexpr size_t scratch_bytes(int64_t ne) {
     return SCR_HDR + scratch_blk_bytes(ne) + ((size_t)ne * 4 + 255) / 256 * 256;
 }
 
-MixedWork work_in(char *base, int64_t ne_max, const DevTables *const *tab, int form, const int *grid) {
+MixedWork work_in(char *base, int64_t ne_max, const DevTables *const *tab, int form, const int *grid, const int *bgrid) {
     MixedWork w;
     w.hdr = (MixedHdr *)base;
     w.blk_sums = (int64_t *)(base + SCR_HDR);
@@ -397,6 +451,7 @@ MixedWork work_in(char *base, int64_t ne_max, const DevTables *const *tab, int f
     w.tab = tab;
     w.form = form;
     w.grid = grid;
+    w.bgrid = bgrid;
     return w;
 }
 
@@ -413,11 +468,36 @@ feint_status enqueue_bucket(const MixedWork &w, const int8_t *p, int64_t ne, int
     return e == hipSuccess ? FEINT_OK : hip_fail("bucketing launch", e);
 }
 
+feint_status enqueue_buckets(const MixedWork &w, const feint_elements *el, void *A, void *b, const int64_t *offA,
+                             const int64_t *offb, uint32_t *status, hipStream_t s) {
+    const BucketLaunch *v = bucket_launches(w.form);
+    (void)hipGetLastError();
+    for (int d = MIX_MAXP; d >= 1; --d) {
+        FwdParams prm;
+        fill_fwd_params(prm, el, w.form, w.tab[d]);
+        prm.A = A; prm.b = b; prm.status = status;
+        prm.offA = offA; prm.offb = offb;
+        prm.perm = w.perm;
+        const MixedHdr *hdr = w.hdr;
+        void *args[] = {&prm, &hdr, &d};
+        // at most one workgroup per element has work
+        const int64_t grid = el->ne < w.bgrid[d] ? el->ne : w.bgrid[d];
+        hipError_t e = hipLaunchKernel(v[d].kernel, dim3((unsigned)grid), dim3(v[d].threads), args, 0, s);
+        if (e == hipSuccess) e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail("bucket launch", e);
+    }
+    return FEINT_OK;
+}
+
 feint_status enqueue_persist(const MixedWork &w, const feint_elements *el, void *A, void *b, const int64_t *offA,
                              const int64_t *offb, uint32_t *status, hipStream_t s, int tile) {
     int cnt = 0;
     const MixVariant *vars = mix_variants(w.form, &cnt);
+    // the launches per degree, but for small FP64 batches the first persistent set (measured
+    // at 300 elements: 0.195 against 0.161 ms; at 1024: 0.209 against 0.368)
+    if (!vars[tile].kernel && w.form == FEINT_FP64 && el->ne <= 512) tile = 1;
     const MixVariant &v = vars[tile];
+    if (!vars[tile].kernel) return enqueue_buckets(w, el, A, b, offA, offb, status, s);
     MixedParams mp;
     std::memset(&mp, 0, sizeof mp);
     mp.base.coords = el->coords; mp.base.D = el->D; mp.base.beta = el->beta; mp.base.c = el->c; mp.base.f = el->f;
@@ -444,23 +524,42 @@ feint_status enqueue_persist(const MixedWork &w, const feint_elements *el, void 
     return e == hipSuccess ? FEINT_OK : hip_fail("persistent launch", e);
 }
 
-// Launch grid of every compiled tile set of `form` on device `dev`: as many
-// workgroups as fit the device at once (persistent waves).
-hipError_t persistent_grids(int form, int dev, int *grid) {
-    int cnt = 0, cus = 0;
-    const MixVariant *vars = mix_variants(form, &cnt);
-    if (cnt > 16) return hipErrorInvalidValue;          // grid arrays hold 16 tile sets
-    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    for (int t = 0; t < cnt && e == hipSuccess; ++t) {
-        int nb = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, vars[t].kernel, 256, 0);
-        grid[t] = (nb > 0 ? nb : 1) * cus;
+// Launch grids of the compiled tile sets of a form and of its launches per degree
+// on a device: as many workgroups as fit it at once.  The queries take about
+// 0.3 ms in all, so their answers are kept (they depend on the kernels alone).
+struct Grids {
+    int set[16] = {0}, degree[8] = {0};
+};
+hipError_t persistent_grids(int form, int dev, int *grid, int *bgrid) {
+    static std::mutex mu;
+    static std::map<int, Grids> known;                  // key: device, form
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = known.find(dev * 4 + form);
+    if (it == known.end()) {
+        Grids g;
+        int cnt = 0, cus = 0;
+        const MixVariant *vars = mix_variants(form, &cnt);
+        if (cnt > 16) return hipErrorInvalidValue;      // grid arrays hold 16 tile sets
+        hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        auto fit = [&](const void *kernel, int threads) {
+            int nb = 0;
+            if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, threads, 0);
+            return (nb > 0 ? nb : 1) * cus;
+        };
+        for (int t = 0; t < cnt; ++t)
+            if (vars[t].kernel) g.set[t] = fit(vars[t].kernel, 256);
+        const BucketLaunch *bl = bucket_launches(form);
+        for (int d = 1; d <= MIX_MAXP; ++d) g.degree[d] = fit(bl[d].kernel, bl[d].threads);
+        if (e != hipSuccess) return e;
+        it = known.emplace(dev * 4 + form, g).first;
     }
-    return e;
+    std::memcpy(grid, it->second.set, sizeof it->second.set);
+    std::memcpy(bgrid, it->second.degree, sizeof it->second.degree);
+    return hipSuccess;
 }
 
 MixedWork plan_work(const feint_mixed_plan *pl) {
-    return work_in(pl->scratch, pl->ne_max, pl->tab, pl->form, pl->grid);
+    return work_in(pl->scratch, pl->ne_max, pl->tab, pl->form, pl->grid, pl->bgrid);
 }
 
 // ---- The allocation-free entry point --------------------------------------
@@ -475,6 +574,7 @@ static __device__ __align__(256) unsigned char scratch[scratch_bytes(NOALLOC_MAX
 struct NoAllocDev {
     char *ptr = nullptr;          // device address of `scratch` on this device
     int grid[2][16] = {{0}};      // persistent grid per form (FP64, FP32) and tile set
+    int bgrid[2][8] = {{0}};      // and of the launches per degree
 };
 std::mutex g_na_mu;
 std::map<int, NoAllocDev> g_na;   // key: device
@@ -488,8 +588,8 @@ feint_status noalloc_device(int dev, const NoAllocDev **out) {
         NoAllocDev nd;
         hipError_t e = hipGetSymbolAddress((void **)&nd.ptr, HIP_SYMBOL(scratch));
         if (e != hipSuccess || !nd.ptr) return hip_fail("hipGetSymbolAddress(scratch)", e);
-        e = persistent_grids(FEINT_FP64, dev, nd.grid[0]);
-        if (e == hipSuccess) e = persistent_grids(FEINT_FP32, dev, nd.grid[1]);
+        e = persistent_grids(FEINT_FP64, dev, nd.grid[0], nd.bgrid[0]);
+        if (e == hipSuccess) e = persistent_grids(FEINT_FP32, dev, nd.grid[1], nd.bgrid[1]);
         if (e != hipSuccess) return hip_fail("persistent grid", e);
         it = g_na.emplace(dev, nd).first;
     }
@@ -520,7 +620,7 @@ feint_status feint_mixed_plan_create(int64_t ne_max, feint_form form, feint_mixe
     }
     e = hipMalloc((void **)&pl->scratch, scratch_bytes(ne_max));
     if (e != hipSuccess) { delete pl; return hip_fail("hipMalloc(plan)", e); }
-    e = persistent_grids(form, pl->dev, pl->grid);
+    e = persistent_grids(form, pl->dev, pl->grid, pl->bgrid);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
         (void)hipFree(pl->scratch);
@@ -692,7 +792,7 @@ feint_status feint_integrate_mixed_noalloc(const feint_elements *el, const int8_
     const NoAllocDev *nd = nullptr;
     s = noalloc_device(dev, &nd);
     if (s != FEINT_OK) return s;
-    const MixedWork w = work_in(nd->ptr, NOALLOC_MAX_NE, tab, form, nd->grid[form == FEINT_FP64 ? 0 : 1]);
+    const MixedWork w = work_in(nd->ptr, NOALLOC_MAX_NE, tab, form, nd->grid[form == FEINT_FP64 ? 0 : 1], nd->bgrid[form == FEINT_FP64 ? 0 : 1]);
     const hipStream_t st = (hipStream_t)stream;
     s = enqueue_bucket(w, p, el->ne, offA, offb, dev_status, st);
     if (s != FEINT_OK || el->ne == 0) return s;
