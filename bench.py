@@ -806,7 +806,8 @@ def bench_adjoint(args):
         res[form] = dict(kernel_ms_mean=ms, kernel_ms_min=mn, ms_per_step=wall, elements_per_s=ne / (wall * 1e-3),
                          block=block, tune_ms=tune_ms,
                          fdom_equiv_gflops=costmodel.f_dom(p, rule) * ne / (ms * 1e-3) / 1e9,
-                         gflops_alg=(costmodel.f_adjoint_factored(p, rule) if costmodel.is_kf_tile(block)
+                         gflops_alg=(costmodel.f_adjoint_pair(p, rule) if costmodel.is_pair_tile(block)
+                                     else costmodel.f_adjoint_factored(p, rule) if costmodel.is_kf_tile(block)
                                      else costmodel.f_dom(p, rule)) * ne / (ms * 1e-3) / 1e9,
                          hbm_gbs_algorithmic=ne * costmodel.adjoint_bytes_per_element(p, es) / (ms * 1e-3) / 1e9,
                          grads=[o[torch.from_numpy(sample).to(dev)].cpu().numpy() for o in out])

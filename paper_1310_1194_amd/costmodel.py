@@ -214,6 +214,16 @@ def f_pair(p: int, rule: str = "collapsed") -> int:
     return gemm + zeta + 8 * sizes[0][0] * nk * nk + load
 
 
+def f_adjoint_pair(p: int, rule: str = "collapsed") -> int:
+    """Flops per element of the adjoint through the pair products: eight additions
+    per orbit and column for the classes' values, the transposed products, the
+    zeta sums backwards (13 multiply-adds per triangle point, (k, k') and zeta
+    point), the load vector's sums."""
+    nk, nij = p + 1, nq(p, rule) // (p + 1)
+    sizes = pair_sizes(p, rule)
+    return (sum(2 * r * k for r, k in sizes) + 8 * sizes[0][0]) * nk * nk + 26 * nij * nk ** 3 + 2 * nij * (nshp(p) + nk * nk)
+
+
 def pair_mfma_flops(p: int, rule: str = "collapsed", split: bool = False) -> int:
     """Issued matrix flops per element of the pair products (one product): tiles
     of 16 orbits, blocks of 8 (FP64), 4 (FP32; the last block of 16) or 32 (split

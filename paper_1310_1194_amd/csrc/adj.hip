@@ -40,7 +40,137 @@ struct AdjParams {
     const void *BT;     // [npad][nqp*4]  in the form's precision
     const void *tau;    // triangle factors [nij][4][tpad] and line factors [4][p+1][p+1],
     const void *lamT;   // both in the form's precision
+    // products of pairs of triangle functions (FP64): transposed table, stacked line
+    // products, orbits, points of the reflected pairs
+    const double *padj, *plines, *pqw;
+    const uint32_t *potab;
+    const uint16_t *ppts;
 };
+
+// The chain rule at one point qp = (xi1, xi2, zeta, w): gradients of <W_q, S> +
+// w det J f tau with respect to the element's inputs, added to gr.
+__device__ inline void chain_rule_at(const ElemIn &E, const double *qp, const double S[16], double tau, double gr[32]) {
+    const double xi1 = qp[0], xi2 = qp[1], ze = qp[2], w = qp[3];
+    double K[9];
+    const double det = prism_jacobian(E.X, xi1, xi2, ze, K);
+    const double wd = w * det;
+    double v[3], KD[9], M[9];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        v[i] = K[3 * i] * E.be[0] + K[3 * i + 1] * E.be[1] + K[3 * i + 2] * E.be[2];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            KD[3 * i + j] = K[3 * i] * E.D[j] + K[3 * i + 1] * E.D[3 + j] + K[3 * i + 2] * E.D[6 + j];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            M[3 * i + j] = KD[3 * i] * K[3 * j] + KD[3 * i + 1] * K[3 * j + 1] + KD[3 * i + 2] * K[3 * j + 2];
+    const double s[3] = {S[1], S[2], S[3]};
+    double Sp[9];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) Sp[3 * i + j] = S[4 * (i + 1) + 1 + j];
+    double contr = E.c * S[0];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        contr += v[i] * s[i];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) contr += M[3 * i + j] * Sp[3 * i + j];
+    }
+    const double Lq = wd * (contr + E.f * tau);
+    // gradient slots: vertices 0..17, D 18..26, beta 27..29, c 30, f 31
+    gr[30] += wd * S[0];
+    gr[31] += wd * tau;
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+        gr[27 + m] += wd * (K[m] * s[0] + K[3 + m] * s[1] + K[6 + m] * s[2]);
+    double SK[9];   // S' K
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            SK[3 * i + j] = Sp[3 * i] * K[j] + Sp[3 * i + 1] * K[3 + j] + Sp[3 * i + 2] * K[6 + j];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int n = 0; n < 3; ++n)   // dD_mn = wd sum_k K_km (S'K)_kn
+            gr[18 + 3 * m + n] += wd * (K[m] * SK[n] + K[3 + m] * SK[3 + n] + K[6 + m] * SK[6 + n]);
+    // dL/dK = wd (S' K D^T + S'^T K D + s beta^T)
+    double StK[9], dK[9];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            StK[3 * i + j] = Sp[i] * K[j] + Sp[3 + i] * K[3 + j] + Sp[6 + i] * K[6 + j];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            dK[3 * i + j] = wd * (SK[3 * i] * E.D[3 * j] + SK[3 * i + 1] * E.D[3 * j + 1] + SK[3 * i + 2] * E.D[3 * j + 2]
+                                  + StK[3 * i] * E.D[j] + StK[3 * i + 1] * E.D[3 + j] + StK[3 * i + 2] * E.D[6 + j]
+                                  + s[i] * E.be[j]);
+    // dL/dJ = Lq K^T - K^T dK K^T
+    double KtdK[9], dJ[9];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            KtdK[3 * i + j] = K[i] * dK[j] + K[3 + i] * dK[3 + j] + K[6 + i] * dK[6 + j];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            dJ[3 * i + j] = Lq * K[3 * j + i] - (KtdK[3 * i] * K[3 * j] + KtdK[3 * i + 1] * K[3 * j + 1] + KtdK[3 * i + 2] * K[3 * j + 2]);
+    // J columns: c0 = s(v1-v0)+t(v4-v3), c1 = s(v2-v0)+t(v5-v3), c2 = (l0(v3-v0)+l1(v4-v1)+l2(v5-v2))/2
+    const double t = 0.5 * (1.0 + ze), sb = 0.5 * (1.0 - ze), l0 = 1.0 - xi1 - xi2;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double g0 = dJ[3 * d], g1 = dJ[3 * d + 1], g2 = 0.5 * dJ[3 * d + 2];
+        gr[0 + d] += -sb * g0 - sb * g1 - l0 * g2;
+        gr[3 + d] += sb * g0 - xi1 * g2;
+        gr[6 + d] += sb * g1 - xi2 * g2;
+        gr[9 + d] += -t * g0 - t * g1 + l0 * g2;
+        gr[12 + d] += t * g0 + xi1 * g2;
+        gr[15 + d] += t * g1 + xi2 * g2;
+    }
+}
+
+// Sum the lanes' 32 partial gradients over the wave by recursive halving:
+// at each step a lane keeps half of its values and adds the partner's copy
+// of that half.  Lanes 2c and 2c+1 end with component c.
+__device__ inline double reduce_scatter32(double v[32], int lane) {
+    double w16[16], w8[8], w4[4], w2[2];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const bool up = lane & 32;
+        const double keep = up ? v[j + 16] : v[j], send = up ? v[j] : v[j + 16];
+        w16[j] = keep + __shfl_xor(send, 32, 64);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const bool up = lane & 16;
+        const double keep = up ? w16[j + 8] : w16[j], send = up ? w16[j] : w16[j + 8];
+        w8[j] = keep + __shfl_xor(send, 16, 64);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const bool up = lane & 8;
+        const double keep = up ? w8[j + 4] : w8[j], send = up ? w8[j] : w8[j + 4];
+        w4[j] = keep + __shfl_xor(send, 8, 64);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const bool up = lane & 4;
+        const double keep = up ? w4[j + 2] : w4[j], send = up ? w4[j] : w4[j + 2];
+        w2[j] = keep + __shfl_xor(send, 4, 64);
+    }
+    const bool up = lane & 2;
+    double r = (up ? w2[1] : w2[0]) + __shfl_xor(up ? w2[0] : w2[1], 2, 64);
+    return r + __shfl_xor(r, 1, 64);
+}
 
 template <int P, typename T, int TA, int TB, int R = 0>
 struct Adj {
@@ -55,133 +185,13 @@ struct Adj {
 
     __device__ static void chain_rule(const AdjParams &prm, const ElemIn &E, int q, const double S[16],
                                       bool with_load, int64_t e, double gr[32]) {
-        const double *qp = prm.qw + 4 * q;
-        const double xi1 = qp[0], xi2 = qp[1], ze = qp[2], w = qp[3];
-        double K[9];
-        const double det = prism_jacobian(E.X, xi1, xi2, ze, K);
-        const double wd = w * det;
         double tau = 0.0;
         if (with_load) {
             const T *gv = (const T *)prm.g + e * N;
             const double *phi = prm.B64 + (size_t)q * 4 * NP;
             for (int a = 0; a < N; ++a) tau += (double)gv[a] * phi[a];
         }
-        double v[3], KD[9], M[9];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            v[i] = K[3 * i] * E.be[0] + K[3 * i + 1] * E.be[1] + K[3 * i + 2] * E.be[2];
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                KD[3 * i + j] = K[3 * i] * E.D[j] + K[3 * i + 1] * E.D[3 + j] + K[3 * i + 2] * E.D[6 + j];
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                M[3 * i + j] = KD[3 * i] * K[3 * j] + KD[3 * i + 1] * K[3 * j + 1] + KD[3 * i + 2] * K[3 * j + 2];
-        const double s[3] = {S[1], S[2], S[3]};
-        double Sp[9];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) Sp[3 * i + j] = S[4 * (i + 1) + 1 + j];
-        double contr = E.c * S[0];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            contr += v[i] * s[i];
-#pragma unroll
-            for (int j = 0; j < 3; ++j) contr += M[3 * i + j] * Sp[3 * i + j];
-        }
-        const double Lq = wd * (contr + E.f * tau);
-        // gradient slots: vertices 0..17, D 18..26, beta 27..29, c 30, f 31
-        gr[30] += wd * S[0];
-        gr[31] += wd * tau;
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-            gr[27 + m] += wd * (K[m] * s[0] + K[3 + m] * s[1] + K[6 + m] * s[2]);
-        double SK[9];   // S' K
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                SK[3 * i + j] = Sp[3 * i] * K[j] + Sp[3 * i + 1] * K[3 + j] + Sp[3 * i + 2] * K[6 + j];
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-#pragma unroll
-            for (int n = 0; n < 3; ++n)   // dD_mn = wd sum_k K_km (S'K)_kn
-                gr[18 + 3 * m + n] += wd * (K[m] * SK[n] + K[3 + m] * SK[3 + n] + K[6 + m] * SK[6 + n]);
-        // dL/dK = wd (S' K D^T + S'^T K D + s beta^T)
-        double StK[9], dK[9];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                StK[3 * i + j] = Sp[i] * K[j] + Sp[3 + i] * K[3 + j] + Sp[6 + i] * K[6 + j];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                dK[3 * i + j] = wd * (SK[3 * i] * E.D[3 * j] + SK[3 * i + 1] * E.D[3 * j + 1] + SK[3 * i + 2] * E.D[3 * j + 2]
-                                      + StK[3 * i] * E.D[j] + StK[3 * i + 1] * E.D[3 + j] + StK[3 * i + 2] * E.D[6 + j]
-                                      + s[i] * E.be[j]);
-        // dL/dJ = Lq K^T - K^T dK K^T
-        double KtdK[9], dJ[9];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                KtdK[3 * i + j] = K[i] * dK[j] + K[3 + i] * dK[3 + j] + K[6 + i] * dK[6 + j];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                dJ[3 * i + j] = Lq * K[3 * j + i] - (KtdK[3 * i] * K[3 * j] + KtdK[3 * i + 1] * K[3 * j + 1] + KtdK[3 * i + 2] * K[3 * j + 2]);
-        // J columns: c0 = s(v1-v0)+t(v4-v3), c1 = s(v2-v0)+t(v5-v3), c2 = (l0(v3-v0)+l1(v4-v1)+l2(v5-v2))/2
-        const double t = 0.5 * (1.0 + ze), sb = 0.5 * (1.0 - ze), l0 = 1.0 - xi1 - xi2;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double g0 = dJ[3 * d], g1 = dJ[3 * d + 1], g2 = 0.5 * dJ[3 * d + 2];
-            gr[0 + d] += -sb * g0 - sb * g1 - l0 * g2;
-            gr[3 + d] += sb * g0 - xi1 * g2;
-            gr[6 + d] += sb * g1 - xi2 * g2;
-            gr[9 + d] += -t * g0 - t * g1 + l0 * g2;
-            gr[12 + d] += t * g0 + xi1 * g2;
-            gr[15 + d] += t * g1 + xi2 * g2;
-        }
-    }
-
-    // Sum the lanes' 32 partial gradients over the wave by recursive halving:
-    // at each step a lane keeps half of its values and adds the partner's copy
-    // of that half.  Lanes 2c and 2c+1 end with component c.
-    __device__ static double reduce_scatter32(double v[32], int lane) {
-        double w16[16], w8[8], w4[4], w2[2];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const bool up = lane & 32;
-            const double keep = up ? v[j + 16] : v[j], send = up ? v[j] : v[j + 16];
-            w16[j] = keep + __shfl_xor(send, 32, 64);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const bool up = lane & 16;
-            const double keep = up ? w16[j + 8] : w16[j], send = up ? w16[j] : w16[j + 8];
-            w8[j] = keep + __shfl_xor(send, 16, 64);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool up = lane & 8;
-            const double keep = up ? w8[j + 4] : w8[j], send = up ? w8[j] : w8[j + 4];
-            w4[j] = keep + __shfl_xor(send, 8, 64);
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const bool up = lane & 4;
-            const double keep = up ? w4[j + 2] : w4[j], send = up ? w4[j] : w4[j + 2];
-            w2[j] = keep + __shfl_xor(send, 4, 64);
-        }
-        const bool up = lane & 2;
-        double r = (up ? w2[1] : w2[0]) + __shfl_xor(up ? w2[0] : w2[1], 2, 64);
-        return r + __shfl_xor(r, 1, 64);
+        chain_rule_at(E, prm.qw + 4 * q, S, tau, gr);
     }
 
     __device__ static void run(const AdjParams &prm, int64_t e, int blk, int wave, Smem &sm) {
@@ -425,7 +435,7 @@ struct KFA {
                     for (int k = 0; k < 16; ++k) S[k] = sm.S[wave][lane][k];
                     Base::chain_rule(prm, E, q, S, with_load, e, gr);
                 }
-                gacc += Base::reduce_scatter32(gr, lane);
+                gacc += reduce_scatter32(gr, lane);
             }
             wave_sync();
         }
@@ -569,7 +579,7 @@ struct KFA2 {
                     for (int k = 0; k < 16; ++k) S[k] = sm.S[el][q][k];
                     Base::chain_rule(prm, E, q, S, true, e, gr);
                 }
-                gacc += Base::reduce_scatter32(gr, lane);
+                gacc += reduce_scatter32(gr, lane);
             }
             if ((lane & 1) == 0) sm.red[wave][lane >> 1] = gacc;
         }
@@ -588,6 +598,10 @@ struct KFA2 {
         }
     }
 };
+
+}  // namespace feint
+#include "adj_pair.h"
+namespace feint {
 
 template <class KER, int MINW = 1>
 __global__ __launch_bounds__(256, MINW) void adj_direct(AdjParams prm) {
@@ -639,6 +653,14 @@ feint_status launch_adj_coop(const AdjParams &prm, hipStream_t s) {
     return FEINT_OK;
 }
 
+template <class K, int MINW>
+feint_status launch_adj_pair(const AdjParams &prm, hipStream_t s) {
+    const int64_t blocks = (prm.ne + K::NW / K::WPE_ - 1) / (K::NW / K::WPE_);
+    if (blocks > 0x7fffffffLL) return FEINT_ERR_TOO_LARGE;
+    hipLaunchKernelGGL((adj_pair<K, MINW>), dim3((unsigned)blocks), dim3(K::NTHR), 0, s, prm);
+    return FEINT_OK;
+}
+
 // Compiled block shapes (TA x TB 16x16 tiles of G per wave, or for the
 // factorised kernel TK row indices k by TB column tiles) per degree and
 // quadrature rule (the same shapes for both rules, so one choice per (degree,
@@ -649,8 +671,10 @@ struct AdjVariant {
     feint_status (*launch)(const AdjParams &, hipStream_t);
     int fact;           // 1: factorised along zeta (KFA, TA = row indices k, TB = column tiles),
                         // 2: the same with a two-waves-per-SIMD register budget, 3 (4): the same with
-                        // the chain rule shared by the waves of an element (KFA2; 4 at two waves per SIMD)
+                        // the chain rule shared by the waves of an element (KFA2; 4 at two waves per SIMD),
+                        // 5: products of pairs of triangle functions (ta = 0, tb = waves per element; FP64)
 };
+#define FEINT_ADJP(P, WPE, EPW, W) AdjVariant{0, WPE, &launch_adj_pair<AdjPair<P, R, WPE, EPW>, W>, 5}
 #define FEINT_ADJ(P, T, TA, TB) AdjVariant{TA, TB, &launch_adj<Adj<P, T, TA, TB, R>>, 0}
 #define FEINT_ADJF(P, T, TK, TB) AdjVariant{TK, TB, &launch_adj<KFA<P, T, TK, TB, R>>, 1}
 #define FEINT_ADJF2(P, T, TK, TB) AdjVariant{TK, TB, &launch_adj<KFA<P, T, TK, TB, R>, 2>, 2}
@@ -661,42 +685,47 @@ template <typename T, int R>
 const AdjVariant *adj_variants_of(int p, int *count) {
     static const AdjVariant v1[] = {FEINT_ADJ(1, T, 1, 1), FEINT_ADJF(1, T, 2, 2)};
     static const AdjVariant v2[] = {FEINT_ADJ(2, T, 2, 2), FEINT_ADJ(2, T, 2, 1), FEINT_ADJF(2, T, 3, 3)};
-    // from p = 3 the factorised kernel ("f", "fo2" with two waves per SIMD) first, in the
+    // FP64 from p = 3 first the products of pairs of triangle functions (adj_pair.h; "0xWf",
+    // W waves per element), faster at every batch size there; else, from p = 3, the
+    // factorised kernel ("f", "fo2" with two waves per SIMD) first, in the
     // order measured per form (131072 elements at p = 3 and 4, 16384 at p = 5 and 7); the
     // same shapes for both forms; from p = 5 the one with the chain rule shared by the waves
     // of an element ("fw") first (p = 7: 1.4x FP64, 2.0x FP32), and in FP32 at p = 3 (two
     // waves per element, 1.1x); FP64 at p = 3 level, at p = 4 slower
-    static const AdjVariant v3d[] = {FEINT_ADJF2(3, T, 4, 2), FEINT_ADJ(3, T, 3, 3), FEINT_ADJF(3, T, 4, 2),
+    static const AdjVariant v3d[] = {FEINT_ADJP(3, 2, 1, 3), FEINT_ADJF2(3, T, 4, 2), FEINT_ADJ(3, T, 3, 3), FEINT_ADJF(3, T, 4, 2),
                                      FEINT_ADJF(3, T, 4, 4), FEINT_ADJ(3, T, 3, 1), FEINT_ADJ(3, T, 3, 2),
                                      FEINT_ADJF2(3, T, 4, 1), FEINT_ADJW2(3, T, 4, 2)};
     static const AdjVariant v3f[] = {FEINT_ADJW2(3, T, 4, 2), FEINT_ADJF2(3, T, 4, 2), FEINT_ADJF(3, T, 4, 4),
                                      FEINT_ADJF(3, T, 4, 2), FEINT_ADJ(3, T, 3, 3), FEINT_ADJ(3, T, 3, 1),
                                      FEINT_ADJ(3, T, 3, 2), FEINT_ADJF2(3, T, 4, 1)};
+    static const AdjVariant v4d[] = {FEINT_ADJP(4, 2, 1, 2), FEINT_ADJF2(4, T, 5, 1), FEINT_ADJF(4, T, 5, 1), FEINT_ADJF(4, T, 5, 2),
+                                     FEINT_ADJ(4, T, 5, 2), FEINT_ADJ(4, T, 5, 1), FEINT_ADJ(4, T, 3, 3),
+                                     FEINT_ADJW(4, T, 5, 1)};
     static const AdjVariant v4[] = {FEINT_ADJF2(4, T, 5, 1), FEINT_ADJF(4, T, 5, 1), FEINT_ADJF(4, T, 5, 2),
                                     FEINT_ADJ(4, T, 5, 2), FEINT_ADJ(4, T, 5, 1), FEINT_ADJ(4, T, 3, 3),
                                     FEINT_ADJW(4, T, 5, 1)};
-    static const AdjVariant v5d[] = {FEINT_ADJW(5, T, 6, 1), FEINT_ADJF(5, T, 6, 2), FEINT_ADJF(5, T, 6, 1), FEINT_ADJ(5, T, 8, 2),
+    static const AdjVariant v5d[] = {FEINT_ADJP(5, 4, 1, 2), FEINT_ADJW(5, T, 6, 1), FEINT_ADJF(5, T, 6, 2), FEINT_ADJF(5, T, 6, 1), FEINT_ADJ(5, T, 8, 2),
                                      FEINT_ADJ(5, T, 4, 2), FEINT_ADJ(5, T, 8, 1)};
     static const AdjVariant v5f[] = {FEINT_ADJW(5, T, 6, 1), FEINT_ADJF(5, T, 6, 1), FEINT_ADJF(5, T, 6, 2), FEINT_ADJ(5, T, 8, 2),
                                      FEINT_ADJ(5, T, 4, 2), FEINT_ADJ(5, T, 8, 1)};
     static const AdjVariant v6[] = {FEINT_ADJW(6, T, 7, 1), FEINT_ADJF(6, T, 7, 1), FEINT_ADJF(6, T, 4, 2), FEINT_ADJ(6, T, 7, 2),
                                     FEINT_ADJ(6, T, 7, 1), FEINT_ADJ(6, T, 13, 1)};
-    static const AdjVariant v7d[] = {FEINT_ADJW(7, T, 8, 1), FEINT_ADJF(7, T, 8, 1), FEINT_ADJF(7, T, 4, 2), FEINT_ADJ(7, T, 6, 3),
+    static const AdjVariant v6d[] = {FEINT_ADJP(6, 8, 1, 2), FEINT_ADJW(6, T, 7, 1), FEINT_ADJF(6, T, 7, 1), FEINT_ADJF(6, T, 4, 2), FEINT_ADJ(6, T, 7, 2),
+                                     FEINT_ADJ(6, T, 7, 1), FEINT_ADJ(6, T, 13, 1)};
+    static const AdjVariant v7d[] = {FEINT_ADJP(7, 8, 1, 2), FEINT_ADJW(7, T, 8, 1), FEINT_ADJF(7, T, 8, 1), FEINT_ADJF(7, T, 4, 2), FEINT_ADJ(7, T, 6, 3),
                                      FEINT_ADJ(7, T, 9, 2), FEINT_ADJ(7, T, 6, 2), FEINT_ADJ(7, T, 9, 1)};
     static const AdjVariant v7f[] = {FEINT_ADJW(7, T, 8, 1), FEINT_ADJF(7, T, 8, 1), FEINT_ADJF(7, T, 4, 2), FEINT_ADJ(7, T, 6, 2),
                                      FEINT_ADJ(7, T, 9, 2), FEINT_ADJ(7, T, 6, 3), FEINT_ADJ(7, T, 9, 1)};
-    static_assert(sizeof v3d == sizeof v3f && sizeof v5d == sizeof v5f && sizeof v7d == sizeof v7f,
-                  "one count per degree for both forms");
     const bool f64 = sizeof(T) == 8;
 #define FEINT_AN(a) *count = (int)(sizeof(a) / sizeof(a[0])); return a
     switch (p) {
     case 1: FEINT_AN(v1);
     case 2: FEINT_AN(v2);
-    case 3: *count = (int)(sizeof(v3d) / sizeof(v3d[0])); return f64 ? v3d : v3f;
-    case 4: FEINT_AN(v4);
-    case 5: *count = (int)(sizeof(v5d) / sizeof(v5d[0])); return f64 ? v5d : v5f;
-    case 6: FEINT_AN(v6);
-    case 7: *count = (int)(sizeof(v7d) / sizeof(v7d[0])); return f64 ? v7d : v7f;
+    case 3: if (f64) { FEINT_AN(v3d); } FEINT_AN(v3f);
+    case 4: if (f64) { FEINT_AN(v4d); } FEINT_AN(v4);
+    case 5: if (f64) { FEINT_AN(v5d); } FEINT_AN(v5f);
+    case 6: if (f64) { FEINT_AN(v6d); } FEINT_AN(v6);
+    case 7: if (f64) { FEINT_AN(v7d); } FEINT_AN(v7f);
     }
 #undef FEINT_AN
     *count = 0;
@@ -742,6 +771,7 @@ feint_status adj_setup(const feint_elements *el, int p, feint_form form, const v
     prm.qw = T->qw; prm.B64 = T->B64;
     prm.BT = form == FEINT_FP64 ? (const void *)T->BT64 : (const void *)T->BT32;
     prm.tau = form == FEINT_FP64 ? (const void *)T->tau64 : (const void *)T->tau32;
+    prm.padj = T->padj; prm.plines = T->plines; prm.pqw = T->pqw; prm.potab = T->potab; prm.ppts = T->ppts;
     prm.lamT = form == FEINT_FP64 ? (const void *)T->lam : (const void *)T->lam32;
     return FEINT_OK;
 }
@@ -812,7 +842,7 @@ feint_status feint_adjoint_tile_describe(int p, feint_form form, int tile, char 
     const AdjVariant *v = adj_variants(form, p, &cnt);
     if (!buf || len == 0 || tile < 0 || tile >= cnt) return FEINT_ERR_INVALID_ARG;
     std::snprintf(buf, len, "%dx%d%s%s", v[tile].ta, v[tile].tb,
-                  v[tile].fact >= 3 ? "fw" : v[tile].fact ? "f" : "", v[tile].fact == 2 || v[tile].fact == 4 ? "o2" : "");
+                  v[tile].fact == 5 ? "f" : v[tile].fact >= 3 ? "fw" : v[tile].fact ? "f" : "", v[tile].fact == 2 || v[tile].fact == 4 ? "o2" : "");
     return FEINT_OK;
 }
 

@@ -64,9 +64,10 @@ feint_status prepare_tables(int p, int rule, int type) {
     const size_t s_m64 = align(H.Mref.size() * 8), s_m32 = align(H.Mref32.size() * 4);
     const size_t s_tb = align(H.taub_hi.size() * 2);
     const size_t s_p64 = align(H.pair64.size() * 8), s_p32 = align(H.pair32.size() * 4), s_pb = align(H.pairb.size() * 2);
-    const size_t s_po = align(H.potab.size() * 4), s_pp = align(H.ppts.size() * 2), s_pt = align(H.pbt64.size() * 8), s_pq = align(H.pqw.size() * 8);
+    const size_t s_po = align(H.potab.size() * 4), s_pp = align(H.ppts.size() * 2), s_pt = align(H.pbt64.size() * 8), s_pq = align(H.pqw.size() * 8),
+                 s_pa = align(H.padj.size() * 8), s_pl = align(H.plines.size() * 8);
     const size_t total = s_tau + s_tau32 + s_lam + s_lam32 + s_qw + s_gll + 2 * s_b64 + 3 * s_b32 + 4 * s_sp + s_ycf +
-                         s_m64 + s_m32 + 4 * s_tb + s_p64 + s_p32 + 2 * s_pb + s_po + s_pp + 2 * s_pt + s_pq;
+                         s_m64 + s_m32 + 4 * s_tb + s_p64 + s_p32 + 2 * s_pb + s_po + s_pp + 2 * s_pt + s_pq + s_pa + s_pl;
     char *base = nullptr;
     e = hipMalloc((void **)&base, total);
     if (e != hipSuccess) { set_error("hipMalloc(tables)", e); return FEINT_ERR_HIP; }
@@ -115,6 +116,8 @@ feint_status prepare_tables(int p, int rule, int type) {
     T->pbt64 = (const double *)put(H.pbt64.data(), H.pbt64.size() * 8, s_pt);
     T->pbt32 = (const float *)put(H.pbt32.data(), H.pbt32.size() * 4, s_pt);
     T->pqw = (const double *)put(H.pqw.data(), H.pqw.size() * 8, s_pq);
+    T->padj = (const double *)put(H.padj.data(), H.padj.size() * 8, s_pa);
+    T->plines = (const double *)put(H.plines.data(), H.plines.size() * 8, s_pl);
     T->pair_shift = H.pair_shift;
     T->pair_gz = (float)H.pair_gz;
     T->tau_f16_shift = H.tau_f16_shift;

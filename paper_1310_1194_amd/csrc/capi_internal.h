@@ -24,7 +24,7 @@ struct DevTables {
     const uint16_t *taubh, *taubl, *tauhh, *tauhl;
     int tau_f16_shift;
     float f16_zc, f16_zb;
-    const double *pair64, *pbt64, *pqw;
+    const double *pair64, *pbt64, *pqw, *padj, *plines;
     const float *pair32, *pbt32;
     const uint16_t *pairb, *pairh, *ppts;
     const uint32_t *potab;

@@ -481,14 +481,19 @@ void build_pair_tables(HostTables &T) {
     // orbits of the pairs (t, t'), in the order of pair_dims.h
     std::vector<std::pair<int, int>> orb[5];
     std::vector<char> seen((size_t)nt * nt, 0);
-    for (int a = 0; a < nt; ++a)
-        for (int b = 0; b < nt; ++b) {
-            if (seen[a * nt + b]) continue;
-            const int im[4] = {a * nt + b, b * nt + a, st[a] * nt + st[b], st[b] * nt + st[a]};
-            for (int x : im) seen[x] = 1;
-            const bool fa = st[a] == a, fb = st[b] == b;
-            orb[fa && fb ? (a == b ? 4 : 3) : a == b ? 1 : b == st[a] ? 2 : 0].push_back({a, b});
-        }
+    // patch by patch of (t, t'): the adjoint reads an orbit's four entries from rows t and t' of
+    // dL/dA, 16 orbits at a time, so neighbours in both directions share lines
+    constexpr int PA = 8, PB = 4;
+    for (int a0 = 0; a0 < nt; a0 += PA)
+        for (int b0 = 0; b0 < nt; b0 += PB)
+            for (int a = a0; a < nt && a < a0 + PA; ++a)
+                for (int b = b0; b < nt && b < b0 + PB; ++b) {
+                    if (seen[a * nt + b]) continue;
+                    const int im[4] = {a * nt + b, b * nt + a, st[a] * nt + st[b], st[b] * nt + st[a]};
+                    for (int x : im) seen[x] = 1;
+                    const bool fa = st[a] == a, fb = st[b] == b;
+                    orb[fa && fb ? (a == b ? 4 : 3) : a == b ? 1 : b == st[a] ? 2 : 0].push_back({a, b});
+                }
     std::vector<std::pair<int, int>> rows;
     for (auto &o : orb) rows.insert(rows.end(), o.begin(), o.end());
     if ((int)rows.size() != D.rows || (int)orb[0].size() != D.nfull) throw std::runtime_error("pair tables: orbits");
@@ -576,6 +581,34 @@ void build_pair_tables(HostTables &T) {
                 T.pbt32[blk + at32(s % 16, t % 16)] = (float)v;
             }
         }
+    // adjoint
+    for (int c = 0; c < 4; ++c) {
+        const int K = pair_k(p, rule, c), ob = pair_tiles(p, c) * 2, kt = (K + 15) / 16;
+        const size_t base = T.padj.size();
+        T.padj.resize(base + (size_t)kt * ob * 128, 0.0);
+        for (int o = 0; o < pair_rows(p, c); ++o) {
+            const int a = rows[o].first, b = rows[o].second;
+            int im[4] = {a * nt + b, b * nt + a, st[a] * nt + st[b], st[b] * nt + st[a]}, size = 0;
+            for (int x = 0; x < 4; ++x) {
+                bool first = true;
+                for (int y = 0; y < x; ++y) first = first && im[y] != im[x];
+                size += first;
+            }
+            for (int k = 0; k < K; ++k)
+                T.padj[base + (((size_t)(k / 16) * ob + o / 8) * 64 + o % 4 * 16 + k % 16) * 2 + o % 8 / 4] =
+                    0.25 * size * cls[c][(size_t)o * K + k];
+        }
+    }
+    const int stack = 16 / nk < 4 ? 16 / nk : 4, nset = (4 + stack - 1) / stack, ct = (nk * nk + 15) / 16;
+    T.plines.assign((size_t)nset * ct * 256, 0.0);
+    for (int q = 0; q < nset; ++q)
+        for (int col = 0; col < nk * nk; ++col)
+            for (int row = 0; row < stack * nk; ++row) {
+                const int d = q * stack + row / nk, m = row % nk, k = col / nk, kp = col % nk;
+                if (d > 3) continue;
+                const double x = T.lam[((size_t)(d >= 2 ? 3 : 0) * nk + k) * nk + m], y = T.lam[((size_t)(d % 2 ? 3 : 0) * nk + kp) * nk + m];
+                T.plines[(((size_t)q * ct + col / 16) * 4 + col % 16 / 4) * 64 + col % 4 * 16 + row] = x * y;
+            }
     T.pqw.clear();
     for (int m = 0; m < nk; ++m)
         for (int x = 0; x < 2 * D.sets; ++x) {

@@ -59,6 +59,11 @@ struct HostTables {
     std::vector<uint32_t> potab;     // [orbits padded to 16]  t, t', reflected t, reflected t', a byte each; all ones past the last
     std::vector<uint16_t> ppts;      // [sets][2]  triangle points of a reflected pair, twice the same for a fixed point
     std::vector<double> pqw;         // [line point][sets][2][4]  points of the pairs (xi1, xi2, zeta, w), a fixed point twice
+    // adjoint (FP64): the transposed classes, each row times a quarter of its orbit's size,
+    // [class][tile of 16 contraction rows][8 orbits][64 lanes][2], lane l, value v = contraction
+    // row l%16, orbit 4 v + l/16; line products, [set of types][16 columns][4][64]: lane l of
+    // step r holds row l%16 = (type, zeta point) at column 4 r + l/16, types L L', L l', l L', l l'
+    std::vector<double> padj, plines;
     // load vector: (T(i) + T(j)) / 2 per set, then (T(i) - T(j)) / 2 (a fixed point: T, 0),
     // [tile of 16 functions][blocks of 16 sets, sums then differences] as pair64 / pair32
     std::vector<double> pbt64;
