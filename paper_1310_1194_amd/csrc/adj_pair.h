@@ -298,7 +298,9 @@ struct AdjPair {
                     double tau = 0.0;
 #pragma unroll
                     for (int k = 0; k < NK; ++k) tau += ((const double *)prm.lamT)[k * NK + m] * sm.u[el][ij * NK + k];
-                    chain_rule_at(E, prm.pqw + 4 * task, Sq, tau, gr);
+                    const double *pt = prm.pqw + 4 * task;
+                    const double qp[4] = {pt[0], pt[1], pt[2], set < NPAIR ? pt[3] : 2.0 * pt[3]};
+                    chain_rule_at(E, qp, Sq, tau, gr);
                 }
                 gacc += reduce_scatter32(gr, lane);
             }

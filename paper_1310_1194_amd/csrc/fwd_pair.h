@@ -24,15 +24,23 @@
 // padding of 36 functions to 48), 4x at p = 5, 2x at p = 4, and none is spent on
 // forming operands from the table.
 // Bound by the matrix cores in FP64 at p = 7 (58 % of an element's time in the
-// products, which then run at their peak rate), elsewhere by the phases that do
-// not overlap with them.  Collapsed rule, ms, the best other kernel -> this one
+// products, which then run at their peak rate), elsewhere by the latency of an
+// element's phases, which overlap only with other workgroups' (p = 4: a quarter
+// fewer workgroups per CU leave each phase as long as it was).  What shortened them:
+// the table's first steps fetched before the barrier and PD steps ahead, what an
+// element's first phases read held in LDS (a global load there waits for the
+// stores of the element before), places and E rows looked up instead of formed,
+// A stored in 16-byte pieces: p = 4 bf16x3 1.77 -> 1.57 ms, p = 5 FP32 1.86 -> 1.59,
+// p = 7 bf16x3 2.88 -> 2.06.
+// Collapsed rule, ms, the best other kernel -> this one
 // (131072 elements at p = 3, 4, 32768 at p = 5, 16384 at p = 6, 7):
-//   FP64    p = 3 1.80 -> 1.09, 4 4.83 -> 4.13, 5 7.19 -> 3.31, 6 7.15 -> 4.83, 7 21.8 -> 8.39
-//   FP32    p = 3 0.98 -> 0.61, 4 2.93 -> 2.45, 5 3.86 -> 1.86, 6 5.06 -> 2.70, 7 12.4 -> 4.76
-//   bf16x3  p = 2 0.83 -> 0.71, 3 1.41 -> 0.63, 4 2.67 -> 1.89, 5 2.56 -> 1.58, 6 2.76 -> 2.09, 7 6.44 -> 2.88
-//   fp16x3  p = 2 1.00 -> 0.99, 3 1.42 -> 1.01, 4 2.78 -> 2.46, 5 3.18 -> 2.00, 6 3.76 -> 2.24, 7 7.31 -> 3.37
-// At p = 2 in FP64 and FP32 the kernel of lanes per element is faster (0.86
-// against 1.17 ms, 0.56 against 0.70 on 262144 elements) and this one is not compiled.
+//   FP64    p = 3 1.80 -> 0.91, 4 4.83 -> 3.91, 5 7.19 -> 3.05, 6 7.15 -> 4.59, 7 21.8 -> 8.31
+//   FP32    p = 3 0.98 -> 0.52, 4 2.93 -> 2.20, 5 3.86 -> 1.59, 6 5.06 -> 2.32, 7 12.4 -> 4.28
+//   bf16x3  p = 2 0.83 -> 0.60, 3 1.41 -> 0.51, 4 2.67 -> 1.65, 5 2.56 -> 1.02, 6 2.76 -> 1.29, 7 6.44 -> 2.06
+//   fp16x3  p = 2 1.00 -> 0.90, 3 1.42 -> 0.71, 4 2.78 -> 2.29, 5 3.18 -> 1.19, 6 3.76 -> 1.67, 7 7.31 -> 2.34
+// and at every smaller batch (one element: p = 7 FP64 0.13 against 0.40, p = 4 0.015
+// against 0.025).  At p = 2 in FP64 and FP32 the kernel of lanes per element is faster (0.81
+// against 0.97 ms, 0.55 against 0.59 on 262144 elements) and this one is not compiled.
 // Errors against 64 bits are no larger in any form (FP32 p = 7 1.9e-7, was 3.1e-7;
 // bf16x3 p = 4 2.3e-6, was 4.3e-6): fewer terms are summed per entry.
 #pragma once
@@ -62,28 +70,66 @@ __device__ inline int phase_tid() {
     return t;
 }
 
-// An element's inputs as staged in LDS: vertices, then D, beta, c, f of the
-// element or of its six vertices.
+// A value that no kernel in flight writes, at a uniform address: read through the
+// scalar cache.  (A vector load in one branch makes the compiler wait, where the
+// branches meet, for every vector memory operation before it, stores of A included.)
+template <class I> __device__ inline I uniform_load(const I *p) {
+    return *(const __attribute__((address_space(4))) I *)(uintptr_t)p;
+}
+__device__ inline int64_t pair_elem(const FwdParams &prm, int64_t slot) {
+    return prm.perm ? (int64_t)uniform_load(prm.perm + slot) : slot;
+}
+
+// An element's inputs as staged in LDS: the edge vectors v1-v0, v2-v0, v4-v3, v5-v3,
+// v3-v0, v4-v1, v5-v2, then D, beta, c, f of the element or of its six vertices.
+// A value is fetched as two numbers whose difference is staged, so that nothing
+// waits for the loads before the store.
+__device__ inline double2 pair_edge(const FwdParams &prm, int64_t e, int i) {
+    const int edge = i / 3, d = i - 3 * edge, hi = 0x5435421 >> (4 * edge) & 7, lo = 0x2103300 >> (4 * edge) & 7;
+    const double *x = prm.coords + 18 * e + d;
+    return {x[3 * hi], x[3 * lo]};
+}
+// The Jacobian's cofactor rows in the operators o, e and d/dzeta; returns det J.
+__device__ inline double pair_cofactors(const double *in, const double *pt, double co[3], double ce[3], double cz[3]) {
+    const double t = 0.5 * (1.0 + pt[2]), s = 0.5 * (1.0 - pt[2]);
+    const double h0 = 0.5 * (1.0 - pt[0] - pt[1]), h1 = 0.5 * pt[0], h2 = 0.5 * pt[1];
+    double a[3], b[3], c[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        a[d] = s * in[d] + t * in[6 + d];
+        b[d] = s * in[3 + d] + t * in[9 + d];
+        c[d] = h0 * in[12 + d] + h1 * in[15 + d] + h2 * in[18 + d];
+    }
+    co[0] = b[1] * c[2] - b[2] * c[1]; co[1] = b[2] * c[0] - b[0] * c[2]; co[2] = b[0] * c[1] - b[1] * c[0];
+    ce[0] = c[1] * a[2] - c[2] * a[1]; ce[1] = c[2] * a[0] - c[0] * a[2]; ce[2] = c[0] * a[1] - c[1] * a[0];
+    cz[0] = a[1] * b[2] - a[2] * b[1]; cz[1] = a[2] * b[0] - a[0] * b[2]; cz[2] = a[0] * b[1] - a[1] * b[0];
+    const double det = a[0] * co[0] + a[1] * co[1] + a[2] * co[2];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) co[d] += 0.5 * ce[d];       // d/dxi1 = o, d/dxi2 = e + o / 2
+    return det;
+}
+// Entries of W_q at a point, in the operators 0, o, e and 3 = d/dzeta:
+// 0o o3 3o, 0e e3 3e, 00 03 33, oo, ee, oe+eo, oe-eo, and w det J f.
+// With C = det J K the cofactors, w det J K D K^T = (w / det J) C D C^T: K is not formed.
+constexpr int PAIR_ENTRIES = 14;
 template <class Geo> struct PairInputs {
-    static constexpr int MAX = 18 + 6 * 14;
-    __device__ static int count(const FwdParams &prm) { return prm.fD ? MAX : 32; }
-    __device__ static double fetch(const FwdParams &prm, int64_t e, int i) {
-        if (i < 18) return prm.coords[18 * e + i];
-        i -= 18;
+    static constexpr int EDGES = 21, MAX = EDGES + 6 * 14;
+    __device__ static int count(const FwdParams &prm) { return prm.fD ? MAX : EDGES + 14; }
+    __device__ static double2 fetch(const FwdParams &prm, int64_t e, int i) {
+        if (i < EDGES) return pair_edge(prm, e, i);
+        i -= EDGES;
         if (prm.fD)
-            return i < 54 ? prm.fD[54 * e + i] : i < 72 ? prm.fbeta[18 * e + i - 54] : i < 78 ? prm.fc[6 * e + i - 72] : prm.ff[6 * e + i - 78];
-        return i < 9 ? prm.D[9 * e + i] : i < 12 ? prm.beta[3 * e + i - 9] : i < 13 ? prm.c[e] : prm.f[e];
+            return {i < 54 ? prm.fD[54 * e + i] : i < 72 ? prm.fbeta[18 * e + i - 54] : i < 78 ? prm.fc[6 * e + i - 72] : prm.ff[6 * e + i - 78], 0.0};
+        return {i < 9 ? prm.D[9 * e + i] : i < 12 ? prm.beta[3 * e + i - 9] : i < 13 ? prm.c[e] : prm.f[e], 0.0};
     }
     struct Coef { double D[9], be[3], c, f; };
-    // W_q and w det J f at a point; returns det J.  The coefficients are read once
-    // the vertices are done with (both at once cost 28 more registers).
-    __device__ static double block(const FwdParams &prm, const double *in, const double *pt, double W[16], double &sf) {
-        double X[18], K[9];
-#pragma unroll
-        for (int i = 0; i < 18; ++i) X[i] = in[i];
-        const double det = prism_jacobian(X, pt[0], pt[1], pt[2], K);
+    // Returns det J.  The coefficients are read once the edges are done with (both at
+    // once cost 28 more registers).
+    __device__ static double block(const FwdParams &prm, const double *in, const double *pt, double v[PAIR_ENTRIES]) {
+        double co[3], ce[3], cz[3];
+        const double det = pair_cofactors(in, pt, co, ce, cz);
         __builtin_amdgcn_sched_barrier(0);
-        in += 18;
+        in += EDGES;
         Coef E;
         if (!prm.fD) {
 #pragma unroll
@@ -111,21 +157,40 @@ template <class Geo> struct PairInputs {
                 E.f += Na * in[78 + a];
             }
         }
-        fused_block(E, K, pt[3] * det, W, sf);
+        const double w = pt[3], wd = w * det, q = w / det;
+        v[6] = wd * E.c;
+        v[13] = wd * E.f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) E.be[d] *= w;
+        auto dot = [](const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; };
+        v[0] = dot(co, E.be); v[3] = dot(ce, E.be); v[7] = dot(cz, E.be);
+        auto times_D = [&](const double *a, double m[3]) {
+            const double x = q * a[0], y = q * a[1], z = q * a[2];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) m[d] = x * E.D[d] + y * E.D[3 + d] + z * E.D[6 + d];
+        };
+        double mo[3], me[3], mz[3];
+        times_D(co, mo); times_D(ce, me); times_D(cz, mz);
+        v[1] = dot(mo, cz); v[2] = dot(mz, co); v[4] = dot(me, cz); v[5] = dot(mz, ce); v[8] = dot(mz, cz);
+        v[9] = dot(mo, co); v[10] = dot(me, ce);
+        const double oe = dot(mo, ce), eo = dot(me, co);
+        v[11] = oe + eo; v[12] = oe - eo;
         return det;
     }
 };
 template <> struct PairInputs<PrismLaplaceGeo> {
-    static constexpr int MAX = 18;
-    __device__ static int count(const FwdParams &) { return 18; }
-    __device__ static double fetch(const FwdParams &prm, int64_t e, int i) { return prm.coords[18 * e + i]; }
-    __device__ static double block(const FwdParams &, const double *in, const double *pt, double W[16], double &sf) {
-        double X[18], K[9];
-#pragma unroll
-        for (int i = 0; i < 18; ++i) X[i] = in[i];
-        const double det = prism_jacobian(X, pt[0], pt[1], pt[2], K);
-        laplace_block(K, pt[3] * det, W);
-        sf = 0.0;
+    static constexpr int EDGES = 21, MAX = EDGES;
+    __device__ static int count(const FwdParams &) { return EDGES; }
+    __device__ static double2 fetch(const FwdParams &prm, int64_t e, int i) { return pair_edge(prm, e, i); }
+    __device__ static double block(const FwdParams &, const double *in, const double *pt, double v[PAIR_ENTRIES]) {
+        double co[3], ce[3], cz[3];
+        const double det = pair_cofactors(in, pt, co, ce, cz), q = pt[3] / det;
+        auto dot = [](const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; };
+        v[0] = v[3] = v[6] = v[7] = v[12] = v[13] = 0.0;
+        const double so[3] = {q * co[0], q * co[1], q * co[2]}, sz[3] = {q * cz[0], q * cz[1], q * cz[2]};
+        const double se[3] = {q * ce[0], q * ce[1], q * ce[2]};
+        v[1] = v[2] = dot(so, cz); v[4] = v[5] = dot(se, cz); v[8] = dot(sz, cz);
+        v[9] = dot(so, co); v[10] = dot(se, ce); v[11] = 2.0 * dot(so, ce);
         return det;
     }
 };
@@ -151,14 +216,15 @@ struct KP {
     static constexpr int NCOL = EPB * KPP * NK, CT = c_cdiv(NCOL, 16);
     static constexpr int WC = NW / WT, CTW = CT / WC;
     static constexpr int TPW = c_cdiv(pair_tiles(P, 0), WT);
-    static constexpr int NE = 14;                             // rows of E: 13 entries of W and w det J f
+    static constexpr int NE = PAIR_ENTRIES;                   // rows of E
     static constexpr int NS = N % 2 ? N : N + 1;              // row of the LDS copy of A: an odd stride spreads the banks
     static_assert(N == c_nshp(P) && CTW * WC == CT && NW % WT == 0, "pair kernel shape");
+    static_assert(NS != N || EPB == 1, "one copy of A with unpadded rows");
     static_assert(EPB == 1 || (PASSES == 1 && NK * NK <= 16 && EPB * NK <= 16), "several elements: one pass, a column tile each");
     static constexpr int kb(int cls) { return pair_kb(P, R, cls, GK); }
     static constexpr int mx(int a, int b) { return a > b ? a : b; }
-    // LDS, in bytes: G of the symmetric and antisymmetric class, E, the load
-    // vector's zeta sums; the copy of A lies over what is no longer read
+    // LDS, in bytes: G of the symmetric and antisymmetric class, E; the load vector's
+    // zeta sums and the copy of A lie over what is no longer read
     static constexpr int GB = 16 * (int)sizeof(T);            // bytes per contraction row and column tile
     // rows of a class in LDS: whole blocks, in FP64 half blocks
     static constexpr int gr(int cls) { return FORM == F64 ? (pair_k(P, R, cls) + 7) / 8 * 8 : kb(cls) * GK; }
@@ -167,49 +233,59 @@ struct KP {
     static constexpr int GAOFF = SC ? 0 : GS;
     static constexpr int EB = (EPB * 2 * NE * NK * S * (int)sizeof(T) + 15) / 16 * 16;
     static constexpr int HT = c_cdiv(S, 16);                  // blocks of 16 sets
-    static constexpr int HB = Geo::LOAD ? 2 * HT * 256 * (int)sizeof(T) : 0;
-    static constexpr int ST = EPB * KS * NT * NS * (int)sizeof(T);
+    static constexpr int HC = EPB * NK;                       // columns of the load vector's sums
+    static constexpr int EP = EPB * (NE - 1) * NK * S;        // E of a parity; w det J f of both follows
+    static_assert(2 * HT * 16 * HC <= EP, "the load vector's sums lie over the even E");
+    static constexpr int VW = 16 / (int)sizeof(T);            // values of a 16-byte store
+    static constexpr int ST = (EPB * KS * NT * NS + (NS == N ? VW : 0)) * (int)sizeof(T);
+    static constexpr int ZR = 16 * (c_cdiv(pair_k(P, R, 0), 16) + c_cdiv(pair_k(P, R, 1), 16) + c_cdiv(pair_k(P, R, 2), 16) + c_cdiv(pair_k(P, R, 3), 16));
     static constexpr int EOFF = PASSES == 1 ? GALL : mx(GALL, (ST + 15) / 16 * 16);
-    static constexpr int HOFF = EOFF + EB;
-    static constexpr int LDS = mx(HOFF + HB, ST);
+    static constexpr int LDS = mx(EOFF + EB, ST);
     struct alignas(16) Smem {
         char raw[(LDS + 15) / 16 * 16];
         double in[EPB][In::MAX];
+        uint2 place[pair_rows(P, 0)];                         // where an orbit's entries lie in the copy of A
+        double tri[2 * S][3], line[NK][2];                    // points: xi1, xi2, weight; zeta, weight
+        T lam[2][NK * NK];                                    // line factors and their derivatives
+        uint16_t zrow[ZR];                                    // contraction rows: place in E, kind
         uint32_t wmax[EPB];                                   // fp16: bits of the largest |E| of the element
     };
 
+    // Element of slot0 + el, el varying over the lanes.
+    __device__ static int64_t element(const FwdParams &prm, int64_t slot0, int el) {
+        if (EPB == 1) return pair_elem(prm, slot0);
+        if (!prm.perm) return slot0 + el;
+        int e = uniform_load(prm.perm + slot0);
+#pragma unroll
+        for (int i = 1; i < EPB; ++i) {
+            const int x = uniform_load(prm.perm + (slot0 + i < prm.ne ? slot0 + i : slot0));
+            e = el == i ? x : e;
+        }
+        return e;
+    }
     // ---- inputs ------------------------------------------------------------------
     static constexpr int NF = c_cdiv(EPB * In::MAX, NTHR);    // values fetched per thread
-    __device__ static void fetch(const FwdParams &prm, int64_t slot0, double (&v)[NF]) {
+    __device__ static void fetch(const FwdParams &prm, int64_t slot0, double2 (&v)[NF]) {
         const int tid = phase_tid();
         const int cnt = In::count(prm);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             const int x = tid + f * NTHR, el = EPB == 1 ? 0 : x / cnt;
-            if (el < EPB && x < EPB * cnt && slot0 + el < prm.ne) v[f] = In::fetch(prm, elem_of(prm, slot0 + el), x - el * cnt);
+            if (el < EPB && x < EPB * cnt && slot0 + el < prm.ne) v[f] = In::fetch(prm, element(prm, slot0, el), x - el * cnt);
         }
     }
-    __device__ static void store_inputs(const FwdParams &prm, const double (&v)[NF], Smem &sm) {
+    __device__ static void store_inputs(const FwdParams &prm, const double2 (&v)[NF], Smem &sm) {
         const int tid = phase_tid();
         const int cnt = In::count(prm);
+        __builtin_amdgcn_s_waitcnt(0x0F70);                   // the loads, for every path from here on
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             const int x = tid + f * NTHR, el = EPB == 1 ? 0 : x / cnt;
-            if (el < EPB && x < EPB * cnt) sm.in[el][x - el * cnt] = v[f];
+            if (el < EPB && x < EPB * cnt) sm.in[el][x - el * cnt] = v[f].x - v[f].y;
         }
     }
 
     // ---- 1: E ------------------------------------------------------------------
-    // entries of E: 0o o3 3o, 0e e3 3e, 00 03 33, oo, ee, oe+eo, oe-eo, w det J f
-    __device__ static void entries(const double W[16], double sf, double v[NE]) {
-        // operators o = d1, e = d2 - d1/2: row o is W[1] + W[2]/2, likewise the columns
-        const double r11 = W[5] + 0.5 * W[9], r12 = W[6] + 0.5 * W[10], e1 = W[9] + 0.5 * W[10];
-        v[0] = W[1] + 0.5 * W[2]; v[1] = W[7] + 0.5 * W[11]; v[2] = W[13] + 0.5 * W[14];
-        v[3] = W[2]; v[4] = W[11]; v[5] = W[14];
-        v[6] = W[0]; v[7] = W[3]; v[8] = W[15];
-        v[9] = r11 + 0.5 * r12; v[10] = W[10]; v[11] = r12 + e1; v[12] = r12 - e1;
-        v[13] = sf;
-    }
     static constexpr bool odd_entry(int x) { return x <= 2 || x == 11 || x == 12; }     // types 0o and oe
 
     // One point per lane, the two points of a pair in neighbouring lanes (both
@@ -225,32 +301,34 @@ struct KP {
             const bool live = task < EPB * TASKS && slot0 + el0 < prm.ne;
             const int el = live ? el0 : 0, rest = live ? task - el0 * TASKS : 0;
             const int m = rest / (2 * S), set = (rest - m * 2 * S) >> 1, side = rest & 1;
-            const double *qp = prm.pqw + 4 * rest;
-            const double pt[4] = {qp[0], qp[1], qp[2], qp[3]};
-            double W[16], sf, v[NE];
-            const double det = In::block(prm, sm.in[el], pt, W, sf);
+            const double *tp = sm.tri[rest - m * 2 * S];
+            const double pt[4] = {tp[0], tp[1], sm.line[m][0], tp[2] * sm.line[m][1]};
+            double v[NE];
+            const double det = In::block(prm, sm.in[el], pt, v);
             if (live && !(det > 0.0) && prm.status) atomicOr(prm.status, 1u);
             if (live && prm.xq) {
-                const int64_t e = elem_of(prm, slot0 + el);
+                const int64_t e = element(prm, slot0, el);
                 const int q = m * NIJ + prm.ppts[2 * set + side];
                 double x[3];
-                prism_map(sm.in[el], pt[0], pt[1], pt[2], x);
+                prism_map(prm.coords + 18 * e, pt[0], pt[1], pt[2], x);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) prm.xq[(e * NQ + q) * 3 + c] = x[c];
             }
-            entries(W, sf, v);
             // even classes (row 0, written by side 0) take the sums of the entries even under
             // the reflection and the differences of the odd ones, odd classes (row 1, side 1) the
-            // others; a fixed point its entries
-            const bool fixed = set >= NPAIR;
-            T *row = E + ((el * 2 + side) * NE * NK + m) * S + set;
+            // others; a fixed point is its own partner with half its weight
+            const double sg = side == 0 ? 1.0 : -1.0;
+            T *row = E + side * EP + (el * (NE - 1) * NK + m) * S + set;
             float big = 0.0f;
 #pragma unroll
             for (int x = 0; x < NE; ++x) {
-                const double o = lane_swap(v[x]);
-                const double y = fixed ? v[x] : side == 0 ? (odd_entry(x) ? v[x] - o : v[x] + o) : (odd_entry(x) ? o + v[x] : o - v[x]);
+                const double o = lane_swap(v[x]), y = odd_entry(x) ? fma(-sg, o, v[x]) : fma(sg, v[x], o);
                 if (FORM == FP16X3 && x < 13) big = fmaxf(big, fabsf((float)y));
-                if (live) row[x * NK * S] = (T)y;
+                if (x < NE - 1) {
+                    if (live) row[x * NK * S] = (T)y;
+                } else if (Geo::LOAD && live) {
+                    E[2 * EP + ((side * EPB + el) * NK + m) * S + set] = (T)y;
+                }
             }
             if (FORM == FP16X3 && live) atomicMax(&sm.wmax[el], __float_as_uint(big));
         }
@@ -263,10 +341,59 @@ struct KP {
     // G is kept in blocks of 16 rows as the zeta products leave them in registers:
     // lane (g, n), value v is row 4 v + g of column n, which is the second operand
     // of the products' step v (the split forms take two blocks per step).
-    // At: offset of lane (g, column c) in a class's first block.
-    __device__ static int column_at(int c, int rows) {
-        const int g4 = (phase_tid() & 63) >> 4;
-        return (c >> 4) * rows * 16 + (g4 * 16 + (c & 15)) * (SPLIT ? 8 : FORM == F64 ? 2 : 4);
+    // At: offset of this lane's values of element el, column tile j, in a class's first block.
+    static constexpr int GV = SPLIT ? 8 : FORM == F64 ? 2 : 4;
+    __device__ static int column_at(int el, int j, int rows, int lane) {
+        if constexpr (EPB == 1) return j * rows * 16 + lane * GV;
+        const int c = el * NK * NK + (lane & 15);
+        return (c >> 4) * rows * 16 + ((lane & 48) + (c & 15)) * GV;
+    }
+    // Row of a lane of a tile: its set, and the first x of its entries of E.
+    static constexpr int zoff(int cls) { return cls == 0 ? 0 : zoff(cls - 1) + 16 * c_cdiv(pair_k(P, R, cls - 1), 16); }
+    template <int CLS> __device__ static void zeta_rows(Smem &sm) {
+        constexpr int PAR = CLS / 2;
+        constexpr bool SYM = CLS % 2 == 0;
+        constexpr int N0 = rows_of(PAR, 0), N1 = rows_of(PAR, 1), N2 = rows_of(PAR, 2), N3 = rows_of(PAR, 3), N4 = rows_of(PAR, 4);
+        constexpr int K = pair_k(P, R, CLS), Z = zoff(CLS);
+        for (int i = threadIdx.x; i < c_cdiv(K, 16) * 16; i += NTHR) {
+            const int i16 = i & 15, r = FORM == F64 ? i : (i & ~15) + 4 * (i16 & 3) + (i16 >> 2);
+            int set = r < K ? r : K - 1, x = 0;
+            if (set >= N0) { set -= N0; x = 3; }
+            if (x == 3 && set >= N1) { set -= N1; x = SYM ? 6 : 12; }
+            if (x == 6 && set >= N2) { set -= N2; x = 9; }
+            if (x == 9 && set >= N3) { set -= N3; x = 10; }
+            if (x == 10 && set >= N4) { set -= N4; x = 11; }
+            sm.zrow[Z + i] = (uint16_t)((x * NK * S + set) | (x < 9 ? 0x4000 : 0) | (x == 6 ? 0x8000 : 0));
+        }
+    }
+    // What the loop over elements reads unchanged.
+    __device__ static void start(const FwdParams &prm, Smem &sm) {
+        static_assert(NE * NK * S < 0x4000, "places in E");
+        static_for<0, 4>([&](auto c) { zeta_rows<decltype(c)::value>(sm); });
+        for (int i = threadIdx.x; i < pair_rows(P, 0); i += NTHR) {
+            const uint32_t w = prm.potab[i], t = w & 0xFF, u = w >> 8 & 0xFF, rt = w >> 16 & 0xFF, ru = w >> 24;
+            static_assert(NT * NS * PLACE <= 0x10000, "places in the copy of A");
+            sm.place[i] = uint2{(t * NS + u) * PLACE | (u * NS + t) * PLACE << 16, (rt * NS + ru) * PLACE | (ru * NS + rt) * PLACE << 16};
+        }
+        // the points' weights are products of a triangle's and a line's
+        for (int i = threadIdx.x; i < 2 * S; i += NTHR) {
+            sm.tri[i][0] = prm.pqw[4 * i]; sm.tri[i][1] = prm.pqw[4 * i + 1]; sm.tri[i][2] = prm.pqw[4 * i + 3];
+        }
+        if (threadIdx.x < NK) {
+            const double *q = prm.pqw + 4 * 2 * S * threadIdx.x;
+            sm.line[threadIdx.x][0] = q[2];
+            sm.line[threadIdx.x][1] = q[3] / prm.pqw[3];
+        }
+        const T *lam = sizeof(T) == 8 ? (const T *)(const void *)prm.lam : (const T *)(const void *)prm.lam32;
+        for (int i = threadIdx.x; i < NK * NK; i += NTHR) {
+            sm.lam[0][i] = lam[i];
+            sm.lam[1][i] = lam[3 * NK * NK + i];
+        }
+        if (FORM == FP16X3 && threadIdx.x < EPB) sm.wmax[threadIdx.x] = 0;
+    }
+    static constexpr int PLACE = sizeof(T) == 8 ? 1 : 4;      // unit of a place: value, byte
+    __device__ static T &placed(T *at, uint32_t place) {
+        return sizeof(T) == 8 ? at[place] : *(T *)((char *)at + place);
     }
     template <int CLS> __device__ static void put(char *g, int at, int tile, V4 v, float sc) {
         constexpr int KB = kb(CLS), TILES = c_cdiv(pair_k(P, R, CLS), 16);
@@ -300,20 +427,19 @@ struct KP {
     static constexpr int KZ = c_cdiv(NK, 4);
     static constexpr int CTE = EPB == 1 ? CT : 1;
     struct Lines { T ll[KZ], ld[KZ], dl[KZ], dd[KZ]; };
-    __device__ static void load_lines(const FwdParams &prm, int col0, Lines &l) {
-        const T *lam = sizeof(T) == 8 ? (const T *)(const void *)prm.lam : (const T *)(const void *)prm.lam32;
+    __device__ static void load_lines(const Smem &sm, int col0, Lines &l) {
         const int lane = phase_tid() & 63, c = col0 + (lane & 15), cc = c < NK * NK ? c : 0, k = cc / NK, kp = cc - k * NK;
 #pragma unroll
         for (int s = 0; s < KZ; ++s) {
             const int m = 4 * s + (lane >> 4), mm = m < NK ? m : 0;
             const T on = m < NK ? (T)1 : (T)0;
-            const T a = on * lam[k * NK + mm], da = on * lam[(3 * NK + k) * NK + mm], b = lam[kp * NK + mm], db = lam[(3 * NK + kp) * NK + mm];
+            const T a = on * sm.lam[0][k * NK + mm], da = on * sm.lam[1][k * NK + mm], b = sm.lam[0][kp * NK + mm], db = sm.lam[1][kp * NK + mm];
             l.ll[s] = a * b; l.ld[s] = a * db; l.dl[s] = da * b; l.dd[s] = da * db;
         }
     }
-    __device__ static void lines(const FwdParams &prm, int k0, Lines (&l)[CTE]) {
+    __device__ static void lines(const Smem &sm, int k0, Lines (&l)[CTE]) {
 #pragma unroll
-        for (int j = 0; j < CTE; ++j) load_lines(prm, k0 * NK + j * 16, l[j]);
+        for (int j = 0; j < CTE; ++j) load_lines(sm, k0 * NK + j * 16, l[j]);
     }
     // A task is a tile of 16 contraction rows for every column tile of one element:
     // its rows of E are read once.
@@ -326,6 +452,7 @@ struct KP {
         // tiles of 16 rows: those of 0o and 0e alone serve both classes
         constexpr int BOTH = SYM && ANTI ? N1 / 16 : 0, TS = SYM ? c_cdiv(KS0, 16) : 0, TA = ANTI ? c_cdiv(KS1, 16) : 0;
         constexpr int TT = BOTH + (SYM ? TS - BOTH : 0) + (ANTI ? TA - BOTH : 0);
+        constexpr int Z0 = zoff(C0), Z1 = zoff(C1);
         char *gs = sm.raw, *ga = sm.raw + GAOFF;
         const int tid = phase_tid(), lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
         float sc = FORM == FP16X3 && EPB == 1 ? scale(prm, sm, 0) : 1.0f;
@@ -335,21 +462,12 @@ struct KP {
             if (FORM == FP16X3 && EPB > 1) sc = scale(prm, sm, el);
             const bool sym = SYM && task < TS, anti = ANTI && (task < BOTH || !sym);
             const int tile = sym ? task : task - (SYM ? TS - BOTH : 0);
-            // the row of this lane, its first entry x and its set
-            const int last = sym ? KS0 - 1 : KS1 - 1, r0 = tile * 16 + 4 * (i16 & 3) + (i16 >> 2);
-            int set = FORM == F64 ? tile * 16 + i16 : r0, x = 0;
-            set = set < last ? set : last;
-            if (set >= N0) { set -= N0; x = 3; }
-            if (x == 3 && set >= N1 - N0) { set -= N1 - N0; x = sym ? 6 : 12; }
-            if (SYM) {
-                if (x == 6 && set >= N2 - N1) { set -= N2 - N1; x = 9; }
-                if (x == 9 && set >= N3 - N2) { set -= N3 - N2; x = 10; }
-                if (x == 10 && set >= N4 - N3) { set -= N4 - N3; x = 11; }
-            }
-            const T *E = (const T *)(sm.raw + EOFF) + ((el * 2 + PAR) * NE + x) * NK * S + set;
+            const uint32_t zr = sm.zrow[(sym ? Z0 : Z1) + tile * 16 + i16];
+            const bool x9 = zr & 0x4000, x6 = zr & 0x8000;
+            const T *E = (const T *)(sm.raw + EOFF) + PAR * EP + el * (NE - 1) * NK * S + (zr & 0x3FFF);
             auto at = [&](int d, int s) {
                 const int m = 4 * s + g4;
-                return E[(d * NK + (m < NK ? m : NK - 1)) * S];
+                return E[(m < NK ? m : NK - 1) * S + d * NK * S];
             };
             // which products the tile's rows take: those of 0o and 0e (L l', l L') and of 00 (L l', l l');
             // each kind is straight-line code, with independent chains of products
@@ -362,8 +480,8 @@ struct KP {
                     a0[s] = at(0, s);
                     if (MX || ZX) {
                         const T u = at(1, s), w = at(2, s);
-                        a1[s] = x < 9 ? u : (T)0;
-                        a2[s] = x < 9 ? w : (T)0;
+                        a1[s] = x9 ? u : (T)0;
+                        a2[s] = x9 ? w : (T)0;
                     }
                 }
                 V4 p[CTE], q[CTE], w[CTE];
@@ -379,20 +497,19 @@ struct KP {
                     }
                     if (MX) {
 #pragma unroll
-                        for (int j = 0; j < CTE; ++j) w[j] = mfma4(ZX && x == 6 ? (T)0 : a2[s], l[j].dl[s], w[j]);
+                        for (int j = 0; j < CTE; ++j) w[j] = mfma4(ZX && x6 ? (T)0 : a2[s], l[j].dl[s], w[j]);
                     }
                     if (ZX) {
 #pragma unroll
-                        for (int j = 0; j < CTE; ++j) w[j] = mfma4(MX && x != 6 ? (T)0 : a2[s], l[j].dd[s], w[j]);
+                        for (int j = 0; j < CTE; ++j) w[j] = mfma4(MX && !x6 ? (T)0 : a2[s], l[j].dd[s], w[j]);
                     }
                 }
 #pragma unroll
                 for (int j = 0; j < CTE; ++j) {
                     if (MX || ZX) p[j] += w[j];
-                    const int c = EPB == 1 ? j * 16 + i16 : el * NK * NK + i16;
                     if (EPB == 1 || i16 < NK * NK) {
-                        if (sym) put<C0>(gs, column_at(c, gr(C0)), tile, MX || ZX ? p[j] + q[j] : p[j], sc);
-                        if (anti) put<C1>(ga, column_at(c, gr(C1)), tile, MX || ZX ? p[j] - q[j] : p[j], sc);
+                        if (sym) put<C0>(gs, column_at(el, j, gr(C0), lane), tile, MX || ZX ? p[j] + q[j] : p[j], sc);
+                        if (anti) put<C1>(ga, column_at(el, j, gr(C1), lane), tile, MX || ZX ? p[j] - q[j] : p[j], sc);
                     }
                 }
             };
@@ -401,34 +518,34 @@ struct KP {
             else if (mixed) form(ic<1>{}, ic<1>{});
             else form(ic<0>{}, ic<1>{});
         }
-        if (Geo::LOAD && SYM && k0 == 0) load_sums<PAR>(prm, sm);
+        if (Geo::LOAD && SYM && PAR == 1 && k0 + KPP >= NK) load_sums(sm);
     }
 
     // ---- load vector ------------------------------------------------------------
     // b[(k,t)] = sum over the sets of T(t) H(k), H = sum_m L_k w det J f, by halves
     // for the sum and the difference of a pair of points; both sums on the matrix
     // cores, the columns being k of every element.
-    template <int PAR> __device__ static void load_sums(const FwdParams &prm, Smem &sm) {
-        T *H = (T *)(sm.raw + HOFF);
-        const T *lam = sizeof(T) == 8 ? (const T *)(const void *)prm.lam : (const T *)(const void *)prm.lam32;
+    // Taken when the even E is no longer read: they lie over it.
+    __device__ static void load_sums(Smem &sm) {
+        T *H = (T *)(sm.raw + EOFF);
         const int tid = phase_tid(), lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
 #pragma unroll 1
-        for (int id = NW - 1 - wave_uniform(tid >> 6); id < EPB * HT; id += NW) {
-            const int el = id / HT, tile = id - el * HT, k = i16 < NK ? i16 : 0;
+        for (int id = NW - 1 - wave_uniform(tid >> 6); id < 2 * EPB * HT; id += NW) {
+            const int par = id / (EPB * HT), el = id / HT - par * EPB, tile = id % HT, k = i16 < NK ? i16 : 0;
             const int row = tile * 16 + (FORM == F64 ? i16 : 4 * (i16 & 3) + (i16 >> 2)), set = row < S ? row : S - 1;
-            const T *E = (const T *)(sm.raw + EOFF) + ((el * 2 + PAR) * NE + 13) * NK * S + set;
+            const T *E = (const T *)(sm.raw + EOFF) + 2 * EP + (par * EPB + el) * NK * S + set;
             V4 p = {0, 0, 0, 0};
 #pragma unroll
             for (int s = 0; s < KZ; ++s) {
                 const int m = 4 * s + g4, mm = m < NK ? m : 0;
-                const T lk = m < NK ? lam[k * NK + mm] : (T)0;
+                const T lk = m < NK ? sm.lam[0][k * NK + mm] : (T)0;
                 p = mfma4(E[mm * S], lk, p);
             }
             if (i16 < NK) {
-                T *q = H + (PAR * HT + tile) * 256 + (g4 * 16 + el * NK + i16) * (FORM == F64 ? 2 : 4);
+                T *q = H + (par * HT + tile) * 16 * HC + (g4 * HC + el * NK + i16) * (FORM == F64 ? 2 : 4);
                 if constexpr (FORM == F64) {
                     *(V2 *)q = V2{p[0], p[1]};
-                    *(V2 *)(q + 128) = V2{p[2], p[3]};
+                    *(V2 *)(q + 8 * HC) = V2{p[2], p[3]};
                 } else {
                     *(V4 *)q = p;
                 }
@@ -436,9 +553,9 @@ struct KP {
         }
     }
     __device__ static void load_vector(const FwdParams &prm, int64_t slot0, int wave, Smem &sm) {
-        const T *H = (const T *)(sm.raw + HOFF);
+        const T *H = (const T *)(sm.raw + EOFF);
         const T *bt = sizeof(T) == 8 ? (const T *)(const void *)prm.pbt64 : (const T *)(const void *)prm.pbt32;
-        const int lane = phase_tid() & 63, i16 = lane & 15;
+        const int lane = phase_tid() & 63, i16 = lane & 15, hl = (lane >> 4) * HC + (i16 < HC ? i16 : 0);
 #pragma unroll 1
         for (int tile = NW - 1 - wave; tile < c_cdiv(NT, 16); tile += NW) {
             V4 v = {0, 0, 0, 0};
@@ -448,19 +565,20 @@ struct KP {
                 if constexpr (FORM == F64) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const V2 x = *(const V2 *)(A + (2 * b + h) * 128 + 2 * lane), y = *(const V2 *)(H + (2 * b + h) * 128 + 2 * lane);
+                        const V2 x = *(const V2 *)(A + (2 * b + h) * 128 + 2 * lane), y = *(const V2 *)(H + (2 * b + h) * 8 * HC + 2 * hl);
                         v = mfma4(x[0], y[0], v);
                         v = mfma4(x[1], y[1], v);
                     }
                 } else {
-                    const V4 x = *(const V4 *)(A + b * 256 + 4 * lane), y = *(const V4 *)(H + b * 256 + 4 * lane);
+                    const V4 x = *(const V4 *)(A + b * 256 + 4 * lane), y = *(const V4 *)(H + b * 16 * HC + 4 * hl);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) v = mfma4(x[u], y[u], v);
                 }
             }
             const int el = i16 / NK, k = i16 - el * NK;
             if (el >= EPB || slot0 + el >= prm.ne) continue;
-            T *bo = (T *)prm.b + offb_of(prm, elem_of(prm, slot0 + el), N) + k * NT;
+            const int64_t e = element(prm, slot0, el);
+            T *bo = (T *)prm.b + (EPB == 1 && prm.offb ? uniform_load(prm.offb + e) : offb_of(prm, e, N)) + k * NT;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int t = tile * 16 + acc_row<T>(lane, r);
@@ -470,85 +588,115 @@ struct KP {
     }
 
     // ---- 3: products ------------------------------------------------------------
+    // The table's first steps of a class are fetched before the class's G is complete,
+    // the others PD steps ahead.
+    static constexpr int PD = FORM == F64 || TPW <= 2 ? 2 : 1;
+    static constexpr int PV = SPLIT ? 2 : 1;                  // vectors per tile and step
+    static constexpr int KW = SPLIT ? 32 : FORM == F64 ? 8 : 16;                           // rows per step
+    static constexpr int steps(int cls) { return c_cdiv(pair_k(P, R, cls), KW); }
+    template <int F, bool = true> struct Frag { typedef typename SplitT<F>::vec V; };
+    template <bool B> struct Frag<F64, B> { typedef V2 V; };
+    template <bool B> struct Frag<F32, B> { typedef V4 V; };
+    typedef typename Frag<FORM>::V FV;
+    struct Ahead { FV a[PD][TPW][PV]; };
+    template <int CLS> static constexpr int stride() { return (SPLIT ? 2 * kb(CLS) : kb(CLS) * GK / KW) * 64; }   // vectors per tile
+    template <int CLS> __device__ static const FV *table(const FwdParams &prm) {
+        return (const FV *)prm.pairA + (size_t)(SPLIT ? pair_off(P, R, CLS, GK) * 2 : pair_off(P, R, CLS, GK) * GK / KW) * 64 + (phase_tid() & 63);
+    }
+    template <int CLS> __device__ static void ahead(const FwdParams &prm, int wt, Ahead &h) {
+        constexpr int TL = pair_tiles(P, CLS), NA = c_cdiv(TL, WT);
+        const FV *A = table<CLS>(prm);
+#pragma unroll
+        for (int b = 0; b < PD; ++b)
+            if (b < steps(CLS)) {
+#pragma unroll
+                for (int i = 0; i < NA; ++i) {
+                    const int t = wt + i * WT < TL ? wt + i * WT : TL - 1;
+#pragma unroll
+                    for (int v = 0; v < PV; ++v) h.a[b][i][v] = A[t * stride<CLS>() + (PV * b + v) * 64];
+                }
+            }
+    }
     template <int CLS, int NA>
-    __device__ static void product(const FwdParams &prm, const char *g, int wt, int ct0, V4 (&acc)[TPW][CTW]) {
-        const int tid = phase_tid();
-        constexpr int KB = kb(CLS);
-        const int lane = tid & 63;
-        if constexpr (!SPLIT) {
-            // steps of VW x 4 rows; rows past the last step of the class are not taken
-            constexpr int VW = FORM == F64 ? 2 : 4, KV = KB * 4 / VW, GV = gr(CLS) / (4 * VW), STEPS = c_cdiv(pair_k(P, R, CLS), 4 * VW);
-            constexpr int TAIL = c_cdiv(pair_k(P, R, CLS) - (STEPS - 1) * 4 * VW, 4);      // steps in the last of them
-            typedef T VT __attribute__((ext_vector_type(VW)));
-            const VT *A = (const VT *)prm.pairA + (size_t)(pair_off(P, R, CLS, GK) * 4 / VW + wt * KV) * 64 + lane;
-            const VT *B = (const VT *)g + ct0 * GV * 64 + lane;
-            VT a[NA];
+    __device__ static void product(const FwdParams &prm, const char *g, int wt, int ct0, Ahead &h, V4 (&acc)[TPW][CTW]) {
+        constexpr int STEPS = steps(CLS), ST1 = stride<CLS>(), KB = kb(CLS);
+        constexpr int GVS = gr(CLS) / KW;                     // steps of G per column tile (not the split forms)
+        constexpr int TAIL = c_cdiv(pair_k(P, R, CLS) - (STEPS - 1) * KW, 4);              // steps of 4 rows in the last one
+        const FV *A = table<CLS>(prm) + wt * ST1;
+        const FV *B = (const FV *)g + ct0 * (SPLIT ? KB : GVS) * 64 + (phase_tid() & 63);
+        auto step = [&](int b8, int slot, bool more, int nv) {
+            if constexpr (!SPLIT) {
+                FV b[CTW];
 #pragma unroll
-            for (int i = 0; i < NA; ++i) a[i] = A[i * WT * KV * 64];
-            auto step = [&](int b8, int nv) {
-                VT an[NA], b[CTW];
-                const int nx = b8 + 1 < STEPS ? b8 + 1 : b8;
+                for (int j = 0; j < CTW; ++j) b[j] = B[(j * GVS + b8) * 64];
 #pragma unroll
-                for (int i = 0; i < NA; ++i) an[i] = A[(i * WT * KV + nx) * 64];
-#pragma unroll
-                for (int j = 0; j < CTW; ++j) b[j] = B[(j * GV + b8) * 64];
-#pragma unroll
-                for (int v = 0; v < VW; ++v)
+                for (int v = 0; v < KW / 4; ++v)
                     if (v < nv) {
 #pragma unroll
                         for (int i = 0; i < NA; ++i)
 #pragma unroll
-                            for (int j = 0; j < CTW; ++j) acc[i][j] = mfma4(a[i][v], b[j][v], acc[i][j]);
+                            for (int j = 0; j < CTW; ++j) acc[i][j] = mfma4(h.a[slot][i][0][v], b[j][v], acc[i][j]);
                     }
-#pragma unroll
-                for (int i = 0; i < NA; ++i) a[i] = an[i];
-            };
-#pragma unroll 2
-            for (int b8 = 0; b8 + 1 < STEPS; ++b8) step(b8, VW);
-            step(STEPS - 1, TAIL);
-        } else {
-            typedef typename SplitT<FORM>::vec HV;
-            const HV *A = (const HV *)prm.pairA + (size_t)(pair_off(P, R, CLS, GK) + wt * KB) * 128 + lane;
-            const HV *B = (const HV *)g + ct0 * KB * 64 + lane;
-            HV ah[NA], al[NA];
-#pragma unroll
-            for (int i = 0; i < NA; ++i) { ah[i] = A[i * WT * KB * 128]; al[i] = A[i * WT * KB * 128 + 64]; }
-#pragma unroll
-            for (int b8 = 0; b8 < KB; ++b8) {
-                HV nh[NA], nl[NA], bh[CTW], bl[CTW];
-                const int nx = b8 + 1 < KB ? b8 + 1 : b8;
-#pragma unroll
-                for (int i = 0; i < NA; ++i) { nh[i] = A[(i * WT * KB + nx) * 128]; nl[i] = A[(i * WT * KB + nx) * 128 + 64]; }
+            } else {
+                FV bh[CTW], bl[CTW];
 #pragma unroll
                 for (int j = 0; j < CTW; ++j) { bh[j] = B[(j * KB + b8) * 64]; bl[j] = B[(j * KB + b8 + CT * KB) * 64]; }
 #pragma unroll
                 for (int i = 0; i < NA; ++i)
 #pragma unroll
-                    for (int j = 0; j < CTW; ++j) acc[i][j] = mfma32(ah[i], bl[j], acc[i][j]);
+                    for (int j = 0; j < CTW; ++j) acc[i][j] = mfma32(h.a[slot][i][0], bl[j], acc[i][j]);
 #pragma unroll
                 for (int i = 0; i < NA; ++i)
 #pragma unroll
-                    for (int j = 0; j < CTW; ++j) acc[i][j] = mfma32(al[i], bh[j], acc[i][j]);
+                    for (int j = 0; j < CTW; ++j) acc[i][j] = mfma32(h.a[slot][i][PV - 1], bh[j], acc[i][j]);
 #pragma unroll
                 for (int i = 0; i < NA; ++i)
 #pragma unroll
-                    for (int j = 0; j < CTW; ++j) acc[i][j] = mfma32(ah[i], bh[j], acc[i][j]);
-#pragma unroll
-                for (int i = 0; i < NA; ++i) { ah[i] = nh[i]; al[i] = nl[i]; }
+                    for (int j = 0; j < CTW; ++j) acc[i][j] = mfma32(h.a[slot][i][0], bh[j], acc[i][j]);
             }
-        }
+            if (more) {
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+#pragma unroll
+                    for (int v = 0; v < PV; ++v) h.a[slot][i][v] = A[i * WT * ST1 + (PV * (b8 + PD) + v) * 64];
+            }
+        };
+        // whole rounds of PD steps that fetch as many, then the rest
+        constexpr int ROUNDS = STEPS > PD ? (STEPS - PD) / PD : 0;
+#pragma unroll 1
+        for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+            for (int u = 0; u < PD; ++u) step(r * PD + u, u, true, KW / 4);
+        static_for<ROUNDS * PD, STEPS>([&](auto b) {
+            constexpr int b8 = decltype(b)::value;
+            step(b8, b8 % PD, b8 + PD < STEPS, b8 == STEPS - 1 ? TAIL : KW / 4);
+        });
+        // Fetched for a tile that this wave does not have: taken here, as the wait for these
+        // registers' next use would else wait for the stores of A too.
+#pragma unroll
+        for (int b = 0; b < PD; ++b)
+            if (b < STEPS) {
+#pragma unroll
+                for (int i = NA; i < c_cdiv(pair_tiles(P, CLS), WT); ++i)
+#pragma unroll
+                    for (int v = 0; v < PV; ++v) asm volatile("" : : "v"(h.a[b][i][v]));
+            }
     }
     // The class's tiles of this wave are a prefix of its list.
     template <int CLS>
-    __device__ static void products(const FwdParams &prm, const char *g, int wt, int ct0, V4 (&acc)[TPW][CTW]) {
+    __device__ static void products(const FwdParams &prm, const char *g, int wt, int ct0, Ahead &h, V4 (&acc)[TPW][CTW]) {
         constexpr int TL = pair_tiles(P, CLS);
         static_for<1, TPW + 1>([&](auto n) {
             constexpr int NA = decltype(n)::value;
             // some wave has NA tiles: wt + (NA - 1) WT < TL <= wt + NA WT
             if constexpr ((NA - 1) * WT < TL && TL <= WT - 1 + NA * WT)
-                if (wt + (NA - 1) * WT < TL && TL <= wt + NA * WT) product<CLS, NA>(prm, g, wt, ct0, acc);
+                if (wt + (NA - 1) * WT < TL && TL <= wt + NA * WT) product<CLS, NA>(prm, g, wt, ct0, h, acc);
         });
     }
+    // Whether any wave has an i-th tile in a class: where none has, the class adds nothing.
+    static constexpr bool has(int cls, int i) { return i * WT < pair_tiles(P, cls); }
+    static constexpr bool odd(int i) { return has(2, i) || has(3, i); }
+    static constexpr bool anti(int i) { return has(1, i) || has(3, i); }
     __device__ static void zero(V4 (&acc)[TPW][CTW]) {
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
@@ -559,25 +707,72 @@ struct KP {
     template <int PAR>
     __device__ static void parity(const FwdParams &prm, int k0, int wt, int ct0, V4 (&s)[TPW][CTW], V4 (&d)[TPW][CTW],
                                   const Lines (&l)[CTE], Smem &sm) {
+        Ahead h;
         zeta<PAR, true, !SC>(prm, k0, l, sm);
+        ahead<2 * PAR>(prm, wt, h);
         __syncthreads();
         zero(s);
-        products<2 * PAR>(prm, sm.raw, wt, ct0, s);
+        products<2 * PAR>(prm, sm.raw, wt, ct0, h, s);
+        ahead<2 * PAR + 1>(prm, wt, h);
         if (SC) {
             __syncthreads();
             zeta<PAR, false, true>(prm, k0, l, sm);
             __syncthreads();
         }
         zero(d);
-        products<2 * PAR + 1>(prm, sm.raw + GAOFF, wt, ct0, d);
+        products<2 * PAR + 1>(prm, sm.raw + GAOFF, wt, ct0, h, d);
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
+            if (has(2 * PAR + 1, i)) {
 #pragma unroll
-            for (int j = 0; j < CTW; ++j) {
-                const V4 x = s[i][j], y = d[i][j];
-                s[i][j] = x + y;
-                d[i][j] = x - y;
+                for (int j = 0; j < CTW; ++j) {
+                    const V4 x = s[i][j], y = d[i][j];
+                    s[i][j] = x + y;
+                    d[i][j] = x - y;
+                }
             }
+    }
+
+    // ---- 4: A -------------------------------------------------------------------
+    __device__ static T *out(const FwdParams &prm, int64_t slot, int k) {
+        const int64_t e = pair_elem(prm, slot);
+        return (T *)prm.A + (prm.offA ? uniform_load(prm.offA + e) : e * (int64_t)N * N) + (size_t)k * NT * N;
+    }
+    // values between the last 16-byte boundary and p
+    __device__ static int head(const T *p) { return (int)((uintptr_t)p / sizeof(T) % VW); }
+    // cnt values of the copy, whole rows, to A: in 16-byte pieces (8 bytes where only
+    // pairs divide a row).
+    __device__ static void copy_out(T *Ao, const T *src, int cnt, int tid) {
+        if constexpr (NS == N) {
+            typedef T VT __attribute__((ext_vector_type(VW)));
+            const int h = head(Ao), end = h + cnt;
+            Ao -= h;
+            for (int q = tid * VW; q < end; q += NTHR * VW) {
+                if (q >= h && q + VW <= end) {
+                    *(VT *)(Ao + q) = *(const VT *)(src + q);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < VW; ++i)
+                        if (q + i >= h && q + i < end) Ao[q + i] = src[q + i];
+                }
+            }
+        } else {
+            constexpr int VN = N % VW == 0 ? VW : 2, NV = N / VN, INV = ((1 << 20) + NV - 1) / NV;
+            static_assert(N % VN == 0 && KS * NT * NV * (NV - 1) < 1 << 20, "row of a piece");
+            typedef T VT __attribute__((ext_vector_type(VN)));
+            if ((uintptr_t)Ao % sizeof(VT) == 0) {
+#pragma unroll 4
+                for (int q = tid; q < cnt / VN; q += NTHR) {
+                    const T *x = src + q * VN + (__umul24(q, INV) >> 20);
+                    VT v;
+#pragma unroll
+                    for (int i = 0; i < VN; ++i) v[i] = x[i];
+                    *(VT *)(Ao + q * VN) = v;
+                }
+            } else {
+                for (int x = tid; x < cnt; x += NTHR) Ao[x] = src[x + x / N];
+            }
+        }
     }
 
     // ---- one group of elements ----------------------------------------------------
@@ -587,42 +782,48 @@ struct KP {
         const int lane = tid & 63;
         const int wt = wave % WT, ct0 = wave / WT * CTW;
         points(prm, slot0, sm);
-        double nx[NF];
+        double2 nx[NF];
         if (next0 < prm.ne) fetch(prm, next0, nx);
         Lines l[CTE];
-        if (PASSES == 1) lines(prm, 0, l);
+        if (PASSES == 1) lines(sm, 0, l);
         __syncthreads();
 #pragma unroll 1
         for (int k0 = 0; k0 < NK; k0 += KPP) {
             V4 es[TPW][CTW], ed[TPW][CTW], os[TPW][CTW], od[TPW][CTW];
-            if (PASSES > 1) lines(prm, k0, l);
+            if (PASSES > 1) lines(sm, k0, l);
             parity<0>(prm, k0, wt, ct0, es, ed, l, sm);
             if (k0 == 0) {
                 if (next0 < prm.ne) store_inputs(prm, nx, sm);
             }
             __syncthreads();
             parity<1>(prm, k0, wt, ct0, os, od, l, sm);
-            if (Geo::LOAD && k0 == 0) load_vector(prm, slot0, wave, sm);
+            if (Geo::LOAD && k0 + KPP >= NK) load_vector(prm, slot0, wave, sm);
             // the four entries of an orbit
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
 #pragma unroll
                 for (int j = 0; j < CTW; ++j) {
-                    const V4 x = es[i][j], y = ed[i][j], z = os[i][j], w = od[i][j];
+                    if (!odd(i)) continue;
+                    const V4 x = es[i][j], y = has(1, i) ? ed[i][j] : x, z = os[i][j], w = has(3, i) ? od[i][j] : z;
                     es[i][j] = x + z; os[i][j] = x - z;
-                    ed[i][j] = y + w; od[i][j] = y - w;
+                    if (anti(i)) { ed[i][j] = y + w; od[i][j] = y - w; }
                 }
-            __syncthreads();
-            T *st = (T *)sm.raw;
-            // (t, t', reflected t, reflected t') of the wave's orbits, a byte each
-            uint32_t place[TPW][4];
+            // the places of the wave's orbits, all read before the first write waits for LDS
+            uint2 place[TPW][4];
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) place[i][r] = wt + i * WT < pair_tiles(P, 0) ? prm.potab[(wt + i * WT) * 16 + acc_row<T>(lane, r)] : 0u;
+                for (int r = 0; r < 4; ++r) {
+                    const int o = (wt + i * WT) * 16 + acc_row<T>(lane, r);
+                    place[i][r] = sm.place[o < pair_rows(P, 0) ? o : 0];
+                }
+            __syncthreads();
 #pragma unroll 1
             for (int kr = 0; kr < KPP && k0 + kr < NK; kr += KS) {
                 if (kr > 0) __syncthreads();
+                // one element: the copy starts where A's 16-byte pieces do, if its rows are not padded
+                T *st = (T *)sm.raw;
+                if (NS == N) st += head(out(prm, slot0, k0 + kr));
 #pragma unroll
                 for (int j = 0; j < CTW; ++j) {
                     const int c = (ct0 + j) * 16 + (lane & 15);
@@ -636,26 +837,23 @@ struct KP {
                         if (wt + i * WT >= pair_tiles(P, 0)) break;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            uint32_t o = place[i][r];
-                            asm volatile("" : "+v"(o));      // the four addresses are formed here, not kept across the rounds
-                            if ((wt + i * WT + 1) * 16 > pair_rows(P, 0) && o == 0xFFFFFFFFu) continue;
-                            const int t = o & 0xFF, u = o >> 8 & 0xFF, rt = o >> 16 & 0xFF, ru = o >> 24;
-                            at[__umul24(t, NS) + u] = FORM == FP16X3 ? es[i][j][r] * un : es[i][j][r];
-                            at[__umul24(u, NS) + t] = FORM == FP16X3 ? ed[i][j][r] * un : ed[i][j][r];
-                            at[__umul24(rt, NS) + ru] = FORM == FP16X3 ? os[i][j][r] * un : os[i][j][r];
-                            at[__umul24(ru, NS) + rt] = FORM == FP16X3 ? od[i][j][r] * un : od[i][j][r];
+                            const int o = (wt + i * WT) * 16 + acc_row<T>(lane, r);
+                            if ((wt + i * WT + 1) * 16 > pair_rows(P, 0) && o >= pair_rows(P, 0)) continue;
+                            uint2 pl = place[i][r];
+                            asm volatile("" : "+v"(pl.x), "+v"(pl.y));     // unpacked here, not kept unpacked across the rounds
+                            const T e0 = es[i][j][r], e1 = anti(i) ? ed[i][j][r] : e0;
+                            const T e2 = odd(i) ? os[i][j][r] : e0, e3 = !odd(i) ? e1 : anti(i) ? od[i][j][r] : e2;
+                            placed(at, pl.x & 0xFFFF) = FORM == FP16X3 ? e0 * un : e0;
+                            placed(at, pl.x >> 16) = FORM == FP16X3 ? e1 * un : e1;
+                            placed(at, pl.y & 0xFFFF) = FORM == FP16X3 ? e2 * un : e2;
+                            placed(at, pl.y >> 16) = FORM == FP16X3 ? e3 * un : e3;
                         }
                     }
                 }
                 __syncthreads();
                 const int ks = NK - k0 - kr < KS ? NK - k0 - kr : KS;
-                for (int el = 0; el < EPB && slot0 + el < prm.ne; ++el) {
-                    T *Ao = (T *)prm.A + offA_of(prm, elem_of(prm, slot0 + el), N) + (size_t)(k0 + kr) * NT * N;
-                    const T *src = st + el * NT * NK * NS;
-                    const int cnt = ks * NT * N;
-#pragma unroll 8
-                    for (int x = tid; x < cnt; x += NTHR) Ao[x] = src[NS == N ? x : x + x / N];
-                }
+                for (int el = 0; el < EPB && slot0 + el < prm.ne; ++el)
+                    copy_out(out(prm, slot0 + el, k0 + kr), (const T *)sm.raw + el * NT * NK * NS, ks * NT * N, tid);
             }
             if (FORM == FP16X3 && k0 + KPP >= NK && tid < EPB) sm.wmax[tid] = 0;
             __syncthreads();
@@ -665,8 +863,8 @@ struct KP {
     __device__ static void run(const FwdParams &prm, int64_t first, int64_t step, Smem &sm) {
         const int64_t groups = (prm.ne + EPB - 1) / EPB;
         if (first >= groups) return;
-        if (FORM == FP16X3 && threadIdx.x < EPB) sm.wmax[threadIdx.x] = 0;
-        double v[NF];
+        start(prm, sm);
+        double2 v[NF];
         fetch(prm, first * EPB, v);
         store_inputs(prm, v, sm);
         __syncthreads();
@@ -679,6 +877,10 @@ struct KP {
     }
 };
 
+// Waves that do not divide over the four SIMDs cost most (p = 4: five for the five
+// tiles of orbits 7.1 ms against 4.1 with four in FP64; p = 6: seven for 14 tiles
+// 3.4 against 2.5 in FP32), then workgroups per CU count: the shapes are the
+// fastest of those that fit.
 // Shapes per degree and form: elements per workgroup, waves, waves over the
 // orbits, values of k per pass and per round, SC, waves per SIMD asked of the
 // register allocator.
@@ -688,21 +890,21 @@ template <int P, int FORM> struct PairShape;
         static constexpr int EPB = EPB_, NW = NW_, WT = WT_, KPP = KPP_, KS = KS_, W = W_;                \
         static constexpr bool SC = SC_;                                                                  \
     };
-FEINT_PAIR_SHAPE(3, F64, 4, 4, 2, 4, 4, false, 2)
+FEINT_PAIR_SHAPE(3, F64, 2, 4, 2, 4, 4, false, 4)
 FEINT_PAIR_SHAPE(4, F64, 1, 4, 4, 5, 5, false, 3)
-FEINT_PAIR_SHAPE(5, F64, 1, 4, 4, 6, 3, true, 2)
+FEINT_PAIR_SHAPE(5, F64, 1, 4, 4, 2, 1, false, 3)
 FEINT_PAIR_SHAPE(6, F64, 1, 8, 8, 4, 1, false, 2)
 FEINT_PAIR_SHAPE(7, F64, 1, 8, 8, 4, 1, false, 2)
 FEINT_PAIR_SHAPE(3, F32, 4, 4, 2, 4, 4, false, 4)
 FEINT_PAIR_SHAPE(4, F32, 1, 4, 4, 5, 5, false, 4)
 FEINT_PAIR_SHAPE(5, F32, 1, 4, 4, 6, 3, false, 3)
-FEINT_PAIR_SHAPE(6, F32, 1, 4, 4, 4, 2, false, 2)
+FEINT_PAIR_SHAPE(6, F32, 1, 8, 8, 4, 2, false, 4)
 FEINT_PAIR_SHAPE(7, F32, 1, 8, 8, 8, 2, false, 2)
 FEINT_PAIR_SHAPE(2, BF16X3, 5, 3, 1, 3, 3, false, 4)
-FEINT_PAIR_SHAPE(3, BF16X3, 4, 4, 2, 4, 4, false, 4)
+FEINT_PAIR_SHAPE(3, BF16X3, 4, 4, 2, 4, 4, false, 3)
 FEINT_PAIR_SHAPE(4, BF16X3, 1, 4, 4, 5, 5, false, 4)
-FEINT_PAIR_SHAPE(5, BF16X3, 1, 4, 4, 6, 3, false, 3)
-FEINT_PAIR_SHAPE(6, BF16X3, 1, 4, 4, 4, 2, false, 2)
+FEINT_PAIR_SHAPE(5, BF16X3, 1, 4, 4, 6, 2, false, 3)
+FEINT_PAIR_SHAPE(6, BF16X3, 1, 8, 8, 4, 2, false, 4)
 FEINT_PAIR_SHAPE(7, BF16X3, 1, 8, 8, 8, 2, false, 2)
 template <int P> struct PairShape<P, FP16X3> : PairShape<P, BF16X3> {};
 

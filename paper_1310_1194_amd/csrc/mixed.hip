@@ -20,9 +20,9 @@
 //              the same per-degree device code as the direct kernels.
 // The launches per degree give every kernel its own registers, LDS and workgroup
 // size; k_persist's functions share one budget of a wave per SIMD, and its queue has
-// no workgroup to share G across.  262144 elements: FP32 11.0 ms against 30.4, FP64
-// 19.6 against 65.6; 1024 elements: 0.165 against 0.188, 0.209 against 0.368; at 300
-// elements in FP64 six short launches in a row lose to one (0.195 against 0.161).
+// no workgroup to share G across.  262144 elements: FP32 9.7 ms against 30.5, FP64
+// 18.5 against 67.4; 1024 elements: 0.151 against 0.188, 0.209 against 0.364; at 300
+// elements in FP64 six short launches in a row gain nothing (0.161 against 0.159).
 // No memset nodes are used (counters are cleared by kernels), so the whole
 // sequence is safe to capture and replay.
 #include <hip/hip_runtime.h>

@@ -614,6 +614,7 @@ void build_pair_tables(HostTables &T) {
         for (int x = 0; x < 2 * D.sets; ++x) {
             const double *q = &T.qw[4 * ((size_t)m * T.nij + T.ppts[x])];
             T.pqw.insert(T.pqw.end(), q, q + 4);
+            if (T.ppts[x] == T.ppts[x ^ 1]) T.pqw.back() *= 0.5;      // a fixed point counts twice
         }
     // every G is a sum over m of at most one entry times each of L L', L l', l L', l l'
     T.pair_gz = 0.0;

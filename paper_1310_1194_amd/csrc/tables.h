@@ -58,7 +58,7 @@ struct HostTables {
     std::vector<uint16_t> pairb, pairh;
     std::vector<uint32_t> potab;     // [orbits padded to 16]  t, t', reflected t, reflected t', a byte each; all ones past the last
     std::vector<uint16_t> ppts;      // [sets][2]  triangle points of a reflected pair, twice the same for a fixed point
-    std::vector<double> pqw;         // [line point][sets][2][4]  points of the pairs (xi1, xi2, zeta, w), a fixed point twice
+    std::vector<double> pqw;         // [line point][sets][2][4]  points of the pairs (xi1, xi2, zeta, w), a fixed point twice with half its weight
     // adjoint (FP64): the transposed classes, each row times a quarter of its orbit's size,
     // [class][tile of 16 contraction rows][8 orbits][64 lanes][2], lane l, value v = contraction
     // row l%16, orbit 4 v + l/16; line products, [set of types][16 columns][4][64]: lane l of
