@@ -396,7 +396,8 @@ feint_status feint_laplace_autotune(const double *coords, int64_t ne, int p, fei
    The element matrices and load vectors of one degree are summed into a CSR
    matrix and a right-hand side through the element-to-global dof map.
    Elements are coloured so that no two elements of a colour share a global
-   dof; each colour is one launch and adds its entries without atomics.
+   dof; a row's contributions are added in colour order, in one launch over the
+   rows and without atomics.
 
    feint_asm_plan_create: dofs is a HOST array [ne][n] (int32, n = nshp(p)):
    the global dof of every local shape function, in the library's local
@@ -405,7 +406,8 @@ feint_status feint_laplace_autotune(const double *coords, int64_t ne, int p, fei
    (0 <= dof < ndof < 2^31).  Builds, on the host, the CSR pattern (row i
    holds every dof sharing an element with i, columns ascending), the
    offsets of each element entry inside its row and a greedy colouring, and
-   uploads them to the current device (plan-owned memory).  INVALID_ARG for
+   uploads them, with every dof's rows of element matrices in colour order, to
+   the current device (plan-owned memory).  INVALID_ARG for
    null pointers, ne <= 0, an n that is no prism size, ids out of range or a
    dof repeated within an element; TOO_LARGE if a row exceeds 65535 columns.
 

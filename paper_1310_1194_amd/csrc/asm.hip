@@ -11,14 +11,22 @@
 //     dofs[e][b] inside row dofs[e][a] (uint16: a row of a degree-p prism mesh
 //     holds at most (2p+1)^3 <= 3375 columns),
 //   * a greedy colouring: each element takes the smallest colour not used by
-//     an element sharing one of its dofs; elements are listed colour by colour.
-// Per assembly, on the device: the values and rhs are cleared by a fill
-// kernel (unless accumulating), then one launch per colour adds every entry
-// of its elements: values[row_ptr[dofs[e][a]] + pos[e][a][b]] += A_e[a][b]
-// and rhs[dofs[e][a]] += b_e[a], one wave per element.
+//     an element sharing one of its dofs,
+//   * every dof's rows of element matrices, in the order of their elements' colours.
+// Per assembly, on the device, one launch over the rows of the global matrix:
+// G lanes clear (or read, when accumulating) a row in LDS, add the element rows
+// one after the other, values[row_ptr[dofs[e][a]] + pos[e][a][b]] += A_e[a][b],
+// and write the row; rhs[dofs[e][a]] += b_e[a] likewise.  The order of the sums is
+// that of the colours: no atomics, the same bits in every run.
+// Bound by HBM: A and pos are read once, the values written once.  A launch per
+// colour, one wave per element, read and wrote each value once per colour that
+// meets it and took 13 to 16 launches and two fills: 32768 elements at p = 3 in
+// FP64 0.67 ms, here 0.29 (2.9 TB/s; element rows of 320 bytes touch 2.5 to 3.5 lines
+// of 128); 512 elements 0.23 and 0.010; p = 7, 768 elements, 15.4 and 0.43.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <thread>
@@ -31,15 +39,14 @@
 struct feint_asm_plan {
     int dev = 0;
     int64_t ne = 0, ndof = 0, nnz = 0;
-    int n = 0, ncolors = 0;
-    std::vector<int64_t> color_start;     // host: ncolors + 1 offsets into elems
+    int n = 0, ncolors = 0, max_row = 0;
     std::vector<int32_t> color_of;        // host: colour of every element
     // device buffers (one allocation)
     void *base = nullptr;
     int64_t *row_ptr = nullptr;   // [ndof + 1]
     int32_t *col_idx = nullptr;   // [nnz]
-    int32_t *dofs = nullptr;      // [ne][n]
-    int32_t *elems = nullptr;     // [ne], colour by colour
+    int64_t *inc_ptr = nullptr;   // [ndof + 1]
+    int64_t *inc = nullptr;       // [ne * n] rows e * n + a of the element matrices, dof by dof
     uint16_t *pos = nullptr;      // [ne][n][n]
 };
 
@@ -60,40 +67,120 @@ void parallel_for(int64_t n, F fn) {
     for (auto &x : th) x.join();
 }
 
-template <typename T>
-__global__ void fill_zero(T *p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = (T)0;
+// G lanes take R rows of the global matrix, one after the other, cap values of a row in
+// LDS at a time; CH steps of G lanes cover a row of an element matrix.  The R rows'
+// element rows are one list: U of it are fetched while U are added, also across the
+// ends of rows, so that no row waits for its own first loads.
+template <typename T, int G, int CH, int U, int R>
+__global__ __launch_bounds__(256) void assemble_rows(const T *__restrict__ A, const T *__restrict__ b,
+                                                     const int64_t *__restrict__ inc_ptr, const int64_t *__restrict__ inc,
+                                                     const int64_t *__restrict__ row_ptr, const uint16_t *__restrict__ pos,
+                                                     int n, int64_t ndof, int cap, int accumulate, T *values, T *rhs) {
+    static_assert(R < G, "a lane per row and the end of the last");
+    extern __shared__ __align__(16) char lds[];
+    const int lane = threadIdx.x % G, grp = threadIdx.x / G;
+    T *row = (T *)lds + grp * cap;
+    const int64_t i0 = ((int64_t)blockIdx.x * (256 / G) + grp) * R;
+    if (i0 >= ndof) return;
+    const int nr = ndof - i0 < R ? (int)(ndof - i0) : R;
+    // lane r: where row r begins in the list and in the values
+    const int64_t ip = inc_ptr[i0 + (lane < nr ? lane : nr)], rp = row_ptr[i0 + (lane < nr ? lane : nr)];
+    const int64_t k0 = __shfl(ip, 0, G), v0 = __shfl(rp, 0, G);
+    const int st = (int)(ip - k0), en = __shfl(st, lane < nr ? lane + 1 : nr, G), total = __shfl(st, nr, G);
+    const int at0 = (int)(rp - v0);
+    int longest = 0;
+    for (int r = 0; r < nr; ++r) {
+        const int len = __shfl(at0, r + 1, G) - __shfl(at0, r, G);
+        longest = len > longest ? len : longest;
+    }
+    T sum = accumulate && lane < nr ? rhs[i0 + lane] : (T)0;
+    for (int c0 = 0; c0 < longest; c0 += cap) {
+        int r = -1, end = 0, m = 0;                           // the row at hand, its end in the list, its values in LDS
+        T *out = values;
+        auto close = [&] {
+            wave_sync();
+            for (int j = lane; j < m; j += G) out[j] = row[j];
+        };
+        auto open = [&] {
+            ++r;
+            end = __shfl(st, r + 1, G);
+            const int a = __shfl(at0, r, G), len = __shfl(at0, r + 1, G) - a - c0;
+            m = len < 0 ? 0 : len < cap ? len : cap;
+            out = values + v0 + a + c0;
+            wave_sync();
+            for (int j = lane; j < m; j += G) row[j] = accumulate ? out[j] : (T)0;
+            wave_sync();
+        };
+        for (int xb = 0; xb < total; xb += G) {
+            const int xn = total - xb < G ? total - xb : G;
+            const int64_t mine = lane < xn ? inc[k0 + xb + lane] : 0;
+            const T bm = c0 == 0 && lane < xn ? b[mine] : (T)0;
+            struct Rows { T v[U][CH]; int at[U][CH]; } cur, nxt;
+            auto fetch = [&](int x, Rows &f) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t e = __shfl(mine, x + u < xn ? x + u : 0, G) * n;
+#pragma unroll
+                    for (int h = 0; h < CH; ++h) {
+                        const int j = h * G + lane;
+                        const bool on = x + u < xn && j < n;
+                        f.v[u][h] = on ? A[e + j] : (T)0;
+                        f.at[u][h] = on ? pos[e + j] - c0 : -1;
+                    }
+                }
+            };
+            fetch(0, cur);
+            for (int x = 0; x < xn; x += U) {
+                fetch(x + U, nxt);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (x + u >= xn) break;
+                    while (xb + x + u == end) {
+                        close();
+                        open();
+                    }
+#pragma unroll
+                    for (int h = 0; h < CH; ++h)
+                        if ((unsigned)cur.at[u][h] < (unsigned)m) row[cur.at[u][h]] += cur.v[u][h];
+                    wave_sync();                              // the next element's lanes meet other columns
+                }
+                cur = nxt;
+            }
+            if (c0 == 0)
+                for (int x = 0; x < xn; ++x) {
+                    const T v = __shfl(bm, x, G);
+                    if (xb + x >= st && xb + x < en) sum += v;
+                }
+        }
+        close();
+        wave_sync();
+    }
+    if (lane < nr && (en > st || !accumulate)) rhs[i0 + lane] = sum;
 }
 
-// One wave per element of the colour (elements elems[first .. first + count)).
+template <typename T, int G, int CH, int U, int R>
+void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
+    // 8 KB of LDS per wave at most (FP64): rows of more values are taken in several passes
+    constexpr int CAP = 16 * G, GROUPS = 256 / G;
+    const int cap = pl->max_row < CAP ? pl->max_row : CAP;
+    hipLaunchKernelGGL((assemble_rows<T, G, CH, U, R>), dim3((unsigned)((pl->ndof + GROUPS * R - 1) / (GROUPS * R))), dim3(256), GROUPS * cap * sizeof(T), st,
+                       (const T *)A, (const T *)b, pl->inc_ptr, pl->inc, pl->row_ptr, pl->pos, pl->n, pl->ndof, cap, accumulate,
+                       (T *)values, (T *)rhs);
+}
+// Lanes per row: the fewest of a power of two that hold a row of the element matrix, a
+// wave from p = 3 on; loads in flight per lane about four.  Waves take four rows where
+// these fill the device (1024 SIMDs of several waves): 32768 elements at p = 3, FP64, 0.34
+// ms with one row, 0.29 with four, 0.28 with eight; 512 elements 0.009, 0.017, 0.026.
 template <typename T>
-__global__ __launch_bounds__(256) void scatter_color(const T *__restrict__ A, const T *__restrict__ b,
-                                                     const int32_t *__restrict__ elems, int64_t first,
-                                                     int64_t count, const int32_t *__restrict__ dofs,
-                                                     const int64_t *__restrict__ row_ptr,
-                                                     const uint16_t *__restrict__ pos, int n, T *values,
-                                                     T *rhs) {
-    __shared__ int64_t rowbase[4][c_nshp(7)];
-    const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t item = (int64_t)blockIdx.x * 4 + wave;
-    if (item >= count) return;
-    const int64_t e = elems[first + item];
-    const int32_t *de = dofs + e * n;
-    for (int a = lane; a < n; a += 64) {
-        const int32_t g = de[a];
-        rowbase[wave][a] = row_ptr[g];
-        rhs[g] += b[e * n + a];
-    }
-    wave_sync();
-    const int64_t nn = (int64_t)n * n;
-    const T *Ae = A + e * nn;
-    const uint16_t *pe = pos + e * nn;
-    for (int64_t idx = lane; idx < nn; idx += 64) {
-        const int a = (int)(idx / n);
-        T *v = values + rowbase[wave][a] + pe[idx];
-        *v += Ae[idx];
-    }
+void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
+    const bool few = pl->ndof < 65536;
+    auto f = pl->n <= 8 ? launch_rows<T, 8, 1, 4, 1> : pl->n <= 32 ? launch_rows<T, 32, 1, 4, 2>
+           : pl->n <= 64 ? (few ? launch_rows<T, 64, 1, 4, 1> : launch_rows<T, 64, 1, 4, 4>)
+           : pl->n <= 128 ? (few ? launch_rows<T, 64, 2, 2, 1> : launch_rows<T, 64, 2, 2, 4>)
+           : pl->n <= 256 ? (few ? launch_rows<T, 64, 4, 1, 1> : launch_rows<T, 64, 4, 1, 4>)
+                          : (few ? launch_rows<T, 64, 5, 1, 1> : launch_rows<T, 64, 5, 1, 4>);
+    static_assert(c_nshp(7) <= 5 * 64, "row of an element matrix");
+    f(pl, A, b, values, rhs, accumulate, st);
 }
 
 }  // namespace
@@ -123,11 +210,16 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
         for (int64_t e = 0; e < ne; ++e)
             for (int a = 0; a < n; ++a) inc[fill[dofs[e * n + a]]++] = (int32_t)e;
     }
-    for (int64_t e = 0; e < ne; ++e) {      // a dof listed twice in one element is a bad map
-        std::vector<int32_t> d(dofs + e * n, dofs + (e + 1) * n);
-        std::sort(d.begin(), d.end());
-        if (std::adjacent_find(d.begin(), d.end()) != d.end()) return FEINT_ERR_INVALID_ARG;
-    }
+    std::atomic<bool> twice{false};         // a dof listed twice in one element is a bad map
+    parallel_for(ne, [&](int64_t lo, int64_t hi, unsigned) {
+        std::vector<int32_t> d(n);
+        for (int64_t e = lo; e < hi; ++e) {
+            std::copy(dofs + e * n, dofs + (e + 1) * n, d.begin());
+            std::sort(d.begin(), d.end());
+            if (std::adjacent_find(d.begin(), d.end()) != d.end()) twice = true;
+        }
+    });
+    if (twice) return FEINT_ERR_INVALID_ARG;
 
     // CSR pattern: row lengths, then the sorted columns
     std::vector<int64_t> row_ptr(ndof + 1, 0);
@@ -193,33 +285,36 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
         if (c == ncolors) { ++ncolors; used.push_back(-1); }
         color[e] = c;
     }
-    std::vector<int64_t> cstart(ncolors + 1, 0);
-    for (int64_t e = 0; e < ne; ++e) cstart[color[e] + 1]++;
-    for (int c = 0; c < ncolors; ++c) cstart[c + 1] += cstart[c];
-    std::vector<int32_t> elems(ne);
+    // every dof's element rows, by colour
+    std::vector<int64_t> rows(ne * n);
     {
-        std::vector<int64_t> fill(cstart.begin(), cstart.end() - 1);
-        for (int64_t e = 0; e < ne; ++e) elems[fill[color[e]]++] = (int32_t)e;
+        std::vector<int64_t> fill(inc_ptr.begin(), inc_ptr.end() - 1);
+        for (int64_t x = 0; x < ne * n; ++x) rows[fill[dofs[x]]++] = x;
     }
+    parallel_for(ndof, [&](int64_t lo, int64_t hi, unsigned) {
+        for (int64_t i = lo; i < hi; ++i)
+            std::sort(rows.begin() + inc_ptr[i], rows.begin() + inc_ptr[i + 1],
+                      [&](int64_t x, int64_t y) { return color[x / n] < color[y / n]; });
+    });
 
     // upload
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t s_rp = al((ndof + 1) * 8), s_ci = al(nnz * 4), s_d = al(ne * n * 4), s_el = al(ne * 4),
+    const size_t s_rp = al((ndof + 1) * 8), s_ci = al(nnz * 4), s_in = al(ne * n * 8),
                  s_pos = al(ne * nn * 2);
     feint_asm_plan *pl = new feint_asm_plan;
     if (hipGetDevice(&pl->dev) != hipSuccess) { delete pl; return FEINT_ERR_HIP; }
-    hipError_t err = hipMalloc(&pl->base, s_rp + s_ci + s_d + s_el + s_pos);
+    hipError_t err = hipMalloc(&pl->base, 2 * s_rp + s_ci + s_in + s_pos);
     if (err != hipSuccess) { set_error("asm plan allocation", err); delete pl; return FEINT_ERR_HIP; }
     char *p = (char *)pl->base;
     pl->row_ptr = (int64_t *)p; p += s_rp;
     pl->col_idx = (int32_t *)p; p += s_ci;
-    pl->dofs = (int32_t *)p; p += s_d;
-    pl->elems = (int32_t *)p; p += s_el;
+    pl->inc_ptr = (int64_t *)p; p += s_rp;
+    pl->inc = (int64_t *)p; p += s_in;
     pl->pos = (uint16_t *)p;
     const bool ok = hipMemcpy(pl->row_ptr, row_ptr.data(), (ndof + 1) * 8, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->col_idx, col_idx.data(), nnz * 4, hipMemcpyHostToDevice) == hipSuccess &&
-                    hipMemcpy(pl->dofs, dofs, ne * n * 4, hipMemcpyHostToDevice) == hipSuccess &&
-                    hipMemcpy(pl->elems, elems.data(), ne * 4, hipMemcpyHostToDevice) == hipSuccess &&
+                    hipMemcpy(pl->inc_ptr, inc_ptr.data(), (ndof + 1) * 8, hipMemcpyHostToDevice) == hipSuccess &&
+                    hipMemcpy(pl->inc, rows.data(), ne * n * 8, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->pos, pos.data(), ne * nn * 2, hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) {
         set_error("asm plan upload", hipGetLastError());
@@ -228,7 +323,7 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
         return FEINT_ERR_HIP;
     }
     pl->ne = ne; pl->ndof = ndof; pl->nnz = nnz; pl->n = n; pl->ncolors = ncolors;
-    pl->color_start = std::move(cstart);
+    for (int64_t i = 0; i < ndof; ++i) pl->max_row = std::max(pl->max_row, (int)(row_ptr[i + 1] - row_ptr[i]));
     pl->color_of = std::move(color);
     *out = pl;
     return FEINT_OK;
@@ -264,29 +359,10 @@ feint_status feint_assemble(feint_asm_plan *pl, feint_form form, const void *A, 
     if (!A || !b || !values || !rhs) return FEINT_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();
-    const bool f64 = form == FEINT_FP64;
-    if (!accumulate) {
-        const int64_t nv = pl->nnz, nr = pl->ndof;
-        if (f64) {
-            hipLaunchKernelGGL(fill_zero<double>, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, st, (double *)values, nv);
-            hipLaunchKernelGGL(fill_zero<double>, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, st, (double *)rhs, nr);
-        } else {
-            hipLaunchKernelGGL(fill_zero<float>, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, st, (float *)values, nv);
-            hipLaunchKernelGGL(fill_zero<float>, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, st, (float *)rhs, nr);
-        }
-    }
-    for (int c = 0; c < pl->ncolors; ++c) {
-        const int64_t first = pl->color_start[c], count = pl->color_start[c + 1] - first;
-        const unsigned blocks = (unsigned)((count + 3) / 4);
-        if (f64)
-            hipLaunchKernelGGL(scatter_color<double>, dim3(blocks), dim3(256), 0, st, (const double *)A,
-                               (const double *)b, pl->elems, first, count, pl->dofs, pl->row_ptr, pl->pos, pl->n,
-                               (double *)values, (double *)rhs);
-        else
-            hipLaunchKernelGGL(scatter_color<float>, dim3(blocks), dim3(256), 0, st, (const float *)A,
-                               (const float *)b, pl->elems, first, count, pl->dofs, pl->row_ptr, pl->pos, pl->n,
-                               (float *)values, (float *)rhs);
-    }
+    if (form == FEINT_FP64)
+        launch_rows<double>(pl, A, b, values, rhs, accumulate, st);
+    else
+        launch_rows<float>(pl, A, b, values, rhs, accumulate, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("assembly launch", e); return FEINT_ERR_HIP; }
     return FEINT_OK;
