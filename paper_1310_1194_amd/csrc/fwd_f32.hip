@@ -14,6 +14,7 @@ const FwdVariant v1[] = {
     FEINT_K4S(1, float, 1, 1, 8, 1),
     FEINT_KSC(1, float, 1, 1, 1), FEINT_KF_R(1, float, 2, 2, 2, 0)};
 const FwdVariant v2[] = {
+    FEINT_KP(2, F32),
     FEINT_KV(2, float, 18, 2),
     FEINT_KV(2, float, 32, 2),
     FEINT_K4S(2, float, 2, 2, 8, 1),

@@ -31,16 +31,19 @@
 // element's first phases read held in LDS (a global load there waits for the
 // stores of the element before), places and E rows looked up instead of formed,
 // A stored in 16-byte pieces: p = 4 bf16x3 1.77 -> 1.57 ms, p = 5 FP32 1.86 -> 1.59,
-// p = 7 bf16x3 2.88 -> 2.06.
+// p = 7 bf16x3 2.88 -> 2.06; in fp16 the largest |E| by a wave's maximum instead of 64
+// LDS atomics on one word, its scale from the exponent instead of a logarithm: p = 4
+// 2.29 -> 1.74.
 // Collapsed rule, ms, the best other kernel -> this one
 // (131072 elements at p = 3, 4, 32768 at p = 5, 16384 at p = 6, 7):
-//   FP64    p = 3 1.80 -> 0.91, 4 4.83 -> 3.91, 5 7.19 -> 3.05, 6 7.15 -> 4.59, 7 21.8 -> 8.31
-//   FP32    p = 3 0.98 -> 0.52, 4 2.93 -> 2.20, 5 3.86 -> 1.59, 6 5.06 -> 2.32, 7 12.4 -> 4.28
-//   bf16x3  p = 2 0.83 -> 0.60, 3 1.41 -> 0.51, 4 2.67 -> 1.65, 5 2.56 -> 1.02, 6 2.76 -> 1.29, 7 6.44 -> 2.06
-//   fp16x3  p = 2 1.00 -> 0.90, 3 1.42 -> 0.71, 4 2.78 -> 2.29, 5 3.18 -> 1.19, 6 3.76 -> 1.67, 7 7.31 -> 2.34
+//   FP64    p = 3 1.80 -> 0.85, 4 4.83 -> 3.88, 5 7.19 -> 3.00, 6 7.15 -> 4.59, 7 21.8 -> 8.31
+//   FP32    p = 3 0.98 -> 0.51, 4 2.93 -> 2.19, 5 3.86 -> 1.59, 6 5.06 -> 2.31, 7 12.4 -> 4.27
+//   bf16x3  p = 2 0.83 -> 0.54, 3 1.41 -> 0.48, 4 2.67 -> 1.61, 5 2.56 -> 1.02, 6 2.76 -> 1.32, 7 6.44 -> 2.02
+//   fp16x3  p = 2 1.00 -> 0.60, 3 1.42 -> 0.51, 4 2.78 -> 1.74, 5 3.18 -> 1.02, 6 3.76 -> 1.37, 7 7.31 -> 2.07
 // and at every smaller batch (one element: p = 7 FP64 0.13 against 0.40, p = 4 0.015
-// against 0.025).  At p = 2 in FP64 and FP32 the kernel of lanes per element is faster (0.81
-// against 0.97 ms, 0.55 against 0.59 on 262144 elements) and this one is not compiled.
+// against 0.025).  At p = 2 (262144 elements) the kernel of lanes per element is level in
+// FP32 (0.55 ms; 64 elements 0.012 here against 0.017) and faster in FP64 (0.82 against
+// 0.93), where this one is not compiled.
 // Errors against 64 bits are no larger in any form (FP32 p = 7 1.9e-7, was 3.1e-7;
 // bf16x3 p = 4 2.3e-6, was 4.3e-6): fewer terms are summed per entry.
 #pragma once
@@ -59,6 +62,15 @@ __device__ inline double lane_swap(double v) {
     const uint2 w = {(unsigned)__builtin_amdgcn_mov_dpp((int)u.x, 0xB1, 0xF, 0xF, true),
                      (unsigned)__builtin_amdgcn_mov_dpp((int)u.y, 0xB1, 0xF, 0xF, true)};
     return __builtin_bit_cast(double, w);
+}
+
+__device__ inline uint32_t wave_max(uint32_t v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t w = (uint32_t)__shfl_xor((int)v, o, 64);
+        v = w > v ? w : v;
+    }
+    return v;
 }
 
 // The thread's index, opaque to the optimiser: what is computed from it in a phase
@@ -330,7 +342,14 @@ struct KP {
                     E[2 * EP + ((side * EPB + el) * NK + m) * S + set] = (T)y;
                 }
             }
-            if (FORM == FP16X3 && live) atomicMax(&sm.wmax[el], __float_as_uint(big));
+            if (FORM == FP16X3) {
+                // one LDS atomic per wave and element (a wave's points are of one or two elements)
+#pragma unroll 1
+                for (int x = first / TASKS; x <= (first + 63) / TASKS && x < EPB; ++x) {
+                    const uint32_t m = wave_max(live && el0 == x ? __float_as_uint(big) : 0u);
+                    if ((tid & 63) == 0) atomicMax(&sm.wmax[x], m);
+                }
+            }
         }
     }
 
@@ -409,7 +428,13 @@ struct KP {
             H *q = (H *)g + at + (tile >> 1) * 512 + (tile & 1) * 4;
             if (FORM == FP16X3) v *= sc;
             const H4 h = __builtin_convertvector(v, H4);
-            const V4 l = v - __builtin_convertvector(h, V4);
+            V4 l;
+            if constexpr (FORM == BF16X3) {                   // a bf16 value is the upper half of its float
+                const uint2 u = __builtin_bit_cast(uint2, h);
+                l = v - V4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u)};
+            } else {
+                l = v - __builtin_convertvector(h, V4);
+            }
             *(H4 *)q = h;
             *(H4 *)(q + CT * KB * 512) = __builtin_convertvector(l, H4);
             if (TILES % 2 && tile == TILES - 1) {              // the rest of the last step: zero
@@ -420,7 +445,10 @@ struct KP {
     }
     // fp16: the power of two that puts the bound on |G| of an element in [2^13, 2^14)
     __device__ static float scale(const FwdParams &prm, const Smem &sm, int el) {
-        return pow2_scale((double)__uint_as_float(sm.wmax[el]) * prm.pair_gz);
+        const double m = (double)__uint_as_float(sm.wmax[el]) * prm.pair_gz;
+        if (!(m > 0.0) || !(m < 1e300)) return 1.0f;
+        const int ex = 13 - ((int)(__builtin_bit_cast(uint2, m).y >> 20) - 1023);
+        return __uint_as_float((uint32_t)((ex < -60 ? -60 : (ex > 60 ? 60 : ex)) + 127) << 23);
     }
     // Products of line factors of a column tile, as the second operand: lane (g, n)
     // holds zeta points 4 s + g of column n (zero past the last point).
@@ -831,7 +859,7 @@ struct KP {
                     if (EPB > 1 ? el >= EPB : kk >= KPP || k0 + kk >= NK) continue;      // no column
                     if (kk < kr || kk >= kr + KS) continue;                              // another round's
                     T *at = st + (EPB == 1 ? 0 : el * NT * NK * NS) + (kk - kr) * NT * NS + (cc - kk * NK) * NT;
-                    const T un = FORM == FP16X3 ? (T)(ldexpf(1.0f, -prm.pair_shift) / scale(prm, sm, el)) : (T)1;
+                    const T un = FORM == FP16X3 ? (T)ldexpf(1.0f / scale(prm, sm, el), -prm.pair_shift) : (T)1;
 #pragma unroll
                     for (int i = 0; i < TPW; ++i) {
                         if (wt + i * WT >= pair_tiles(P, 0)) break;
@@ -890,7 +918,7 @@ template <int P, int FORM> struct PairShape;
         static constexpr int EPB = EPB_, NW = NW_, WT = WT_, KPP = KPP_, KS = KS_, W = W_;                \
         static constexpr bool SC = SC_;                                                                  \
     };
-FEINT_PAIR_SHAPE(3, F64, 2, 4, 2, 4, 4, false, 4)
+FEINT_PAIR_SHAPE(3, F64, 1, 2, 2, 4, 4, false, 4)
 FEINT_PAIR_SHAPE(4, F64, 1, 4, 4, 5, 5, false, 3)
 FEINT_PAIR_SHAPE(5, F64, 1, 4, 4, 2, 1, false, 3)
 FEINT_PAIR_SHAPE(6, F64, 1, 8, 8, 4, 1, false, 2)
@@ -900,8 +928,9 @@ FEINT_PAIR_SHAPE(4, F32, 1, 4, 4, 5, 5, false, 4)
 FEINT_PAIR_SHAPE(5, F32, 1, 4, 4, 6, 3, false, 3)
 FEINT_PAIR_SHAPE(6, F32, 1, 8, 8, 4, 2, false, 4)
 FEINT_PAIR_SHAPE(7, F32, 1, 8, 8, 8, 2, false, 2)
-FEINT_PAIR_SHAPE(2, BF16X3, 5, 3, 1, 3, 3, false, 4)
-FEINT_PAIR_SHAPE(3, BF16X3, 4, 4, 2, 4, 4, false, 3)
+FEINT_PAIR_SHAPE(2, F32, 3, 2, 1, 3, 3, false, 4)
+FEINT_PAIR_SHAPE(2, BF16X3, 3, 2, 1, 3, 3, false, 4)
+FEINT_PAIR_SHAPE(3, BF16X3, 2, 2, 1, 4, 4, false, 3)
 FEINT_PAIR_SHAPE(4, BF16X3, 1, 4, 4, 5, 5, false, 4)
 FEINT_PAIR_SHAPE(5, BF16X3, 1, 4, 4, 6, 2, false, 3)
 FEINT_PAIR_SHAPE(6, BF16X3, 1, 8, 8, 4, 2, false, 4)
