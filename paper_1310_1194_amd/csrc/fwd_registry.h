@@ -60,6 +60,21 @@ int64_t items_of(int64_t ne) { return items_for<KER>(ne); }
 #define FEINT_KTS(P, T, W) FwdVariant{1, 2, 11, W, &launch_direct<KT<P, T, 1, true>, W>, &items_of<KT<P, T, 1, true>>}
 #define FEINT_KTE(P, T, E, S, W) \
     FwdVariant{1, (S ? 2 : 1) + 4 * E, 11, W, &launch_direct<KT<P, T, 1, S, E>, W>, &items_of<KT<P, T, 1, S, E>>}
+// L: staged stores of whole lines, E elements per wave ("ref2s")
+#define FEINT_KTL(P, T, E, W) FwdVariant{2, 2 + 4 * E, 11, W, &launch_direct<KT<P, T, 1, 2, E>, W>, &items_of<KT<P, T, 1, 2, E>>}
+// B: these for outputs past 256 MB, the staged kernel of 16 elements per wave for others.
+// Whole lines pay where the matrices leave the last-level cache (256 MB) before their
+// neighbours complete the lines that they share: p = 4 FP32, us, staged -> whole lines,
+// 49 MB 29 -> 31, 490 MB 188 -> 135, 1.9 GB 726 -> 521; p = 3 FP32 160 MB 40 -> 53, 1.3 GB
+// 474 -> 348; p = 4 FP64 98 MB 35 -> 43, 980 MB 343 -> 268.  Where n^2 values are whole
+// lines (p = 5, 7) staged stores are as good or better at every size.
+template <class SMALL, class LARGE, int MINW>
+void launch_by_output(const FwdParams &prm, hipStream_t s) {
+    if (prm.ne * LARGE::N2 * LARGE::VALUE > (int64_t)256 << 20) launch_direct<LARGE, MINW>(prm, s);
+    else launch_direct<SMALL, MINW>(prm, s);
+}
+#define FEINT_KTB(P, T, E, W)                                                                                       \
+    FwdVariant{2, 2 + 4 * E, 11, W, &launch_by_output<KT<P, T, 1, 1, 16>, KT<P, T, 1, 2, E>, W>, &items_of<KT<P, T, 1, 1, 16>>}
 #define FEINT_KE_G(P, T, W, GEO) \
     FwdVariant{0, 1, 3, W, &launch_direct<KE<P, T, 0, GEO>, W>, &items_of<KE<P, T, 0, GEO>>}
 // P: software-pipelined split kernel (staged = 4).

@@ -23,7 +23,10 @@
 // element rows at a time); accumulator rows are elements, so 16 lanes store 16
 // consecutive entries of one element, or with STG four column tiles go
 // through LDS first and each store writes 64 consecutive entries of one
-// element.  Stores and fragment loads go through buffer resources: a
+// element, or whole lines of one element (whole_lines below).  Past p = 3 the
+// accumulators' own stores are bound by L2 write requests, 64 bytes at any
+// alignment being two: p = 4 FP32, 393216 elements, TA busy 90 % of 687 us;
+// staged in whole lines 521 us (3.7 TB/s).  Stores and fragment loads go through buffer resources: a
 // wave-uniform base, one fixed 32-bit offset per lane and row, the tile's
 // offset in a scalar register, so the loop carries no per-lane address
 // arithmetic.  The load vector b[e][a] = sf_e m0[a] follows.
@@ -32,12 +35,14 @@
 
 namespace feint {
 
-template <int P, typename T, int RTP = 4, bool STG = false, int EPW = 64>
+// STG 0: accumulators stored as they are; 1, 2: through LDS, 64 entries, whole lines at a time.
+template <int P, typename T, int RTP = 4, int STG = 0, int EPW = 64>
 struct KT {
     static constexpr int RT = EPW / 16;                // row tiles of 16 elements per wave
+    static constexpr int VALUE = (int)sizeof(T);
     static_assert(EPW == 16 || EPW == 32 || EPW == 64, "elements per wave");
     static_assert(RTP >= 1 && RT % RTP == 0, "row tiles per pass");
-    static_assert(!STG || RTP == 1, "staged stores take one row tile per pass");
+    static_assert(STG == 0 || RTP == 1, "staged stores take one row tile per pass");
     typedef TetGeo G;
     static constexpr int N = G::nshp(P), NQ = G::nq(P, 0), N2 = N * N, N2P = (N2 + 15) / 16 * 16;
     static constexpr int NCT = N2P / 16;               // column tiles of 16 entries
@@ -46,14 +51,83 @@ struct KT {
     typedef typename AccT<T>::type V4;
     static constexpr int SP = 64 + 2;                  // staging row: 64 entries + pad
     static constexpr int NB = (N2 + 63) / 64;          // 64-entry column blocks
-    // W of the wave's elements; staged stores reuse it for 16 x SP values
-    static constexpr int WD = STG && 16 * SP * (int)sizeof(T) > EPW * WS * 8 ? (16 * SP * (int)sizeof(T) + 7) / 8 : EPW * WS;
+    // whole lines: blocks of 256 bytes per element, a ring of two of them
+    static constexpr int LN = 128 / (int)sizeof(T), BE = 2 * LN, VL = 16 / (int)sizeof(T), RING = 2 * BE, RS = RING + VL;
+    // W of the wave's elements; staged stores reuse it for 16 x SP values, 16 x RS
+    static constexpr int SB = 16 * (STG == 2 ? RS : SP) * (int)sizeof(T);
+    static constexpr int WD = STG && SB > EPW * WS * 8 ? (SB + 7) / 8 : EPW * WS;
     struct Slice {
-        double W[WD];
+        alignas(16) double W[WD];
         double sf[EPW];
         int64_t oA[EPW], ob[EPW];                      // output offsets of the wave's elements
     };
     struct Smem { Slice w[4]; };
+
+    // 16 elements at a time; per block of 256 bytes per element the results go into a
+    // ring (the slice, free once the A fragments are in registers) at the places of
+    // their addresses modulo 16 bytes, and what is complete leaves in whole lines: 16
+    // lanes write two of an element, whatever the alignment of its matrix.
+    template <class LoadB, class Mma>
+    __device__ static void whole_lines(const FwdParams &prm, Slice &sl, int64_t base, const T (&afr)[RT][4], LoadB load_b, Mma mma) {
+        (void)afr;
+        typedef T VT __attribute__((ext_vector_type(VL)));
+        constexpr int TB = BE / 16, NBLKS = (N2 + LN - 1 + BE - 1) / BE;
+        static_assert(SB <= (int)sizeof(Slice::W), "the ring fits the slice");
+        const int lane = threadIdx.x & 63, i16 = lane & 15;
+        T *ring = (T *)(void *)sl.W;
+        char *Ab = (char *)((T *)prm.A + base);
+        auto head = [&](int el) { return (int)((uintptr_t)((T *)prm.A + sl.oA[el]) / sizeof(T) % LN); };
+        wave_sync();
+        static_for<0, RT>([&](auto GI) {
+            constexpr int G = decltype(GI)::value;
+            int sh[4], h[4];
+            uint32_t off[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                sh[r] = head(G * 16 + acc_row<T>(lane, r)) % VL;
+                const int el = G * 16 + 4 * r + (lane >> 4);
+                h[r] = head(el);
+                off[r] = (uint32_t)((sl.oA[el] - base) * (int64_t)sizeof(T));
+            }
+            T bf[TB][4];
+            auto load = [&](int blk) {
+#pragma unroll
+                for (int t = 0; t < TB; ++t)
+                    if (blk * TB + t < NCT) load_b(blk * TB + t, bf[t]);
+            };
+            load(0);
+#pragma unroll 1
+            for (int blk = 0; blk < NBLKS; ++blk) {
+#pragma unroll
+                for (int t = 0; t < TB; ++t)
+                    if (blk * TB + t < NCT) {
+                        V4 acc[1];
+                        mma(bf[t], acc, ic<G>());
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            ring[acc_row<T>(lane, r) * RS + ((blk * BE + t * 16 + i16 + sh[r]) & (RING - 1))] = acc[0][r];
+                    }
+                load(blk + 1);
+                wave_sync();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // entries [blk BE - h, (blk + 1) BE - h) of element 4 r + lane / 16
+                    const int x = blk * BE - h[r] + i16 * VL;
+                    const T *src = ring + (4 * r + (lane >> 4)) * RS;
+                    const int at = (x + h[r] % VL) & (RING - 1);
+                    T *dst = (T *)(Ab + off[r]) + x;
+                    if (x >= 0 && x + VL <= N2) {
+                        *(VT *)dst = *(const VT *)(src + at);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < VL; ++c)
+                            if (x + c >= 0 && x + c < N2) dst[c] = src[(at + c) & (RING - 1)];
+                    }
+                }
+                wave_sync();
+            }
+        });
+    }
 
     __device__ static void run(const FwdParams &prm, int64_t group, int blk, int wave, Smem &sm) {
         (void)blk;
@@ -106,11 +180,17 @@ struct KT {
 
         const T *Mt = sizeof(T) == 8 ? (const T *)(const void *)prm.Mref64 : (const T *)(const void *)prm.Mref32;
         const auto rM = buffer_rsrc(uniform_ptr(Mt), (uint32_t)(16 * N2P * sizeof(T)));
-        const uint32_t vM = (uint32_t)((kg * N2P + i16) * sizeof(T));
-        // B fragment of column tile ct, K-step kb: lane l supplies M[slot 4 kb + l / 16][entry 16 ct + l % 16]
+        // B fragments of column tile ct: lane l supplies M[slot 4 kb + l / 16][entry 16 ct + l % 16],
+        // K-steps kb = 0..3 in 16-byte loads (a load for each: TA busy 90 % of p = 4's time in FP32)
         auto load_b = [&](int ct, T (&bf)[4]) {
+            constexpr int PC = (int)sizeof(T) / 4;            // 16-byte pieces
+            typedef T VT __attribute__((ext_vector_type(4 / PC)));
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) bf[kb] = buffer_load<T>(rM, vM, (uint32_t)((kb * 4 * N2P + ct * 16) * sizeof(T)));
+            for (int h = 0; h < PC; ++h) {
+                const VT v = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b128(rM, lane * 16, (ct * PC + h) * 1024, 0));
+#pragma unroll
+                for (int i = 0; i < 4 / PC; ++i) bf[h * (4 / PC) + i] = v[i];
+            }
         };
         // the MFMAs of one column tile for row tiles G .. G + RTP - 1
         auto mma = [&](const T (&bc)[4], V4 (&acc)[RTP], auto G) {
@@ -139,7 +219,7 @@ struct KT {
         constexpr int NFULL = N2 / 16;                 // tiles with 16 valid entries
         const auto rA = buffer_rsrc(uniform_ptr((const T *)prm.A + base), 0xffffffffu);
         const bool fastw = nact == EPW && __all(near);
-        if constexpr (STG) if (fastw) {
+        if constexpr (STG == 1) if (fastw) {
             // 16 elements at a time; per block of four column tiles the results
             // go through the slice (free once the A fragments are in registers) so
             // that each store writes 64 consecutive entries of one element
@@ -178,7 +258,8 @@ struct KT {
                 }
             });
         }
-        if constexpr (!STG) if (fastw) {
+        if constexpr (STG == 2) if (fastw) whole_lines(prm, sl, base, afr, load_b, mma);
+        if constexpr (STG == 0) if (fastw) {
             // RTP row tiles (16 RTP elements) at a time, each group through all
             // column tiles before the next
             static_for<0, RT / RTP>([&](auto GI) {

@@ -23,7 +23,7 @@ struct FwdParams {
     const uint16_t *Bhi;     // [nkb][npad/16][64][8] split table of the form (bf16 or fp16),
     const uint16_t *Blo;     //   in A-fragment order
     const float *Ycf;        // [nkb][npad/16][64][8] FP32 columns in B-fragment order
-    const double *Mref64;    // tetrahedra: reference matrices [16][n*n padded to 16] and load vector [n]
+    const double *Mref64;    // tetrahedra: reference matrices as the MFMA's second operand ([16 entries][64 lanes][4], FP64 two halves of [64][2]) and load vector [n]
     const float *Mref32;
     const uint16_t *taubh;   // prisms: triangle factors split into hi / lo, A-fragment order (bf16;
     const uint16_t *taubl;   //   fp16 of tau * 2^tau_f16_shift for the fp16 form)

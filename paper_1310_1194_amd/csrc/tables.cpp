@@ -942,6 +942,7 @@ HostTables build_tet_tables(int p) {
                                   {2, 1}, {2, 2}, {2, 3}, {3, 1}, {3, 2}, {3, 3}};
     const size_t n2p = ((size_t)n * n + 15) / 16 * 16;    // entries padded to whole blocks of 16 (zero)
     T.Mref.assign(n2p * 16 + n, 0.0);
+    T.Mref32.assign(n2p * 16, 0.0f);
     std::vector<long double> acc((size_t)13 * n * n, 0.0L), b0(n, 0.0L);
     for (int q = 0; q < T.nq; ++q) {
         const long double w = T.qw[4 * q + 3];
@@ -958,10 +959,15 @@ HostTables build_tet_tables(int p) {
     }
     for (int a = 0; a < n; ++a) {
         for (int b = 0; b < n; ++b)
-            for (int k = 0; k < 13; ++k) T.Mref[(size_t)k * n2p + (size_t)a * n + b] = (double)acc[((size_t)k * n + a) * n + b];
+            for (int k = 0; k < 13; ++k) {
+                // slot k = 4 kb + kg of an entry is lane (kg, entry % 16)'s value kb
+                const size_t c = (size_t)a * n + b, ct = c / 16, lane = (size_t)(k % 4) * 16 + c % 16, kb = (size_t)k / 4;
+                const double v = (double)acc[((size_t)k * n + a) * n + b];
+                T.Mref[((ct * 2 + kb / 2) * 64 + lane) * 2 + kb % 2] = v;
+                T.Mref32[(ct * 64 + lane) * 4 + kb] = (float)v;
+            }
         T.Mref[n2p * 16 + a] = (double)b0[a];
     }
-    T.Mref32.assign(T.Mref.begin(), T.Mref.end());
     return T;
 }
 
