@@ -7,6 +7,7 @@
 namespace feint {
 namespace {
 const FwdVariant v1[] = {
+    FEINT_KM(float, 2, 0),
     FEINT_KE(1, float, 3),
     FEINT_KE(1, float, 2),
     FEINT_KV(1, float, 8, 2),

@@ -7,6 +7,7 @@
 namespace feint {
 namespace {
 const FwdVariant v1[] = {
+    FEINT_KM(double, 2, 0),
     FEINT_KE(1, double, 2),
     FEINT_KV(1, double, 8, 2),
     FEINT_KV(1, double, 6, 2),

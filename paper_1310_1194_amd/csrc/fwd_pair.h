@@ -64,6 +64,9 @@ __device__ inline double lane_swap(double v) {
     return __builtin_bit_cast(double, w);
 }
 
+__device__ inline float lane_swap(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
 __device__ inline uint32_t wave_max(uint32_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -124,6 +127,27 @@ __device__ inline double pair_cofactors(const double *in, const double *pt, doub
 // 0o o3 3o, 0e e3 3e, 00 03 33, oo, ee, oe+eo, oe-eo, and w det J f.
 // With C = det J K the cofactors, w det J K D K^T = (w / det J) C D C^T: K is not formed.
 constexpr int PAIR_ENTRIES = 14;
+template <class Coef>
+__device__ inline void pair_entries(const Coef &E, double w, double det, const double co[3], const double ce[3], const double cz[3],
+                                    double v[PAIR_ENTRIES]) {
+    const double wd = w * det, q = w / det;
+    v[6] = wd * E.c;
+    v[13] = wd * E.f;
+const double be[3] = {w * E.be[0], w * E.be[1], w * E.be[2]};
+    auto dot = [](const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; };
+    v[0] = dot(co, be); v[3] = dot(ce, be); v[7] = dot(cz, be);
+    auto times_D = [&](const double *a, double m[3]) {
+        const double x = q * a[0], y = q * a[1], z = q * a[2];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) m[d] = x * E.D[d] + y * E.D[3 + d] + z * E.D[6 + d];
+    };
+    double mo[3], me[3], mz[3];
+    times_D(co, mo); times_D(ce, me); times_D(cz, mz);
+    v[1] = dot(mo, cz); v[2] = dot(mz, co); v[4] = dot(me, cz); v[5] = dot(mz, ce); v[8] = dot(mz, cz);
+    v[9] = dot(mo, co); v[10] = dot(me, ce);
+    const double oe = dot(mo, ce), eo = dot(me, co);
+    v[11] = oe + eo; v[12] = oe - eo;
+}
 template <class Geo> struct PairInputs {
     static constexpr int EDGES = 21, MAX = EDGES + 6 * 14;
     __device__ static int count(const FwdParams &prm) { return prm.fD ? MAX : EDGES + 14; }
@@ -169,24 +193,7 @@ template <class Geo> struct PairInputs {
                 E.f += Na * in[78 + a];
             }
         }
-        const double w = pt[3], wd = w * det, q = w / det;
-        v[6] = wd * E.c;
-        v[13] = wd * E.f;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) E.be[d] *= w;
-        auto dot = [](const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; };
-        v[0] = dot(co, E.be); v[3] = dot(ce, E.be); v[7] = dot(cz, E.be);
-        auto times_D = [&](const double *a, double m[3]) {
-            const double x = q * a[0], y = q * a[1], z = q * a[2];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) m[d] = x * E.D[d] + y * E.D[3 + d] + z * E.D[6 + d];
-        };
-        double mo[3], me[3], mz[3];
-        times_D(co, mo); times_D(ce, me); times_D(cz, mz);
-        v[1] = dot(mo, cz); v[2] = dot(mz, co); v[4] = dot(me, cz); v[5] = dot(mz, ce); v[8] = dot(mz, cz);
-        v[9] = dot(mo, co); v[10] = dot(me, ce);
-        const double oe = dot(mo, ce), eo = dot(me, co);
-        v[11] = oe + eo; v[12] = oe - eo;
+        pair_entries(E, pt[3], det, co, ce, cz, v);
         return det;
     }
 };

@@ -10,6 +10,7 @@
 #include "fwd_ymfma.h"
 #include "fwd_hsf.h"
 #include "fwd_tref.h"
+#include "fwd_one.h"
 #include "fwd_pair.h"
 
 namespace feint {
@@ -55,6 +56,8 @@ int64_t items_of(int64_t ne) { return items_for<KER>(ne); }
 #define FEINT_KE_R(P, T, W, R) \
     FwdVariant{0, 1, 3, W, &launch_direct<KE<P, T, R>, W>, &items_of<KE<P, T, R>>}
 #define FEINT_KE(P, T, W) FEINT_KE_R(P, T, W, 0)
+// M: prisms of degree 1 from moments, one element per lane ("v1").
+#define FEINT_KM(T, W, R) FwdVariant{0, 1, 3, W, &launch_direct<KM<T, R>, W>, &items_of<KM<T, R>>}
 // R: tetrahedra from reference matrices (staged = 11): one element per lane.
 #define FEINT_KT(P, T, R, W) FwdVariant{R, 1, 11, W, &launch_direct<KT<P, T, R>, W>, &items_of<KT<P, T, R>>}
 #define FEINT_KTS(P, T, W) FwdVariant{1, 2, 11, W, &launch_direct<KT<P, T, 1, true>, W>, &items_of<KT<P, T, 1, true>>}
