@@ -13,13 +13,15 @@
 //   4. a point per lane: its W's gradient from the rows "even" and "odd" of E, then
 //      the chain rule to the 32 inputs, summed over the element's waves.
 // Collapsed rule, ms, best other kernel -> this one (131072, 65536, 16384, 8192,
-// 4001 elements at p = 3..7): 2.73 -> 1.36, 6.05 -> 2.56, 5.67 -> 1.95, 7.90 -> 2.90,
-// 8.73 -> 2.88; one element 0.039 -> 0.025 at p = 4, 0.17 -> 0.14 at p = 7.
-// At p = 7 the matrix cores are busy half of the cycles; the other half goes to
-// reading G: an orbit's entries (t, t') and (t', t) lie in different rows, 16
-// orbits take about four lines of 128 bytes for each they fill, 4.4 TB/s.  Orbits
-// are ordered by patches of 8 x 4 (t, t') for it (row by row: 3.05 ms; 4 x 4,
-// 8 x 8: 2.88, 2.89; 16 x 16: 2.97).
+// 4001 elements at p = 3..7): 2.73 -> 1.36, 6.05 -> 2.62, 5.67 -> 1.90, 7.90 -> 2.82,
+// 8.73 -> 2.56; one element 0.039 -> 0.025 at p = 4, 0.17 -> 0.14 at p = 7.
+// At p = 7 the matrix cores are busy 55 % of the cycles.  Reading G is not what is
+// left: an orbit's entries (t, t') and (t', t) lie in different rows and 16 orbits take
+// about four lines of 128 bytes for each they fill (4.4 TB/s past L2), but passes over
+// 32 or 16 columns at a time, whose rows stay in L2, took 2.77 and 3.62 ms against 2.65.
+// Two waves per SIMD in step at the barriers are: the next chunk's table under way over
+// the barrier gave 2.81 -> 2.56.  Orbits are ordered by patches of 8 x 4 (t, t'): 3.05
+// ms row by row, 2.88 (4 x 4: 2.88, 8 x 8: 2.89, 16 x 16: 2.97).
 // Against KFA2 the matrix work is 4.6x less at p = 7 (with 16-padded tiles of
 // triangle functions, the unused three quarters of its second product) and no
 // operand is combined from line factors on the vector ALU.
@@ -130,20 +132,43 @@ struct AdjPair {
 
     // ---- 3 -----------------------------------------------------------------------
     static constexpr int rows_of(int par, int y) { return ((y == 0 || y == 5) == (par == 1)) ? S : NPAIR; }
-    template <int CLS, int NTL>
-    __device__ static void backward(const AdjParams &prm, double *Ebuf, int first, const V4 (&acc)[NTL][CT]) {
+    // The tiles' sums over the columns by products of line factors; every tile's before the
+    // first is written (written tile by tile, p = 7 took 2.88 ms).
+    template <int CLS, int NTL, int J0, int GT>
+    __device__ static void backward(const AdjParams &prm, int first, const V4 (&acc)[NTL][CT], V4 (&p)[GT][SETS_L]) {
+        constexpr int PAR = CLS / 2, ANTI = CLS & 1, TL = tiles(CLS);
+        constexpr int N1 = rows_of(PAR, 0) + rows_of(PAR, 1), N2 = N1 + rows_of(PAR, 2);
+        const double *lines = prm.plines + (threadIdx.x & 63);
+#pragma unroll
+        for (int j = 0; j < GT; ++j) {
+            const int tile = first + (J0 + j) * WH;
+            if (tile >= TL) continue;
+            // rows of 0o, 0e or 00 among the tile's
+            const bool mixed = tile * 16 < (ANTI ? N1 : N2);
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    p[j][0] = mfma4(lines[(c * 4 + r) * 64], acc[J0 + j][c][r], p[j][0]);
+                    if (mixed) {
+#pragma unroll
+                        for (int q = 1; q < SETS_L; ++q) p[j][q] = mfma4(lines[((q * CT + c) * 4 + r) * 64], acc[J0 + j][c][r], p[j][q]);
+                    }
+                }
+        }
+    }
+    template <int CLS, int J0, int GT>
+    __device__ static void gradients(double *Ebuf, int first, const V4 (&p)[GT][SETS_L]) {
         constexpr int PAR = CLS / 2, ANTI = CLS & 1, TL = tiles(CLS);
         constexpr int N0 = rows_of(PAR, 0), N1 = N0 + rows_of(PAR, 1), N2 = N1 + rows_of(PAR, 2), N3 = N2 + rows_of(PAR, 3);
         constexpr int N4 = N3 + rows_of(PAR, 4), K = pair_k(P, R, CLS);
         const int lane = threadIdx.x & 63, i16 = lane & 15;
-        const double *lines = prm.plines + lane;
 #pragma unroll
-        for (int j = 0; j < NTL; ++j) {
-            const int tile = first + j * WH;
+        for (int j = 0; j < GT; ++j) {
+            const int tile = first + (J0 + j) * WH;
             if (tile >= TL) continue;
-            // the column's type y and set; mixed: rows of 0o, 0e or 00 among the tile's
+            // the column's type y and set
             const int kap = tile * 16 + i16;
-            const bool mixed = tile * 16 < (ANTI ? N1 : N2);
             int set = kap, y = 0;
             if (set >= N0) { set -= N0; y = 1; }
             if (y == 1 && set >= N1 - N0) { set -= N1 - N0; y = ANTI ? 5 : 2; }
@@ -153,19 +178,6 @@ struct AdjPair {
                 if (y == 4 && set >= N4 - N3) { set -= N4 - N3; y = 5; }
             }
             const int slot = ANTI ? (y < 2 ? 12 + 3 * y : 18) : (y < 3 ? 3 * y : 6 + y);
-            V4 p[SETS_L];
-#pragma unroll
-            for (int q = 0; q < SETS_L; ++q) p[q] = V4{0, 0, 0, 0};
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    p[0] = mfma4(lines[(c * 4 + r) * 64], acc[j][c][r], p[0]);
-                    if (mixed) {
-#pragma unroll
-                        for (int q = 1; q < SETS_L; ++q) p[q] = mfma4(lines[((q * CT + c) * 4 + r) * 64], acc[j][c][r], p[q]);
-                    }
-                }
             if (kap >= K) continue;
 #pragma unroll
             for (int q = 0; q < SETS_L; ++q)
@@ -173,9 +185,23 @@ struct AdjPair {
                 for (int r = 0; r < 4; ++r) {
                     const int row = acc_row<double>(lane, r), d = q * TS + row / NK, m = row % NK;      // d: ll, ld, dl, dd
                     const bool on = row < TS * NK && (d == 0 || (d == 1 && y < 3) || (d == 2 && y < 2) || (d == 3 && y == 2));
-                    if (on) Ebuf[((PAR * SLOTS + slot + (d == 0 ? 0 : d == 1 ? 1 : 2)) * NK + m) * S + set] = p[q][r];
+                    if (on) Ebuf[((PAR * SLOTS + slot + (d == 0 ? 0 : d == 1 ? 1 : 2)) * NK + m) * S + set] = p[j][q][r];
                 }
         }
+    }
+
+    template <int CLS, int NTL> __device__ static void sums(const AdjParams &prm, double *Ebuf, int first, const V4 (&acc)[NTL][CT]) {
+        constexpr int GT = P <= 4 ? 1 : NTL;                  // tiles at a time: at p = 4 all of them spill
+        static_for<0, NTL / GT>([&](auto gi) {
+            constexpr int J0 = decltype(gi)::value * GT;
+            V4 p[GT][SETS_L];
+#pragma unroll
+            for (int j = 0; j < GT; ++j)
+#pragma unroll
+                for (int q = 0; q < SETS_L; ++q) p[j][q] = V4{0, 0, 0, 0};
+            backward<CLS, NTL, J0, GT>(prm, first, acc, p);
+            gradients<CLS, J0, GT>(Ebuf, first, p);
+        });
     }
 
     // ---- 4 -----------------------------------------------------------------------
@@ -218,26 +244,32 @@ struct AdjPair {
         const int fa = ((idx - TSY) % WH + WH) % WH;          // the antisymmetric tiles go on where the symmetric ones end
         double v[PP][4];
         if (live) fetch(prm, G, 0, t0, v);
-        if (live) store(buf, t0, v);
+        V2 bs[TSW][2], ba[TAW][2];
+        if (live) {
+            table<2 * PAR, TSW>(prm, 0, idx, bs);
+            table<2 * PAR + 1, TAW>(prm, 0, fa, ba);
+            store(buf, t0, v);
+        }
         __syncthreads();
 #pragma unroll 1
         for (int ch = 0; ch < CHUNKS; ++ch) {
             const double *now = buf + (ch & 1) * CHUNK;
-            // the table first: waiting for it does not wait for the next chunk of G
-            V2 bs[TSW][2], ba[TAW][2];
             if (live) {
-                table<2 * PAR, TSW>(prm, ch, idx, bs);
-                table<2 * PAR + 1, TAW>(prm, ch, fa, ba);
                 if (ch + 1 < CHUNKS) fetch(prm, G, ch + 1, t0, v);
                 product<2 * PAR, TSW>(now, ch, idx, bs, s);
                 product<2 * PAR + 1, TAW>(now, ch, fa, ba, a);
-                if (ch + 1 < CHUNKS) store(buf + ((ch + 1) & 1) * CHUNK, t0, v);
+                // the next chunk's table is under way over the barrier
+                if (ch + 1 < CHUNKS) {
+                    table<2 * PAR, TSW>(prm, ch + 1, idx, bs);
+                    table<2 * PAR + 1, TAW>(prm, ch + 1, fa, ba);
+                    store(buf + ((ch + 1) & 1) * CHUNK, t0, v);
+                }
             }
             __syncthreads();
         }
         if (live) {
-            backward<2 * PAR, TSW>(prm, buf, idx, s);
-            backward<2 * PAR + 1, TAW>(prm, buf, fa, a);
+            sums<2 * PAR, TSW>(prm, buf, idx, s);
+            sums<2 * PAR + 1, TAW>(prm, buf, fa, a);
         }
     }
     __device__ static void load_sums(const AdjParams &prm, int64_t e, int wv, double *u) {
