@@ -52,6 +52,8 @@ DTYPE_DESC = {"bf16x3": "bf16x3 (split bf16 MFMA, fp32 accumulate, fp64 geometry
 KERNEL_SOURCES = ["paper_1310_1194_amd/csrc/fwd_kernels.h", "paper_1310_1194_amd/csrc/fwd_staged.h",
                   "paper_1310_1194_amd/csrc/fwd_pipe.h", "paper_1310_1194_amd/csrc/fwd_valu.h",
                   "paper_1310_1194_amd/csrc/fwd_fact.h", "paper_1310_1194_amd/csrc/fwd_ymfma.h",
+                  "paper_1310_1194_amd/csrc/fwd_pair.h", "paper_1310_1194_amd/csrc/pair_dims.h",
+                  "paper_1310_1194_amd/csrc/fwd_one.h",
                   "paper_1310_1194_amd/csrc/fwd_registry.h", "paper_1310_1194_amd/csrc/fwd_bf16.hip",
                   "paper_1310_1194_amd/csrc/fwd_f16.hip", "paper_1310_1194_amd/csrc/fwd_f32.hip",
                   "paper_1310_1194_amd/csrc/fwd_f64.hip",
@@ -957,7 +959,7 @@ def bench_mixed(args):
 
 
 def bench_assemble(args):
-    """Global assembly of the p=4 element matrices (CSR, colour by colour):
+    """Global assembly of the p=4 element matrices (CSR, row by row in colour order):
     set-up on the host once, then the timed device assembly per form."""
     import torch
     import paper_1310_1194_amd as F
