@@ -23,8 +23,8 @@
 // matrix work is 3.1x less at p = 7 (75 -> 24 MFLOP per element counted with the
 // padding of 36 functions to 48), 4x at p = 5, 2x at p = 4, and none is spent on
 // forming operands from the table.
-// Bound by the matrix cores in FP64 at p = 7 (58 % of an element's time in the
-// products, which then run at their peak rate), elsewhere by the latency of an
+// Bound by the matrix cores in FP64 at p = 7 (busy 65 % of the cycles; 53 % at p = 4,
+// in FP32 59 % at p = 6, in bf16x3 31 % at p = 4), elsewhere by the latency of an
 // element's phases, which overlap only with other workgroups' (p = 4: a quarter
 // fewer workgroups per CU leave each phase as long as it was).  What shortened them:
 // the table's first steps fetched before the barrier and PD steps ahead, what an
