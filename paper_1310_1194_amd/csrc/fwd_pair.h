@@ -226,6 +226,11 @@ struct KP {
     typedef typename PF::T T;
     typedef typename AccT<T>::type V4;
     typedef T V2 __attribute__((ext_vector_type(2)));
+    // The load vector's sums: in FP64 at p = 2 in FP32, as in the kernel of lanes per element
+    // (b is then rounded once; summed in FP32, entries were up to 22 times that rounding off).
+    typedef std::conditional_t<P == 2 && FORM == F32, double, T> LT;
+    typedef typename AccT<LT>::type VL4;
+    typedef LT VL2 __attribute__((ext_vector_type(2)));
     static constexpr bool SPLIT = FORM == BF16X3 || FORM == FP16X3;
     static constexpr PairDims D = pair_dims(P, R);
     static constexpr int NK = D.nk, NT = D.nt, N = NT * NK, NIJ = D.nij, NQ = NIJ * NK;
@@ -250,22 +255,26 @@ struct KP {
     static constexpr int GS = CT * mx(gr(0), gr(2)) * GB, GA = CT * mx(gr(1), gr(3)) * GB;
     static constexpr int GALL = SC ? mx(GS, GA) : GS + GA;
     static constexpr int GAOFF = SC ? 0 : GS;
-    static constexpr int EB = (EPB * 2 * NE * NK * S * (int)sizeof(T) + 15) / 16 * 16;
+    static constexpr int EP = EPB * (NE - 1) * NK * S;        // E of a parity; w det J f of both follows
+    static constexpr int EB = (2 * EP * (int)sizeof(T) + 2 * EPB * NK * S * (int)sizeof(LT) + 15) / 16 * 16;
     static constexpr int HT = c_cdiv(S, 16);                  // blocks of 16 sets
     static constexpr int HC = EPB * NK;                       // columns of the load vector's sums
-    static constexpr int EP = EPB * (NE - 1) * NK * S;        // E of a parity; w det J f of both follows
-    static_assert(2 * HT * 16 * HC <= EP, "the load vector's sums lie over the even E");
+    static constexpr int HB = 2 * HT * 16 * HC * (int)sizeof(LT);
+    static constexpr bool OVER = HB <= EP * (int)sizeof(T);   // the load vector's sums lie over the even E
+    static_assert(OVER || PASSES == 1, "E of every pass");
     static constexpr int VW = 16 / (int)sizeof(T);            // values of a 16-byte store
     static constexpr int ST = (EPB * KS * NT * NS + (NS == N ? VW : 0)) * (int)sizeof(T);
     static constexpr int ZR = 16 * (c_cdiv(pair_k(P, R, 0), 16) + c_cdiv(pair_k(P, R, 1), 16) + c_cdiv(pair_k(P, R, 2), 16) + c_cdiv(pair_k(P, R, 3), 16));
     static constexpr int EOFF = PASSES == 1 ? GALL : mx(GALL, (ST + 15) / 16 * 16);
-    static constexpr int LDS = mx(EOFF + EB, ST);
+    static constexpr int LOFF = EOFF + 2 * EP * (int)sizeof(T), HOFF = OVER ? EOFF : EOFF + EB;
+    static constexpr int LDS = mx(EOFF + EB + (OVER ? 0 : HB), ST);
     struct alignas(16) Smem {
         char raw[(LDS + 15) / 16 * 16];
         double in[EPB][In::MAX];
         uint2 place[pair_rows(P, 0)];                         // where an orbit's entries lie in the copy of A
         double tri[2 * S][3], line[NK][2];                    // points: xi1, xi2, weight; zeta, weight
         T lam[2][NK * NK];                                    // line factors and their derivatives
+        LT lamL[sizeof(LT) != sizeof(T) ? NK * NK : 1];       // line factors for the load vector, where not the same
         uint16_t zrow[ZR];                                    // contraction rows: place in E, kind
         uint32_t wmax[EPB];                                   // fp16: bits of the largest |E| of the element
     };
@@ -346,7 +355,7 @@ struct KP {
                 if (x < NE - 1) {
                     if (live) row[x * NK * S] = (T)y;
                 } else if (Geo::LOAD && live) {
-                    E[2 * EP + ((side * EPB + el) * NK + m) * S + set] = (T)y;
+                    ((LT *)(sm.raw + LOFF))[((side * EPB + el) * NK + m) * S + set] = (LT)y;
                 }
             }
             if (FORM == FP16X3) {
@@ -414,6 +423,7 @@ struct KP {
         for (int i = threadIdx.x; i < NK * NK; i += NTHR) {
             sm.lam[0][i] = lam[i];
             sm.lam[1][i] = lam[3 * NK * NK + i];
+            if constexpr (sizeof(LT) != sizeof(T)) sm.lamL[i] = prm.lam[i];
         }
         if (FORM == FP16X3 && threadIdx.x < EPB) sm.wmax[threadIdx.x] = 0;
     }
@@ -562,50 +572,51 @@ struct KP {
     // cores, the columns being k of every element.
     // Taken when the even E is no longer read: they lie over it.
     __device__ static void load_sums(Smem &sm) {
-        T *H = (T *)(sm.raw + EOFF);
+        LT *H = (LT *)(sm.raw + HOFF);
+        const LT *L = sizeof(LT) != sizeof(T) ? sm.lamL : (const LT *)(const void *)sm.lam[0];
         const int tid = phase_tid(), lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
 #pragma unroll 1
         for (int id = NW - 1 - wave_uniform(tid >> 6); id < 2 * EPB * HT; id += NW) {
             const int par = id / (EPB * HT), el = id / HT - par * EPB, tile = id % HT, k = i16 < NK ? i16 : 0;
-            const int row = tile * 16 + (FORM == F64 ? i16 : 4 * (i16 & 3) + (i16 >> 2)), set = row < S ? row : S - 1;
-            const T *E = (const T *)(sm.raw + EOFF) + 2 * EP + (par * EPB + el) * NK * S + set;
-            V4 p = {0, 0, 0, 0};
+            const int row = tile * 16 + (sizeof(LT) == 8 ? i16 : 4 * (i16 & 3) + (i16 >> 2)), set = row < S ? row : S - 1;
+            const LT *E = (const LT *)(sm.raw + LOFF) + (par * EPB + el) * NK * S + set;
+            VL4 p = {0, 0, 0, 0};
 #pragma unroll
             for (int s = 0; s < KZ; ++s) {
                 const int m = 4 * s + g4, mm = m < NK ? m : 0;
-                const T lk = m < NK ? sm.lam[0][k * NK + mm] : (T)0;
+                const LT lk = m < NK ? L[k * NK + mm] : (LT)0;
                 p = mfma4(E[mm * S], lk, p);
             }
             if (i16 < NK) {
-                T *q = H + (par * HT + tile) * 16 * HC + (g4 * HC + el * NK + i16) * (FORM == F64 ? 2 : 4);
-                if constexpr (FORM == F64) {
-                    *(V2 *)q = V2{p[0], p[1]};
-                    *(V2 *)(q + 8 * HC) = V2{p[2], p[3]};
+                LT *q = H + (par * HT + tile) * 16 * HC + (g4 * HC + el * NK + i16) * (sizeof(LT) == 8 ? 2 : 4);
+                if constexpr (sizeof(LT) == 8) {
+                    *(VL2 *)q = VL2{p[0], p[1]};
+                    *(VL2 *)(q + 8 * HC) = VL2{p[2], p[3]};
                 } else {
-                    *(V4 *)q = p;
+                    *(VL4 *)q = p;
                 }
             }
         }
     }
     __device__ static void load_vector(const FwdParams &prm, int64_t slot0, int wave, Smem &sm) {
-        const T *H = (const T *)(sm.raw + EOFF);
-        const T *bt = sizeof(T) == 8 ? (const T *)(const void *)prm.pbt64 : (const T *)(const void *)prm.pbt32;
+        const LT *H = (const LT *)(sm.raw + HOFF);
+        const LT *bt = sizeof(LT) == 8 ? (const LT *)(const void *)prm.pbt64 : (const LT *)(const void *)prm.pbt32;
         const int lane = phase_tid() & 63, i16 = lane & 15, hl = (lane >> 4) * HC + (i16 < HC ? i16 : 0);
 #pragma unroll 1
         for (int tile = NW - 1 - wave; tile < c_cdiv(NT, 16); tile += NW) {
-            V4 v = {0, 0, 0, 0};
-            const T *A = bt + tile * 2 * HT * 256;
+            VL4 v = {0, 0, 0, 0};
+            const LT *A = bt + tile * 2 * HT * 256;
 #pragma unroll
             for (int b = 0; b < 2 * HT; ++b) {
-                if constexpr (FORM == F64) {
+                if constexpr (sizeof(LT) == 8) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const V2 x = *(const V2 *)(A + (2 * b + h) * 128 + 2 * lane), y = *(const V2 *)(H + (2 * b + h) * 8 * HC + 2 * hl);
+                        const VL2 x = *(const VL2 *)(A + (2 * b + h) * 128 + 2 * lane), y = *(const VL2 *)(H + (2 * b + h) * 8 * HC + 2 * hl);
                         v = mfma4(x[0], y[0], v);
                         v = mfma4(x[1], y[1], v);
                     }
                 } else {
-                    const V4 x = *(const V4 *)(A + b * 256 + 4 * lane), y = *(const V4 *)(H + b * 16 * HC + 4 * hl);
+                    const VL4 x = *(const VL4 *)(A + b * 256 + 4 * lane), y = *(const VL4 *)(H + b * 16 * HC + 4 * hl);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) v = mfma4(x[u], y[u], v);
                 }
@@ -616,8 +627,8 @@ struct KP {
             T *bo = (T *)prm.b + (EPB == 1 && prm.offb ? uniform_load(prm.offb + e) : offb_of(prm, e, N)) + k * NT;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int t = tile * 16 + acc_row<T>(lane, r);
-                if (t < NT) bo[t] = v[r];
+                const int t = tile * 16 + acc_row<LT>(lane, r);
+                if (t < NT) bo[t] = (T)v[r];
             }
         }
     }
