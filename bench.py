@@ -353,7 +353,7 @@ def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
         if costmodel.is_kf_tile(r["tile"]):       # prisms and hexahedra: factorised along the third coordinate
             r["alg_flops_per_element"] = (costmodel.f_factored_zfirst(n, p + 1, q) if costmodel.is_zfirst_tile(r["tile"])
                                           else costmodel.f_factored(n, p + 1, q))
-        elif costmodel.is_pair_tile(r["tile"]):   # prisms: products of pairs of triangle functions
+        elif costmodel.is_pair_tile(r["tile"]) or r["tile"] == "2x2so4":   # prisms: products of pairs of triangle functions
             r["alg_flops_per_element"] = costmodel.f_pair(p, rule)
         elif kind == "tet" and costmodel.is_tet_ref_tile(r["tile"]):   # the reference-matrix GEMM
             r["alg_flops_per_element"] = costmodel.f_tet_reference(n)

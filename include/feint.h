@@ -251,7 +251,7 @@ void feint_mixed_plan_destroy(feint_mixed_plan *plan);
    Each (degree, form) has several compiled variants: tile shapes of the MFMA
    kernels (16x16 output tiles per wave), for FP64 and FP32 the kernels that
    contract per triangle point (the rule and the basis factorised along
-   zeta: fewer flops, the default from p = 3), and for FP64 and FP32 at
+   zeta: fewer flops) or, on prisms, by pairs of triangle functions, and for FP64 and FP32 at
    p <= 3 vector-ALU kernels that give each element a group of lanes (Sec.
    2.2's operation counts make the contraction too small at low degree to
    fill MFMA tiles; which side of the crossover a degree falls on is what
@@ -270,10 +270,13 @@ feint_status feint_tile_set(int p, feint_form form, int tile);
    Sec. 4), or "KxTNf" (contraction per triangle point, or per plane point
    for hexahedra: K zeta rows of shape functions by TN column tiles per
    wave, FP64 and FP32), or "0xWf" (prisms: products of pairs of triangle
-   functions, W waves per workgroup; the default from p = 3, in the split
-   forms from p = 2),
+   functions, W waves per workgroup; the default in FP64 from p = 3, in the
+   split forms and in FP32 from p = 2, there not for small batches or, in FP32,
+   large ones),
    or "vL" (vector-ALU kernel, L lanes per element); "o2" marks a
-   two-waves-per-SIMD register budget. */
+   two-waves-per-SIMD register budget.  At p = 2 "2x2so4" is "2x2s" for
+   small batches and "0x2fo4" for larger ones, "v18o4" "0x2fo4" for small
+   batches and for coefficients at the vertices, else "v18o2". */
 feint_status feint_tile_describe(int p, feint_form form, int tile, char *buf, size_t len);
 feint_status feint_autotune(const feint_elements *el, int p, feint_form form,
                             void *A, void *b, int reps, double *best_ms, void *stream);

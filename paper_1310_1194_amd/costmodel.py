@@ -234,7 +234,10 @@ def pair_mfma_flops(p: int, rule: str = "collapsed", split: bool = False) -> int
 
 
 def f_kernel(p: int, rule: str, desc: str) -> int:
-    """Algorithmic flops per element of the algorithm the tile runs."""
+    """Algorithmic flops per element of the algorithm the tile runs (at p = 2
+    "2x2so4" runs the pair products, but for small batches)."""
+    if desc == "2x2so4":
+        return f_pair(p, rule)
     return f_pair(p, rule) if is_pair_tile(desc) else f_kf(p, rule) if is_kf_tile(desc) else f_dom(p, rule)
 
 

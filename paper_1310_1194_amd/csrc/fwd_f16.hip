@@ -7,6 +7,7 @@ namespace {
 const FwdVariant v1[] = {
     FEINT_K32S(1, FP16X3, 1, 1, true, 1)};
 const FwdVariant v2[] = {
+    FEINT_P2_SPLIT(FP16X3, 0, 1024),
     FEINT_KP(2, FP16X3),
     FEINT_K32S(2, FP16X3, 2, 2, true, 1)};
 const FwdVariant v3[] = {

@@ -1,6 +1,6 @@
 // Forward kernels, FP32 form: compiled variants per degree (the first is the default until the
 // autotuner picks another): vector-ALU kernels at low degree, v_mfma_f32_16x16x4_f32 tiles point by point,
-// and from p = 3 the products of pairs of triangle functions (KP, "0xWf") and the contraction per triangle
+// from p = 2 the products of pairs of triangle functions (KP, "0xWf") and the contraction per triangle
 // point (KF); "KxTNfw" is KF with the waves of an element sharing its point blocks through LDS (KF2).
 #include "fwd_registry.h"
 
@@ -15,6 +15,7 @@ const FwdVariant v1[] = {
     FEINT_K4S(1, float, 1, 1, 8, 1),
     FEINT_KSC(1, float, 1, 1, 1), FEINT_KF_R(1, float, 2, 2, 2, 0)};
 const FwdVariant v2[] = {
+    FEINT_P2_F32,
     FEINT_KP(2, F32),
     FEINT_KV(2, float, 18, 2),
     FEINT_KV(2, float, 32, 2),

@@ -40,10 +40,10 @@
 //   FP32    p = 3 0.98 -> 0.51, 4 2.93 -> 2.19, 5 3.86 -> 1.59, 6 5.06 -> 2.31, 7 12.4 -> 4.27
 //   bf16x3  p = 2 0.83 -> 0.54, 3 1.41 -> 0.48, 4 2.67 -> 1.61, 5 2.56 -> 1.02, 6 2.76 -> 1.32, 7 6.44 -> 2.02
 //   fp16x3  p = 2 1.00 -> 0.60, 3 1.42 -> 0.51, 4 2.78 -> 1.74, 5 3.18 -> 1.02, 6 3.76 -> 1.37, 7 7.31 -> 2.07
-// and at every smaller batch (one element: p = 7 FP64 0.13 against 0.40, p = 4 0.015
-// against 0.025).  At p = 2 (262144 elements) the kernel of lanes per element is level in
-// FP32 (0.55 ms; 64 elements 0.012 here against 0.017) and faster in FP64 (0.82 against
-// 0.93), where this one is not compiled.
+// and from p = 3 at every smaller batch (one element: p = 7 FP64 0.13 against 0.40, p = 4
+// 0.015 against 0.025).  At p = 2 the number of elements decides (fwd_registry.h); in FP64
+// (262144 elements 0.82 of the kernel of lanes per element against 0.93) and in FP32 on the
+// symmetric rule this one is not compiled.
 // Errors against 64 bits are no larger in any form (FP32 p = 7 1.9e-7, was 3.1e-7;
 // bf16x3 p = 4 2.3e-6, was 4.3e-6): fewer terms are summed per entry.
 #pragma once

@@ -170,6 +170,34 @@ int64_t items_pair(int64_t ne) { return (ne + K::EPB_ - 1) / K::EPB_ * 4; }
                &launch_pair<KPOf<P, F, R, GEO>, PairShape<P, F>::W>, &items_pair<KPOf<P, F, R, GEO>>}
 #define FEINT_KP(P, F) FEINT_KPG(P, F, 0, PrismGeo)
 
+// Two kernels at p = 2 by the number of elements: FEW up to LINE of them (with
+// coefficients at the vertices at any number, if FIELDS), MANY past it ("2x2so4":
+// "2x2s", then "0x2fo4"; "v18o4": "0x2fo4", then "v18o2").  At p = 2 an
+// element of the pair products passes six barriers for little work; a batch of a few
+// elements per CU waits for them, and where the rule has few points the kernels that
+// form W_q once per element and need no barrier are as fast at any size.  us, pair
+// products against the other (200001 elements unless stated):
+//   FP32 collapsed, lanes per element: 300 elements 10.8, 16.5, 16000 38, 39, 32000 69, 64, 408, 368; coefficients
+//     at the vertices 12.3, 20.4, 45, 56, 83, 98, 500, 624.  Symmetric rule: 300 10.9, 11.2, 4000 14.8, 12.8, 379,
+//     262; 12.0, 12.3, 17.9, 15.2, 480, 350: lanes per element at every size.
+//   bf16x3 collapsed, staged products: 1000 11.2, 10.8, 2000 11.5, 11.5, 384, 633; vertices 13.4, 10.5, 13.7, 14.3, 478, 944;
+//     symmetric 1000 11.0, 11.0, 4000 14.4, 13.6, 8000 20.2, 22.2, 370, 427; 13.3, 10.1, 17.5, 15.2, 25.8, 25.2, 471, 619.
+//   fp16x3 collapsed: 1000 12.6, 10.7, 2000 12.9, 13.1, 448, 755; vertices 15.0, 12.9, 15.3, 17.0, 537, 1081;
+//     symmetric 1000 12.2, 11.0, 2000 12.3, 11.7, 4000 16.1, 19.1, 424, 652; 14.6, 11.7, 14.8, 15.5, 18.7, 25.4, 517, 986.
+template <auto FEW, auto MANY, int LINE, bool FIELDS>
+void launch_by_count(const FwdParams &prm, hipStream_t s) {
+    if (prm.ne <= LINE || (FIELDS && prm.fD)) FEW(prm, s);
+    else MANY(prm, s);
+}
+#define FEINT_P2_F32                                                                                        \
+    FwdVariant{0, 18, 3, 4, &launch_by_count<&launch_pair<KPOf<2, F32>, PairShape<2, F32>::W>,              \
+                                             &launch_direct<KV<2, float, 18>, 2>, 16384, true>,             \
+               &items_of<KV<2, float, 18>>}
+#define FEINT_P2_SPLIT(F, R, LINE)                                                                          \
+    FwdVariant{2, 2, 1, 4, &launch_by_count<&launch_staged<K32S<2, F, 2, 2, true, R>, 1>,                  \
+                                             &launch_pair<KPOf<2, F, R>, PairShape<2, F>::W>, LINE, false>, \
+               &items_of<K32S<2, F, 2, 2, true, R>>}
+
 #define FEINT_K4U(P, T, TM, TN, W) FEINT_K4U_R(P, T, TM, TN, W, 0)
 #define FEINT_KSC(P, T, TM, TN, W) FEINT_KSC_R(P, T, TM, TN, W, 0)
 #define FEINT_K4S(P, T, TM, TN, SP, W) FEINT_K4S_R(P, T, TM, TN, SP, W, 0)

@@ -18,7 +18,7 @@ const FwdVariant d6[] = {FEINT_KPG(6, F64, S, PrismGeo), FEINT_KF2Z_R(6, double,
 const FwdVariant d7[] = {FEINT_KPG(7, F64, S, PrismGeo), FEINT_KF2Z_R(7, double, 2, 2, 2, 2, S), FEINT_KF2_R(7, double, 2, 2, 2, S), FEINT_KF_R(7, double, 4, 2, 1, S), FEINT_KF_R(7, double, 2, 2, 1, S), FEINT_KF_R(7, double, 4, 1, 1, S), FEINT_K4U_R(7, double, 9, 2, 1, S), FEINT_K4U_R(7, double, 6, 2, 1, S), FEINT_KSC_R(7, double, 6, 2, 1, S)};
 // FP32
 const FwdVariant f1[] = {FEINT_KM(float, 2, S), FEINT_KE_R(1, float, 3, S), FEINT_KV_R(1, float, 8, 2, S), FEINT_K4S_R(1, float, 1, 1, 8, 1, S), FEINT_KSC_R(1, float, 1, 1, 1, S), FEINT_KF_R(1, float, 2, 2, 2, S)};
-const FwdVariant f2[] = {FEINT_KPG(2, F32, S, PrismGeo), FEINT_KV_R(2, float, 18, 2, S), FEINT_K4S_R(2, float, 2, 2, 8, 1, S), FEINT_KSC_R(2, float, 2, 2, 1, S), FEINT_KF_R(2, float, 3, 3, 2, S)};
+const FwdVariant f2[] = {FEINT_KV_R(2, float, 18, 2, S), FEINT_K4S_R(2, float, 2, 2, 8, 1, S), FEINT_KSC_R(2, float, 2, 2, 1, S), FEINT_KF_R(2, float, 3, 3, 2, S)};
 const FwdVariant f3[] = {FEINT_KPG(3, F32, S, PrismGeo), FEINT_KF_R(3, float, 4, 4, 2, S), FEINT_KF2_R(3, float, 4, 2, 2, S), FEINT_K4S_R(3, float, 3, 3, 8, 1, S), FEINT_KV_R(3, float, 40, 2, S), FEINT_KSC_R(3, float, 3, 3, 1, S)};
 const FwdVariant f4[] = {FEINT_KPG(4, F32, S, PrismGeo), FEINT_KF2_R(4, float, 5, 3, 2, S), FEINT_KF_R(4, float, 5, 3, 1, S), FEINT_KF_R(4, float, 5, 5, 1, S), FEINT_K4U_R(4, float, 5, 5, 1, S), FEINT_K4S_R(4, float, 5, 5, 8, 1, S), FEINT_KSC_R(4, float, 5, 5, 1, S)};
 const FwdVariant f5[] = {FEINT_KPG(5, F32, S, PrismGeo), FEINT_KF2_R(5, float, 6, 3, 2, S), FEINT_KF_R(5, float, 6, 6, 1, S), FEINT_KF_R(5, float, 6, 3, 1, S), FEINT_K4S_R(5, float, 8, 4, 8, 1, S), FEINT_K4U_R(5, float, 8, 8, 1, S), FEINT_KSC_R(5, float, 8, 4, 1, S)};
@@ -26,7 +26,7 @@ const FwdVariant f6[] = {FEINT_KPG(6, F32, S, PrismGeo), FEINT_KF2_R(6, float, 2
 const FwdVariant f7[] = {FEINT_KPG(7, F32, S, PrismGeo), FEINT_KF2Z_R(7, float, 4, 2, 4, 2, S), FEINT_KF2_R(7, float, 4, 2, 2, S), FEINT_KF_R(7, float, 8, 2, 1, S), FEINT_K4U_R(7, float, 9, 6, 1, S), FEINT_K4U_R(7, float, 9, 3, 1, S), FEINT_KSC_R(7, float, 9, 3, 1, S)};
 // bf16x3
 const FwdVariant b1[] = {FEINT_K32S_R(1, BF16X3, 1, 1, true, 1, S)};
-const FwdVariant b2[] = {FEINT_KPG(2, BF16X3, S, PrismGeo), FEINT_K32S_R(2, BF16X3, 2, 2, true, 1, S)};
+const FwdVariant b2[] = {FEINT_P2_SPLIT(BF16X3, S, 4096), FEINT_KPG(2, BF16X3, S, PrismGeo), FEINT_K32S_R(2, BF16X3, 2, 2, true, 1, S)};
 const FwdVariant b3[] = {FEINT_KPG(3, BF16X3, S, PrismGeo), FEINT_K32S_R(3, BF16X3, 3, 3, true, 1, S)};
 const FwdVariant b4[] = {FEINT_KPG(4, BF16X3, S, PrismGeo), FEINT_K32P_R(4, BF16X3, 5, 5, 1, S), FEINT_K32U_R(4, BF16X3, 5, 3, 2, S)};
 const FwdVariant b5[] = {FEINT_KPG(5, BF16X3, S, PrismGeo), FEINT_KF2G_R(5, 3, 2, 2, S), FEINT_K32S_R(5, BF16X3, 8, 4, false, 1, S), FEINT_K32U_R(5, BF16X3, 8, 4, 1, S)};
@@ -34,7 +34,7 @@ const FwdVariant b6[] = {FEINT_KPG(6, BF16X3, S, PrismGeo), FEINT_KF2G_R(6, 7, 1
 const FwdVariant b7[] = {FEINT_KPG(7, BF16X3, S, PrismGeo), FEINT_KF2G_R(7, 4, 2, 2, S), FEINT_KF2G_R(7, 4, 1, 2, S), FEINT_K32P_R(7, BF16X3, 6, 6, 1, S), FEINT_K32P_R(7, BF16X3, 6, 3, 1, S)};
 // fp16x3
 const FwdVariant h1[] = {FEINT_K32S_R(1, FP16X3, 1, 1, true, 1, S)};
-const FwdVariant h2[] = {FEINT_KPG(2, FP16X3, S, PrismGeo), FEINT_K32S_R(2, FP16X3, 2, 2, true, 1, S)};
+const FwdVariant h2[] = {FEINT_P2_SPLIT(FP16X3, S, 2048), FEINT_KPG(2, FP16X3, S, PrismGeo), FEINT_K32S_R(2, FP16X3, 2, 2, true, 1, S)};
 const FwdVariant h3[] = {FEINT_KPG(3, FP16X3, S, PrismGeo), FEINT_K32S_R(3, FP16X3, 3, 3, true, 1, S)};
 const FwdVariant h4[] = {FEINT_KPG(4, FP16X3, S, PrismGeo), FEINT_K32P_R(4, FP16X3, 5, 5, 1, S), FEINT_K32U_R(4, FP16X3, 5, 3, 2, S)};
 const FwdVariant h5[] = {FEINT_KPG(5, FP16X3, S, PrismGeo), FEINT_K32S_R(5, FP16X3, 8, 4, false, 1, S), FEINT_KF2GH_R(5, 3, 2, 2, S), FEINT_K32U_R(5, FP16X3, 8, 4, 1, S)};
