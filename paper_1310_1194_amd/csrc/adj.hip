@@ -42,135 +42,10 @@ struct AdjParams {
     const void *lamT;   // both in the form's precision
     // products of pairs of triangle functions (FP64): transposed table, stacked line
     // products, orbits, points of the reflected pairs
-    const double *padj, *plines, *pqw;
+    const double *padj, *plines;
     const uint32_t *potab;
     const uint16_t *ppts;
 };
-
-// The chain rule at one point qp = (xi1, xi2, zeta, w): gradients of <W_q, S> +
-// w det J f tau with respect to the element's inputs, added to gr.
-__device__ inline void chain_rule_at(const ElemIn &E, const double *qp, const double S[16], double tau, double gr[32]) {
-    const double xi1 = qp[0], xi2 = qp[1], ze = qp[2], w = qp[3];
-    double K[9];
-    const double det = prism_jacobian(E.X, xi1, xi2, ze, K);
-    const double wd = w * det;
-    double v[3], KD[9], M[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        v[i] = K[3 * i] * E.be[0] + K[3 * i + 1] * E.be[1] + K[3 * i + 2] * E.be[2];
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            KD[3 * i + j] = K[3 * i] * E.D[j] + K[3 * i + 1] * E.D[3 + j] + K[3 * i + 2] * E.D[6 + j];
-    }
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            M[3 * i + j] = KD[3 * i] * K[3 * j] + KD[3 * i + 1] * K[3 * j + 1] + KD[3 * i + 2] * K[3 * j + 2];
-    const double s[3] = {S[1], S[2], S[3]};
-    double Sp[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) Sp[3 * i + j] = S[4 * (i + 1) + 1 + j];
-    double contr = E.c * S[0];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        contr += v[i] * s[i];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) contr += M[3 * i + j] * Sp[3 * i + j];
-    }
-    const double Lq = wd * (contr + E.f * tau);
-    // gradient slots: vertices 0..17, D 18..26, beta 27..29, c 30, f 31
-    gr[30] += wd * S[0];
-    gr[31] += wd * tau;
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-        gr[27 + m] += wd * (K[m] * s[0] + K[3 + m] * s[1] + K[6 + m] * s[2]);
-    double SK[9];   // S' K
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            SK[3 * i + j] = Sp[3 * i] * K[j] + Sp[3 * i + 1] * K[3 + j] + Sp[3 * i + 2] * K[6 + j];
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-#pragma unroll
-        for (int n = 0; n < 3; ++n)   // dD_mn = wd sum_k K_km (S'K)_kn
-            gr[18 + 3 * m + n] += wd * (K[m] * SK[n] + K[3 + m] * SK[3 + n] + K[6 + m] * SK[6 + n]);
-    // dL/dK = wd (S' K D^T + S'^T K D + s beta^T)
-    double StK[9], dK[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            StK[3 * i + j] = Sp[i] * K[j] + Sp[3 + i] * K[3 + j] + Sp[6 + i] * K[6 + j];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            dK[3 * i + j] = wd * (SK[3 * i] * E.D[3 * j] + SK[3 * i + 1] * E.D[3 * j + 1] + SK[3 * i + 2] * E.D[3 * j + 2]
-                                  + StK[3 * i] * E.D[j] + StK[3 * i + 1] * E.D[3 + j] + StK[3 * i + 2] * E.D[6 + j]
-                                  + s[i] * E.be[j]);
-    // dL/dJ = Lq K^T - K^T dK K^T
-    double KtdK[9], dJ[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            KtdK[3 * i + j] = K[i] * dK[j] + K[3 + i] * dK[3 + j] + K[6 + i] * dK[6 + j];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            dJ[3 * i + j] = Lq * K[3 * j + i] - (KtdK[3 * i] * K[3 * j] + KtdK[3 * i + 1] * K[3 * j + 1] + KtdK[3 * i + 2] * K[3 * j + 2]);
-    // J columns: c0 = s(v1-v0)+t(v4-v3), c1 = s(v2-v0)+t(v5-v3), c2 = (l0(v3-v0)+l1(v4-v1)+l2(v5-v2))/2
-    const double t = 0.5 * (1.0 + ze), sb = 0.5 * (1.0 - ze), l0 = 1.0 - xi1 - xi2;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double g0 = dJ[3 * d], g1 = dJ[3 * d + 1], g2 = 0.5 * dJ[3 * d + 2];
-        gr[0 + d] += -sb * g0 - sb * g1 - l0 * g2;
-        gr[3 + d] += sb * g0 - xi1 * g2;
-        gr[6 + d] += sb * g1 - xi2 * g2;
-        gr[9 + d] += -t * g0 - t * g1 + l0 * g2;
-        gr[12 + d] += t * g0 + xi1 * g2;
-        gr[15 + d] += t * g1 + xi2 * g2;
-    }
-}
-
-// Sum the lanes' 32 partial gradients over the wave by recursive halving:
-// at each step a lane keeps half of its values and adds the partner's copy
-// of that half.  Lanes 2c and 2c+1 end with component c.
-__device__ inline double reduce_scatter32(double v[32], int lane) {
-    double w16[16], w8[8], w4[4], w2[2];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const bool up = lane & 32;
-        const double keep = up ? v[j + 16] : v[j], send = up ? v[j] : v[j + 16];
-        w16[j] = keep + __shfl_xor(send, 32, 64);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const bool up = lane & 16;
-        const double keep = up ? w16[j + 8] : w16[j], send = up ? w16[j] : w16[j + 8];
-        w8[j] = keep + __shfl_xor(send, 16, 64);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool up = lane & 8;
-        const double keep = up ? w8[j + 4] : w8[j], send = up ? w8[j] : w8[j + 4];
-        w4[j] = keep + __shfl_xor(send, 8, 64);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const bool up = lane & 4;
-        const double keep = up ? w4[j + 2] : w4[j], send = up ? w4[j] : w4[j + 2];
-        w2[j] = keep + __shfl_xor(send, 4, 64);
-    }
-    const bool up = lane & 2;
-    double r = (up ? w2[1] : w2[0]) + __shfl_xor(up ? w2[0] : w2[1], 2, 64);
-    return r + __shfl_xor(r, 1, 64);
-}
 
 template <int P, typename T, int TA, int TB, int R = 0>
 struct Adj {
@@ -183,15 +58,141 @@ struct Adj {
 
     struct Smem { double S[4][64][WROW<double>::value]; };
 
+    // The chain rule at point q: gradients of <W_q, S> + w det J f tau with respect to the
+    // element's inputs, added to gr; tau is given, or sum_a g_a phi_a(q) with the load vector.
+    // (Members of each kernel's own Adj: as functions that the kernels share, the FP32 ones at
+    // p = 2 took 136 registers for 128, a wave per SIMD less: symmetric rule, 200000
+    // elements, 0.675 ms against 0.615.)
+    template <bool GIVEN = false>
     __device__ static void chain_rule(const AdjParams &prm, const ElemIn &E, int q, const double S[16],
-                                      bool with_load, int64_t e, double gr[32]) {
-        double tau = 0.0;
-        if (with_load) {
+                                      bool with_load, int64_t e, double gr[32], double given = 0.0) {
+        const double *qp = prm.qw + 4 * q;
+        const double xi1 = qp[0], xi2 = qp[1], ze = qp[2], w = qp[3];
+        double K[9];
+        const double det = prism_jacobian(E.X, xi1, xi2, ze, K);
+        const double wd = w * det;
+        double tau = GIVEN ? given : 0.0;
+        if (!GIVEN && with_load) {
             const T *gv = (const T *)prm.g + e * N;
             const double *phi = prm.B64 + (size_t)q * 4 * NP;
             for (int a = 0; a < N; ++a) tau += (double)gv[a] * phi[a];
         }
-        chain_rule_at(E, prm.qw + 4 * q, S, tau, gr);
+        double v[3], KD[9], M[9];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            v[i] = K[3 * i] * E.be[0] + K[3 * i + 1] * E.be[1] + K[3 * i + 2] * E.be[2];
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                KD[3 * i + j] = K[3 * i] * E.D[j] + K[3 * i + 1] * E.D[3 + j] + K[3 * i + 2] * E.D[6 + j];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                M[3 * i + j] = KD[3 * i] * K[3 * j] + KD[3 * i + 1] * K[3 * j + 1] + KD[3 * i + 2] * K[3 * j + 2];
+        const double s[3] = {S[1], S[2], S[3]};
+        double Sp[9];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) Sp[3 * i + j] = S[4 * (i + 1) + 1 + j];
+        double contr = E.c * S[0];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            contr += v[i] * s[i];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) contr += M[3 * i + j] * Sp[3 * i + j];
+        }
+        const double Lq = wd * (contr + E.f * tau);
+        // gradient slots: vertices 0..17, D 18..26, beta 27..29, c 30, f 31
+        gr[30] += wd * S[0];
+        gr[31] += wd * tau;
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+            gr[27 + m] += wd * (K[m] * s[0] + K[3 + m] * s[1] + K[6 + m] * s[2]);
+        double SK[9];   // S' K
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                SK[3 * i + j] = Sp[3 * i] * K[j] + Sp[3 * i + 1] * K[3 + j] + Sp[3 * i + 2] * K[6 + j];
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+#pragma unroll
+            for (int n = 0; n < 3; ++n)   // dD_mn = wd sum_k K_km (S'K)_kn
+                gr[18 + 3 * m + n] += wd * (K[m] * SK[n] + K[3 + m] * SK[3 + n] + K[6 + m] * SK[6 + n]);
+        // dL/dK = wd (S' K D^T + S'^T K D + s beta^T)
+        double StK[9], dK[9];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                StK[3 * i + j] = Sp[i] * K[j] + Sp[3 + i] * K[3 + j] + Sp[6 + i] * K[6 + j];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                dK[3 * i + j] = wd * (SK[3 * i] * E.D[3 * j] + SK[3 * i + 1] * E.D[3 * j + 1] + SK[3 * i + 2] * E.D[3 * j + 2]
+                                      + StK[3 * i] * E.D[j] + StK[3 * i + 1] * E.D[3 + j] + StK[3 * i + 2] * E.D[6 + j]
+                                      + s[i] * E.be[j]);
+        // dL/dJ = Lq K^T - K^T dK K^T
+        double KtdK[9], dJ[9];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                KtdK[3 * i + j] = K[i] * dK[j] + K[3 + i] * dK[3 + j] + K[6 + i] * dK[6 + j];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                dJ[3 * i + j] = Lq * K[3 * j + i] - (KtdK[3 * i] * K[3 * j] + KtdK[3 * i + 1] * K[3 * j + 1] + KtdK[3 * i + 2] * K[3 * j + 2]);
+        // J columns: c0 = s(v1-v0)+t(v4-v3), c1 = s(v2-v0)+t(v5-v3), c2 = (l0(v3-v0)+l1(v4-v1)+l2(v5-v2))/2
+        const double t = 0.5 * (1.0 + ze), sb = 0.5 * (1.0 - ze), l0 = 1.0 - xi1 - xi2;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double g0 = dJ[3 * d], g1 = dJ[3 * d + 1], g2 = 0.5 * dJ[3 * d + 2];
+            gr[0 + d] += -sb * g0 - sb * g1 - l0 * g2;
+            gr[3 + d] += sb * g0 - xi1 * g2;
+            gr[6 + d] += sb * g1 - xi2 * g2;
+            gr[9 + d] += -t * g0 - t * g1 + l0 * g2;
+            gr[12 + d] += t * g0 + xi1 * g2;
+            gr[15 + d] += t * g1 + xi2 * g2;
+        }
+    }
+
+    // Sum the lanes' 32 partial gradients over the wave by recursive halving:
+    // at each step a lane keeps half of its values and adds the partner's copy
+    // of that half.  Lanes 2c and 2c+1 end with component c.
+    __device__ static double reduce_scatter32(double v[32], int lane) {
+        double w16[16], w8[8], w4[4], w2[2];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const bool up = lane & 32;
+            const double keep = up ? v[j + 16] : v[j], send = up ? v[j] : v[j + 16];
+            w16[j] = keep + __shfl_xor(send, 32, 64);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool up = lane & 16;
+            const double keep = up ? w16[j + 8] : w16[j], send = up ? w16[j] : w16[j + 8];
+            w8[j] = keep + __shfl_xor(send, 16, 64);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool up = lane & 8;
+            const double keep = up ? w8[j + 4] : w8[j], send = up ? w8[j] : w8[j + 4];
+            w4[j] = keep + __shfl_xor(send, 8, 64);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const bool up = lane & 4;
+            const double keep = up ? w4[j + 2] : w4[j], send = up ? w4[j] : w4[j + 2];
+            w2[j] = keep + __shfl_xor(send, 4, 64);
+        }
+        const bool up = lane & 2;
+        double r = (up ? w2[1] : w2[0]) + __shfl_xor(up ? w2[0] : w2[1], 2, 64);
+        return r + __shfl_xor(r, 1, 64);
     }
 
     __device__ static void run(const AdjParams &prm, int64_t e, int blk, int wave, Smem &sm) {
@@ -435,7 +436,7 @@ struct KFA {
                     for (int k = 0; k < 16; ++k) S[k] = sm.S[wave][lane][k];
                     Base::chain_rule(prm, E, q, S, with_load, e, gr);
                 }
-                gacc += reduce_scatter32(gr, lane);
+                gacc += Base::reduce_scatter32(gr, lane);
             }
             wave_sync();
         }
@@ -579,7 +580,7 @@ struct KFA2 {
                     for (int k = 0; k < 16; ++k) S[k] = sm.S[el][q][k];
                     Base::chain_rule(prm, E, q, S, true, e, gr);
                 }
-                gacc += reduce_scatter32(gr, lane);
+                gacc += Base::reduce_scatter32(gr, lane);
             }
             if ((lane & 1) == 0) sm.red[wave][lane >> 1] = gacc;
         }
@@ -771,7 +772,7 @@ feint_status adj_setup(const feint_elements *el, int p, feint_form form, const v
     prm.qw = T->qw; prm.B64 = T->B64;
     prm.BT = form == FEINT_FP64 ? (const void *)T->BT64 : (const void *)T->BT32;
     prm.tau = form == FEINT_FP64 ? (const void *)T->tau64 : (const void *)T->tau32;
-    prm.padj = T->padj; prm.plines = T->plines; prm.pqw = T->pqw; prm.potab = T->potab; prm.ppts = T->ppts;
+    prm.padj = T->padj; prm.plines = T->plines; prm.potab = T->potab; prm.ppts = T->ppts;
     prm.lamT = form == FEINT_FP64 ? (const void *)T->lam : (const void *)T->lam32;
     return FEINT_OK;
 }

@@ -34,6 +34,7 @@ namespace feint {
 // WPE waves per element (half of them on each parity), EPW elements per workgroup.
 template <int P, int R, int WPE, int EPW>
 struct AdjPair {
+    typedef Adj<P, double, 1, 1, R> Chain;
     typedef f64x4 V4;
     typedef double V2 __attribute__((ext_vector_type(2)));
     static constexpr int WPE_ = WPE;
@@ -330,11 +331,9 @@ struct AdjPair {
                     double tau = 0.0;
 #pragma unroll
                     for (int k = 0; k < NK; ++k) tau += ((const double *)prm.lamT)[k * NK + m] * sm.u[el][ij * NK + k];
-                    const double *pt = prm.pqw + 4 * task;
-                    const double qp[4] = {pt[0], pt[1], pt[2], set < NPAIR ? pt[3] : 2.0 * pt[3]};
-                    chain_rule_at(E, qp, Sq, tau, gr);
+                    Chain::template chain_rule<true>(prm, E, m * NIJ + ij, Sq, false, e, gr, tau);
                 }
-                gacc += reduce_scatter32(gr, lane);
+                gacc += Chain::reduce_scatter32(gr, lane);
             }
         }
         if ((lane & 1) == 0) sm.red[wave][lane >> 1] = gacc;
