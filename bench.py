@@ -919,7 +919,7 @@ def bench_mixed(args):
             errs[f"p{d}"] = {"rel_err_A": gA_, "rel_err_A_max_elem": mA_, "rel_err_b": gb_, "elements": len(idx)}
     counts = np.bincount(batch.p, minlength=7)
     fdom = sum(int(counts[d]) * costmodel.f_dom(d) for d in range(1, 7))
-    shapes = plan.tile_describe(plan.tile).split(",")     # one entry per degree 1..6
+    shapes = plan.tile_describe(plan.tile).split("|")[0].split(",")     # one entry per degree 1..6
     flops = sum(int(counts[d]) * costmodel.f_kernel(d, "collapsed", shapes[d - 1]) for d in range(1, 7))
     es = 8 if form == "fp64" else 4
     bytes_ = sum(int(counts[d]) * costmodel.bytes_per_element(d, es) for d in range(1, 7))

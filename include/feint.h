@@ -162,8 +162,7 @@ feint_status feint_adjoint_autotune(const feint_elements *el, int p, feint_form 
 
 /* ---- Mixed-degree batches -------------------------------------------------
    Elements of degrees 1..6 in any order are bucketed by degree and run as one
-   launch per bucket, or as one persistent launch (small FP64 batches, and the
-   other tile sets) (the paper's Sec. 2.2 advice to group elements by
+   launch per bucket, or as one persistent launch, by the tile set (the paper's Sec. 2.2 advice to group elements by
    type and degree so that reference data is fetched once per group).
    Outputs are packed in element order: element e's matrix starts at
    offA[e] elements of the output dtype, its vector at offb[e], where offA
@@ -241,8 +240,9 @@ int feint_mixed_tile_get(const feint_mixed_plan *plan);
 feint_status feint_mixed_tile_set(feint_mixed_plan *plan, int tile);
 /* Describe tile set `tile` into buf: the per-degree shapes for p = 1..6,
    comma-separated, each "TMxTN" (16x16 MFMA tiles per wave), "0xWf" (products
-   of pairs of triangle functions) or "vL" (vector-ALU kernel, L lanes per
-   element).  INVALID_ARG for a null plan or
+   of pairs of triangle functions, a launch per degree) or "vL" (vector-ALU
+   kernel, L lanes per element).  FP64's first set, "a|b", is a, and b (set 1) for
+   batches of up to 400 elements.  INVALID_ARG for a null plan or
    buffer or an index out of range. */
 feint_status feint_mixed_tile_describe(const feint_mixed_plan *plan, int tile, char *buf, size_t len);
 void feint_mixed_plan_destroy(feint_mixed_plan *plan);

@@ -21,8 +21,11 @@
 // The launches per degree give every kernel its own registers, LDS and workgroup
 // size; k_persist's functions share one budget of a wave per SIMD, and its queue has
 // no workgroup to share G across.  262144 elements: FP32 9.7 ms against 30.5, FP64
-// 18.5 against 67.4; 1024 elements: 0.151 against 0.188, 0.209 against 0.364; at 300
-// elements in FP64 six short launches in a row gain nothing (0.161 against 0.159).
+// 18.5 against 67.4; 1000 elements 0.127 against 0.168, 0.188 against 0.335; 300 elements
+// 0.117 against 0.149.  In FP64 six short launches one after the other take 0.15 to 0.17
+// ms for any small batch: 8 elements 0.151 against 0.093, 300 0.171 against 0.133, 400
+// 0.174 against 0.173, 512 0.185 against 0.205; so its first set takes the persistent launch
+// up to 400.
 // No memset nodes are used (counters are cleared by kernels), so the whole
 // sequence is safe to capture and replay.
 #include <hip/hip_runtime.h>
@@ -319,6 +322,7 @@ struct MixVariant {
     const void *kernel;
     MixSizes sz;
     const char *desc;
+    int64_t small = 0;          // batches of up to so many elements take set 1
 };
 
 template <class K1, class K2, class K3, class K4_, class K5, class K6>
@@ -339,11 +343,13 @@ MixVariant make_variant(const char *desc) {
 }
 
 const MixVariant *mix_variants(int form, int *count) {
-    // first the launches per degree; the persistent sets: p = 1, 2 on the vector ALUs (v8: 8 lanes per element, v18: 18), MFMA tiles above:
+    // first the launches per degree (FP64: for batches past 400 elements, and last at every size); the persistent sets: p = 1, 2 on the vector ALUs (v8: 8 lanes per element, v18: 18), MFMA tiles above:
     // the contraction per triangle point (KxTNf) or point by point (TMxTN); the last set
     // of each form keeps point-by-point MFMA tiles at every degree for comparison
+    static_assert(PairShape<3, F32>::NW == 4 && PairShape<4, F32>::NW == 4 && PairShape<5, F32>::NW == 4 && PairShape<6, F32>::NW == 8 &&
+                  PairShape<3, F64>::NW == 2 && PairShape<4, F64>::NW == 4 && PairShape<5, F64>::NW == 4 && PairShape<6, F64>::NW == 8, "descriptions");
     static const MixVariant f32[] = {
-        MixVariant{nullptr, MixSizes{}, "v8,v18,0x4f,0x4f,0x4f,0x4f"},
+        MixVariant{nullptr, MixSizes{}, "v8,v18,0x4f,0x4f,0x4f,0x8f"},
         make_variant<KV<1, float, 8>, KV<2, float, 18>, KF<3, float, 4, 4>, KF<4, float, 5, 3>,
                      KF<5, float, 6, 3>, KF<6, float, 7, 4>>("v8,v18,4x4f,5x3f,6x3f,7x4f"),
         make_variant<KV<1, float, 8>, KV<2, float, 18>, KF<3, float, 4, 4>, KF<4, float, 5, 5>,
@@ -362,7 +368,7 @@ const MixVariant *mix_variants(int form, int *count) {
                      K4<5, float, 8, 2>, K4<6, float, 13, 1>>("1x1,2x2,3x3,5x3,8x2,13x1"),
     };
     static const MixVariant f64[] = {
-        MixVariant{nullptr, MixSizes{}, "v8,v18,0x4f,0x4f,0x4f,0x8f"},
+        MixVariant{nullptr, MixSizes{}, "v8,v18,0x2f,0x4f,0x4f,0x8f|v8,v18,4x2f,5x5f,6x2f,7x1f", 400},
         make_variant<KV<1, double, 8>, KV<2, double, 18>, KF<3, double, 4, 2>, KF<4, double, 5, 5>,
                      KF<5, double, 6, 2>, KF<6, double, 7, 1>>("v8,v18,4x2f,5x5f,6x2f,7x1f"),
         make_variant<KV<1, double, 8>, KV<2, double, 18>, KF<3, double, 4, 2>, KF<4, double, 5, 5>,
@@ -377,6 +383,7 @@ const MixVariant *mix_variants(int form, int *count) {
                      K4<5, double, 8, 2>, K4<6, double, 13, 1>>("v8,v18,3x1,5x2,8x2,13x1"),
         make_variant<K4<1, double, 1, 1>, K4<2, double, 2, 2>, K4<3, double, 3, 3>, K4<4, double, 5, 1>,
                      K4<5, double, 8, 1>, K4<6, double, 13, 1>>("1x1,2x2,3x3,5x1,8x1,13x1"),
+        MixVariant{nullptr, MixSizes{}, "v8,v18,0x2f,0x4f,0x4f,0x8f"},
     };
     if (form == FEINT_FP32) { *count = (int)(sizeof f32 / sizeof f32[0]); return f32; }
     if (form == FEINT_FP64) { *count = (int)(sizeof f64 / sizeof f64[0]); return f64; }
@@ -493,9 +500,7 @@ feint_status enqueue_persist(const MixedWork &w, const feint_elements *el, void 
                              const int64_t *offb, uint32_t *status, hipStream_t s, int tile) {
     int cnt = 0;
     const MixVariant *vars = mix_variants(w.form, &cnt);
-    // the launches per degree, but for small FP64 batches the first persistent set (measured
-    // at 300 elements: 0.195 against 0.161 ms; at 1024: 0.209 against 0.368)
-    if (!vars[tile].kernel && w.form == FEINT_FP64 && el->ne <= 512) tile = 1;
+    if (el->ne <= vars[tile].small) tile = 1;
     const MixVariant &v = vars[tile];
     if (!vars[tile].kernel) return enqueue_buckets(w, el, A, b, offA, offb, status, s);
     MixedParams mp;
