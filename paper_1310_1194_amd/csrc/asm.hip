@@ -46,7 +46,8 @@ struct feint_asm_plan {
     int64_t *row_ptr = nullptr;   // [ndof + 1]
     int32_t *col_idx = nullptr;   // [nnz]
     int64_t *inc_ptr = nullptr;   // [ndof + 1]
-    int64_t *inc = nullptr;       // [ne * n] rows e * n + a of the element matrices, dof by dof
+    void *inc = nullptr;          // [ne * n] rows e * n + a of the element matrices, dof by dof: uint32, or int64 if wide
+    bool wide = false;
     uint16_t *pos = nullptr;      // [ne][n][n]
 };
 
@@ -71,9 +72,9 @@ void parallel_for(int64_t n, F fn) {
 // LDS at a time; CH steps of G lanes cover a row of an element matrix.  The R rows'
 // element rows are one list: U of it are fetched while U are added, also across the
 // ends of rows, so that no row waits for its own first loads.
-template <typename T, int G, int CH, int U, int R>
+template <typename T, typename I, int G, int CH, int U, int R>
 __global__ __launch_bounds__(256) void assemble_rows(const T *__restrict__ A, const T *__restrict__ b,
-                                                     const int64_t *__restrict__ inc_ptr, const int64_t *__restrict__ inc,
+                                                     const int64_t *__restrict__ inc_ptr, const I *__restrict__ inc,
                                                      const int64_t *__restrict__ row_ptr, const uint16_t *__restrict__ pos,
                                                      int n, int64_t ndof, int cap, int accumulate, T *values, T *rhs) {
     static_assert(R < G, "a lane per row and the end of the last");
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256) void assemble_rows(const T *__restrict__ A, co
         };
         for (int xb = 0; xb < total; xb += G) {
             const int xn = total - xb < G ? total - xb : G;
-            const int64_t mine = lane < xn ? inc[k0 + xb + lane] : 0;
+            const int64_t mine = lane < xn ? (int64_t)inc[k0 + xb + lane] : 0;
             const T bm = c0 == 0 && lane < xn ? b[mine] : (T)0;
             struct Rows { T v[U][CH]; int at[U][CH]; } cur, nxt;
             auto fetch = [&](int x, Rows &f) {
@@ -158,29 +159,34 @@ __global__ __launch_bounds__(256) void assemble_rows(const T *__restrict__ A, co
     if (lane < nr && (en > st || !accumulate)) rhs[i0 + lane] = sum;
 }
 
-template <typename T, int G, int CH, int U, int R>
+template <typename T, typename I, int G, int CH, int U, int R>
 void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
     // 8 KB of LDS per wave at most (FP64): rows of more values are taken in several passes
     constexpr int CAP = 16 * G, GROUPS = 256 / G;
     const int cap = pl->max_row < CAP ? pl->max_row : CAP;
-    hipLaunchKernelGGL((assemble_rows<T, G, CH, U, R>), dim3((unsigned)((pl->ndof + GROUPS * R - 1) / (GROUPS * R))), dim3(256), GROUPS * cap * sizeof(T), st,
-                       (const T *)A, (const T *)b, pl->inc_ptr, pl->inc, pl->row_ptr, pl->pos, pl->n, pl->ndof, cap, accumulate,
+    hipLaunchKernelGGL((assemble_rows<T, I, G, CH, U, R>), dim3((unsigned)((pl->ndof + GROUPS * R - 1) / (GROUPS * R))), dim3(256), GROUPS * cap * sizeof(T), st,
+                       (const T *)A, (const T *)b, pl->inc_ptr, (const I *)pl->inc, pl->row_ptr, pl->pos, pl->n, pl->ndof, cap, accumulate,
                        (T *)values, (T *)rhs);
 }
 // Lanes per row: the fewest of a power of two that hold a row of the element matrix, a
 // wave from p = 3 on; loads in flight per lane about four.  Waves take four rows where
 // these fill the device (1024 SIMDs of several waves): 32768 elements at p = 3, FP64, 0.34
 // ms with one row, 0.29 with four, 0.28 with eight; 512 elements 0.009, 0.017, 0.026.
-template <typename T>
+template <typename T, typename I>
 void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
     const bool few = pl->ndof < 65536;
-    auto f = pl->n <= 8 ? launch_rows<T, 8, 1, 4, 1> : pl->n <= 32 ? launch_rows<T, 32, 1, 4, 2>
-           : pl->n <= 64 ? (few ? launch_rows<T, 64, 1, 4, 1> : launch_rows<T, 64, 1, 4, 4>)
-           : pl->n <= 128 ? (few ? launch_rows<T, 64, 2, 2, 1> : launch_rows<T, 64, 2, 2, 4>)
-           : pl->n <= 256 ? (few ? launch_rows<T, 64, 4, 1, 1> : launch_rows<T, 64, 4, 1, 4>)
-                          : (few ? launch_rows<T, 64, 5, 1, 1> : launch_rows<T, 64, 5, 1, 4>);
+    auto f = pl->n <= 8 ? launch_rows<T, I, 8, 1, 4, 1> : pl->n <= 32 ? launch_rows<T, I, 32, 1, 4, 2>
+           : pl->n <= 64 ? (few ? launch_rows<T, I, 64, 1, 4, 1> : launch_rows<T, I, 64, 1, 4, 4>)
+           : pl->n <= 128 ? (few ? launch_rows<T, I, 64, 2, 2, 1> : launch_rows<T, I, 64, 2, 2, 4>)
+           : pl->n <= 256 ? (few ? launch_rows<T, I, 64, 4, 1, 1> : launch_rows<T, I, 64, 4, 1, 4>)
+                          : (few ? launch_rows<T, I, 64, 5, 1, 1> : launch_rows<T, I, 64, 5, 1, 4>);
     static_assert(c_nshp(7) <= 5 * 64, "row of an element matrix");
     f(pl, A, b, values, rhs, accumulate, st);
+}
+template <typename T>
+void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
+    if (pl->wide) launch_rows<T, int64_t>(pl, A, b, values, rhs, accumulate, st);
+    else launch_rows<T, uint32_t>(pl, A, b, values, rhs, accumulate, st);
 }
 
 }  // namespace
@@ -210,24 +216,16 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
         for (int64_t e = 0; e < ne; ++e)
             for (int a = 0; a < n; ++a) inc[fill[dofs[e * n + a]]++] = (int32_t)e;
     }
-    std::atomic<bool> twice{false};         // a dof listed twice in one element is a bad map
-    parallel_for(ne, [&](int64_t lo, int64_t hi, unsigned) {
-        std::vector<int32_t> d(n);
-        for (int64_t e = lo; e < hi; ++e) {
-            std::copy(dofs + e * n, dofs + (e + 1) * n, d.begin());
-            std::sort(d.begin(), d.end());
-            if (std::adjacent_find(d.begin(), d.end()) != d.end()) twice = true;
-        }
-    });
-    if (twice) return FEINT_ERR_INVALID_ARG;
 
     // CSR pattern: row lengths, then the sorted columns
     std::vector<int64_t> row_ptr(ndof + 1, 0);
+    std::atomic<bool> twice{false};         // a dof listed twice in one element is a bad map
     parallel_for(ndof, [&](int64_t lo, int64_t hi, unsigned) {
         std::vector<int32_t> seen;
         for (int64_t i = lo; i < hi; ++i) {
             seen.clear();
             for (int64_t k = inc_ptr[i]; k < inc_ptr[i + 1]; ++k) {
+                if (k > inc_ptr[i] && inc[k] == inc[k - 1]) twice = true;
                 const int32_t *de = dofs + (int64_t)inc[k] * n;
                 seen.insert(seen.end(), de, de + n);
             }
@@ -235,6 +233,7 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
             row_ptr[i + 1] = std::unique(seen.begin(), seen.end()) - seen.begin();
         }
     });
+    if (twice) return FEINT_ERR_INVALID_ARG;
     for (int64_t i = 0; i < ndof; ++i) {
         if (row_ptr[i + 1] > 65535) return FEINT_ERR_TOO_LARGE;
         row_ptr[i + 1] += row_ptr[i];
@@ -285,21 +284,28 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
         if (c == ncolors) { ++ncolors; used.push_back(-1); }
         color[e] = c;
     }
-    // every dof's element rows, by colour
-    std::vector<int64_t> rows(ne * n);
-    {
-        std::vector<int64_t> fill(inc_ptr.begin(), inc_ptr.end() - 1);
-        for (int64_t x = 0; x < ne * n; ++x) rows[fill[dofs[x]]++] = x;
-    }
+    // every dof's element rows, by colour: in the place of its elements where 32 bits hold them
+    const bool wide = ne * n > (int64_t)UINT32_MAX;
+    std::vector<int64_t> rows(wide ? ne * n : 0);
     parallel_for(ndof, [&](int64_t lo, int64_t hi, unsigned) {
-        for (int64_t i = lo; i < hi; ++i)
-            std::sort(rows.begin() + inc_ptr[i], rows.begin() + inc_ptr[i + 1],
-                      [&](int64_t x, int64_t y) { return color[x / n] < color[y / n]; });
+        std::vector<std::pair<int32_t, int32_t>> list;
+        for (int64_t i = lo; i < hi; ++i) {
+            list.clear();
+            for (int64_t k = inc_ptr[i]; k < inc_ptr[i + 1]; ++k) list.push_back({color[inc[k]], inc[k]});
+            std::sort(list.begin(), list.end());
+            int64_t k = inc_ptr[i];
+            for (const auto &x : list) {
+                const int32_t *de = dofs + (int64_t)x.second * n;
+                const int64_t r = (int64_t)x.second * n + (std::find(de, de + n, (int32_t)i) - de);
+                if (wide) rows[k++] = r;
+                else inc[k++] = (int32_t)(uint32_t)r;
+            }
+        }
     });
 
     // upload
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t s_rp = al((ndof + 1) * 8), s_ci = al(nnz * 4), s_in = al(ne * n * 8),
+    const size_t s_rp = al((ndof + 1) * 8), s_ci = al(nnz * 4), s_in = al(ne * n * (wide ? 8 : 4)),
                  s_pos = al(ne * nn * 2);
     feint_asm_plan *pl = new feint_asm_plan;
     if (hipGetDevice(&pl->dev) != hipSuccess) { delete pl; return FEINT_ERR_HIP; }
@@ -309,12 +315,13 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
     pl->row_ptr = (int64_t *)p; p += s_rp;
     pl->col_idx = (int32_t *)p; p += s_ci;
     pl->inc_ptr = (int64_t *)p; p += s_rp;
-    pl->inc = (int64_t *)p; p += s_in;
+    pl->inc = p; p += s_in;
+    pl->wide = wide;
     pl->pos = (uint16_t *)p;
     const bool ok = hipMemcpy(pl->row_ptr, row_ptr.data(), (ndof + 1) * 8, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->col_idx, col_idx.data(), nnz * 4, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->inc_ptr, inc_ptr.data(), (ndof + 1) * 8, hipMemcpyHostToDevice) == hipSuccess &&
-                    hipMemcpy(pl->inc, rows.data(), ne * n * 8, hipMemcpyHostToDevice) == hipSuccess &&
+                    hipMemcpy(pl->inc, wide ? (const void *)rows.data() : inc.data(), ne * n * (wide ? 8 : 4), hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->pos, pos.data(), ne * nn * 2, hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) {
         set_error("asm plan upload", hipGetLastError());
