@@ -216,9 +216,8 @@ template <> struct PairInputs<PrismLaplaceGeo> {
 
 // EPB elements per workgroup of NW waves; a wave takes every WT-th tile of 16
 // orbits and CT / (NW / WT) tiles of 16 columns; EPB = 1: KPP values of k per
-// pass over the columns; KS values of k per round through the LDS copy of A;
-// SC: the symmetric and the antisymmetric G one after the other in the same LDS.
-template <int P, int FORM, int R, class Geo, int EPB, int NW, int WT, int KPP, int KS, bool SC = false>
+// pass over the columns; KS values of k per round through the LDS copy of A.
+template <int P, int FORM, int R, class Geo, int EPB, int NW, int WT, int KPP, int KS>
 struct KP {
     typedef PairForm<FORM> PF;
     typedef PairInputs<Geo> In;
@@ -253,8 +252,7 @@ struct KP {
     // rows of a class in LDS: whole blocks, in FP64 half blocks
     static constexpr int gr(int cls) { return FORM == F64 ? (pair_k(P, R, cls) + 7) / 8 * 8 : kb(cls) * GK; }
     static constexpr int GS = CT * mx(gr(0), gr(2)) * GB, GA = CT * mx(gr(1), gr(3)) * GB;
-    static constexpr int GALL = SC ? mx(GS, GA) : GS + GA;
-    static constexpr int GAOFF = SC ? 0 : GS;
+    static constexpr int GALL = GS + GA;
     static constexpr int EP = EPB * (NE - 1) * NK * S;        // E of a parity; w det J f of both follows
     static constexpr int EB = (2 * EP * (int)sizeof(T) + 2 * EPB * NK * S * (int)sizeof(LT) + 15) / 16 * 16;
     static constexpr int HT = c_cdiv(S, 16);                  // blocks of 16 sets
@@ -488,25 +486,24 @@ struct KP {
     }
     // A task is a tile of 16 contraction rows for every column tile of one element:
     // its rows of E are read once.
-    template <int PAR, bool SYM, bool ANTI>
+    template <int PAR>
     __device__ static void zeta(const FwdParams &prm, int k0, const Lines (&l)[CTE], Smem &sm) {
         constexpr int C0 = 2 * PAR, C1 = 2 * PAR + 1;
         constexpr int N0 = rows_of(PAR, 0), N1 = N0 + rows_of(PAR, 1), N2 = N1 + rows_of(PAR, 2), N3 = N2 + rows_of(PAR, 3);
         constexpr int N4 = N3 + rows_of(PAR, 4), KS0 = pair_k(P, R, C0), KS1 = pair_k(P, R, C1);
         static_assert(KS0 == N4 + rows_of(PAR, 5) && KS1 == N1 + rows_of(PAR, 5), "contraction rows");
         // tiles of 16 rows: those of 0o and 0e alone serve both classes
-        constexpr int BOTH = SYM && ANTI ? N1 / 16 : 0, TS = SYM ? c_cdiv(KS0, 16) : 0, TA = ANTI ? c_cdiv(KS1, 16) : 0;
-        constexpr int TT = BOTH + (SYM ? TS - BOTH : 0) + (ANTI ? TA - BOTH : 0);
+        constexpr int BOTH = N1 / 16, TS = c_cdiv(KS0, 16), TA = c_cdiv(KS1, 16), TT = TS + TA - BOTH;
         constexpr int Z0 = zoff(C0), Z1 = zoff(C1);
-        char *gs = sm.raw, *ga = sm.raw + GAOFF;
+        char *gs = sm.raw, *ga = sm.raw + GS;
         const int tid = phase_tid(), lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
         float sc = FORM == FP16X3 && EPB == 1 ? scale(prm, sm, 0) : 1.0f;
 #pragma unroll 1
         for (int id = wave_uniform(tid >> 6); id < EPB * TT; id += NW) {
             const int el = EPB == 1 ? 0 : id / TT, task = id - el * TT;
             if (FORM == FP16X3 && EPB > 1) sc = scale(prm, sm, el);
-            const bool sym = SYM && task < TS, anti = ANTI && (task < BOTH || !sym);
-            const int tile = sym ? task : task - (SYM ? TS - BOTH : 0);
+            const bool sym = task < TS, anti = task < BOTH || !sym;
+            const int tile = sym ? task : task - (TS - BOTH);
             const uint32_t zr = sm.zrow[(sym ? Z0 : Z1) + tile * 16 + i16];
             const bool x9 = zr & 0x4000, x6 = zr & 0x8000;
             const T *E = (const T *)(sm.raw + EOFF) + PAR * EP + el * (NE - 1) * NK * S + (zr & 0x3FFF);
@@ -563,7 +560,7 @@ struct KP {
             else if (mixed) form(ic<1>{}, ic<1>{});
             else form(ic<0>{}, ic<1>{});
         }
-        if (Geo::LOAD && SYM && PAR == 1 && k0 + KPP >= NK) load_sums(sm);
+        if (Geo::LOAD && PAR == 1 && k0 + KPP >= NK) load_sums(sm);
     }
 
     // ---- load vector ------------------------------------------------------------
@@ -754,19 +751,14 @@ struct KP {
     __device__ static void parity(const FwdParams &prm, int k0, int wt, int ct0, V4 (&s)[TPW][CTW], V4 (&d)[TPW][CTW],
                                   const Lines (&l)[CTE], Smem &sm) {
         Ahead h;
-        zeta<PAR, true, !SC>(prm, k0, l, sm);
+        zeta<PAR>(prm, k0, l, sm);
         ahead<2 * PAR>(prm, wt, h);
         __syncthreads();
         zero(s);
         products<2 * PAR>(prm, sm.raw, wt, ct0, h, s);
         ahead<2 * PAR + 1>(prm, wt, h);
-        if (SC) {
-            __syncthreads();
-            zeta<PAR, false, true>(prm, k0, l, sm);
-            __syncthreads();
-        }
         zero(d);
-        products<2 * PAR + 1>(prm, sm.raw + GAOFF, wt, ct0, h, d);
+        products<2 * PAR + 1>(prm, sm.raw + GS, wt, ct0, h, d);
 #pragma unroll
         for (int i = 0; i < TPW; ++i)
             if (has(2 * PAR + 1, i)) {
@@ -928,35 +920,34 @@ struct KP {
 // 3.4 against 2.5 in FP32), then workgroups per CU count: the shapes are the
 // fastest of those that fit.
 // Shapes per degree and form: elements per workgroup, waves, waves over the
-// orbits, values of k per pass and per round, SC, waves per SIMD asked of the
+// orbits, values of k per pass and per round, waves per SIMD asked of the
 // register allocator.
 template <int P, int FORM> struct PairShape;
-#define FEINT_PAIR_SHAPE(P, FORM, EPB_, NW_, WT_, KPP_, KS_, SC_, W_)                                   \
+#define FEINT_PAIR_SHAPE(P, FORM, EPB_, NW_, WT_, KPP_, KS_, W_)                                        \
     template <> struct PairShape<P, FORM> {                                                              \
         static constexpr int EPB = EPB_, NW = NW_, WT = WT_, KPP = KPP_, KS = KS_, W = W_;                \
-        static constexpr bool SC = SC_;                                                                  \
     };
-FEINT_PAIR_SHAPE(3, F64, 1, 2, 2, 4, 4, false, 4)
-FEINT_PAIR_SHAPE(4, F64, 1, 4, 4, 5, 5, false, 3)
-FEINT_PAIR_SHAPE(5, F64, 1, 4, 4, 2, 1, false, 3)
-FEINT_PAIR_SHAPE(6, F64, 1, 8, 8, 4, 1, false, 2)
-FEINT_PAIR_SHAPE(7, F64, 1, 8, 8, 4, 1, false, 2)
-FEINT_PAIR_SHAPE(3, F32, 4, 4, 2, 4, 4, false, 4)
-FEINT_PAIR_SHAPE(4, F32, 1, 4, 4, 5, 5, false, 4)
-FEINT_PAIR_SHAPE(5, F32, 1, 4, 4, 6, 3, false, 3)
-FEINT_PAIR_SHAPE(6, F32, 1, 8, 8, 4, 2, false, 4)
-FEINT_PAIR_SHAPE(7, F32, 1, 8, 8, 8, 2, false, 2)
-FEINT_PAIR_SHAPE(2, F32, 3, 2, 1, 3, 3, false, 4)
-FEINT_PAIR_SHAPE(2, BF16X3, 3, 2, 1, 3, 3, false, 4)
-FEINT_PAIR_SHAPE(3, BF16X3, 2, 2, 1, 4, 4, false, 3)
-FEINT_PAIR_SHAPE(4, BF16X3, 1, 4, 4, 5, 5, false, 4)
-FEINT_PAIR_SHAPE(5, BF16X3, 1, 4, 4, 6, 2, false, 3)
-FEINT_PAIR_SHAPE(6, BF16X3, 1, 8, 8, 4, 2, false, 4)
-FEINT_PAIR_SHAPE(7, BF16X3, 1, 8, 8, 8, 2, false, 2)
+FEINT_PAIR_SHAPE(3, F64, 1, 2, 2, 4, 4, 4)
+FEINT_PAIR_SHAPE(4, F64, 1, 4, 4, 5, 5, 3)
+FEINT_PAIR_SHAPE(5, F64, 1, 4, 4, 2, 1, 3)
+FEINT_PAIR_SHAPE(6, F64, 1, 8, 8, 4, 1, 2)
+FEINT_PAIR_SHAPE(7, F64, 1, 8, 8, 4, 1, 2)
+FEINT_PAIR_SHAPE(3, F32, 4, 4, 2, 4, 4, 4)
+FEINT_PAIR_SHAPE(4, F32, 1, 4, 4, 5, 5, 4)
+FEINT_PAIR_SHAPE(5, F32, 1, 4, 4, 6, 3, 3)
+FEINT_PAIR_SHAPE(6, F32, 1, 8, 8, 4, 2, 4)
+FEINT_PAIR_SHAPE(7, F32, 1, 8, 8, 8, 2, 2)
+FEINT_PAIR_SHAPE(2, F32, 3, 2, 1, 3, 3, 4)
+FEINT_PAIR_SHAPE(2, BF16X3, 3, 2, 1, 3, 3, 4)
+FEINT_PAIR_SHAPE(3, BF16X3, 2, 2, 1, 4, 4, 3)
+FEINT_PAIR_SHAPE(4, BF16X3, 1, 4, 4, 5, 5, 4)
+FEINT_PAIR_SHAPE(5, BF16X3, 1, 4, 4, 6, 2, 3)
+FEINT_PAIR_SHAPE(6, BF16X3, 1, 8, 8, 4, 2, 4)
+FEINT_PAIR_SHAPE(7, BF16X3, 1, 8, 8, 8, 2, 2)
 template <int P> struct PairShape<P, FP16X3> : PairShape<P, BF16X3> {};
 
 template <int P, int FORM, int R = 0, class Geo = PrismGeo, class S = PairShape<P, FORM>>
-using KPOf = KP<P, FORM, R, Geo, S::EPB, S::NW, S::WT, S::KPP, S::KS, S::SC>;
+using KPOf = KP<P, FORM, R, Geo, S::EPB, S::NW, S::WT, S::KPP, S::KS>;
 
 template <class K, int NW, int MINW>
 __global__ __launch_bounds__(NW * 64, MINW) void fwd_pair(FwdParams prm) {

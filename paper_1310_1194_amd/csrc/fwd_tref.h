@@ -68,8 +68,7 @@ struct KT {
     // their addresses modulo 16 bytes, and what is complete leaves in whole lines: 16
     // lanes write two of an element, whatever the alignment of its matrix.
     template <class LoadB, class Mma>
-    __device__ static void whole_lines(const FwdParams &prm, Slice &sl, int64_t base, const T (&afr)[RT][4], LoadB load_b, Mma mma) {
-        (void)afr;
+    __device__ static void whole_lines(const FwdParams &prm, Slice &sl, int64_t base, LoadB load_b, Mma mma) {
         typedef T VT __attribute__((ext_vector_type(VL)));
         constexpr int TB = BE / 16, NBLKS = (N2 + LN - 1 + BE - 1) / BE;
         static_assert(SB <= (int)sizeof(Slice::W), "the ring fits the slice");
@@ -258,7 +257,7 @@ struct KT {
                 }
             });
         }
-        if constexpr (STG == 2) if (fastw) whole_lines(prm, sl, base, afr, load_b, mma);
+        if constexpr (STG == 2) if (fastw) whole_lines(prm, sl, base, load_b, mma);
         if constexpr (STG == 0) if (fastw) {
             // RTP row tiles (16 RTP elements) at a time, each group through all
             // column tiles before the next
