@@ -358,7 +358,7 @@ def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
         elif kind == "tet" and costmodel.is_tet_ref_tile(r["tile"]):   # the reference-matrix GEMM
             r["alg_flops_per_element"] = costmodel.f_tet_reference(n)
         else:
-            r["alg_flops_per_element"] = fdom
+            r["alg_flops_per_element"] = fdom if other_elem else costmodel.f_kernel(p, rule, r["tile"])
         r["fdom_equiv_gflops"] = fdom * ne / (r["kernel_ms_mean"] * 1e-3) / 1e9
         r["gflops_alg"] = r["alg_flops_per_element"] * ne / (r["kernel_ms_mean"] * 1e-3) / 1e9
         r["tflops_frac_of_peak"] = r["gflops_alg"] / 1e3 / PEAK_TFLOPS[form]
@@ -441,6 +441,8 @@ def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
                               "algorithmic flops of the products of pairs of triangle functions per element "
                               "(costmodel.f_pair)" if costmodel.is_pair_tile(h["tile"]) else
                               "algorithmic flops of the reference-matrix GEMM per element (26 n^2 + n)" if tref else
+                              "algorithmic flops from moments per element (costmodel.f_moments)"
+                              if not other_elem and falg == costmodel.f_moments(rule) else
                               "algorithmic flops 8 n^2 nq per element (one product per entry; "
                               "a split form issues three products)") + "; bytes %d in + (n^2+n) outputs" % in_bytes})
     forms_out = {}

@@ -274,7 +274,9 @@ feint_status feint_tile_set(int p, feint_form form, int tile);
    split forms and in FP32 from p = 2, there not for small batches or, in FP32,
    large ones),
    or "vL" (vector-ALU kernel, L lanes per element); "o2" marks a
-   two-waves-per-SIMD register budget.  At p = 2 "2x2so4" is "2x2s" for
+   two-waves-per-SIMD register budget.  For prisms at p = 1 "v1o2" takes two
+   lanes per element and sums of the coefficient blocks over the triangle's
+   points, "v1" and "v1o3" one lane per element, point by point.  At p = 2 "2x2so4" is "2x2s" for
    small batches and "0x2fo4" for larger ones, "v18o4" "0x2fo4" for small
    batches and for coefficients at the vertices, else "v18o2". */
 feint_status feint_tile_describe(int p, feint_form form, int tile, char *buf, size_t len);

@@ -233,9 +233,23 @@ def pair_mfma_flops(p: int, rule: str = "collapsed", split: bool = False) -> int
     return sum(2 * (-(-r // 16) * 16) * (-(-k // g) * g) for r, k in pair_sizes(p, rule)) * cols
 
 
+def f_moments(rule: str = "collapsed") -> int:
+    """Flops per prism of degree 1 from moments ("v1o2").  Per point: the 18
+    multiply-adds of a derivative's entries times l_t, 18 of the other entries
+    times the 6 products l_t l_t' and 3 of the load vector, 4 additions.  Per zeta
+    point: 16 products of line factors; for each (t, t') three additions and
+    six combinations with T_o, T_e (a multiply-add for two of three t); four
+    multiply-adds for each (k, k', t, t') (the first a product) and the addition over the zeta
+    points; 6 multiply-adds of the load vector."""
+    nij = nq(1, rule) // 2
+    return 2 * ((2 * 39 + 6 + 4) * nij + 16 + 9 * 3 + 6 * 9 * 2 * 2 // 3 + 36 * 8 + 12)
+
+
 def f_kernel(p: int, rule: str, desc: str) -> int:
     """Algorithmic flops per element of the algorithm the tile runs (at p = 2
     "2x2so4" runs the pair products, but for small batches)."""
+    if p == 1 and desc == "v1o2":
+        return f_moments(rule)
     if desc == "2x2so4":
         return f_pair(p, rule)
     return f_pair(p, rule) if is_pair_tile(desc) else f_kf(p, rule) if is_kf_tile(desc) else f_dom(p, rule)

@@ -52,11 +52,12 @@ int64_t items_of(int64_t ne) { return items_for<KER>(ne); }
 // V: vector-ALU kernel, LPE lanes per element (tm = 0, tn = LPE, staged = 3).
 #define FEINT_KV_R(P, T, LPE, W, R) \
     FwdVariant{0, LPE, 3, W, &launch_direct<KV<P, T, LPE, R>, W>, &items_of<KV<P, T, LPE, R>>}
-// E: one element per lane, vector ALU (p = 1; tm = 0, tn = 1 lane per element, staged = 3).
+// E: one element per lane, vector ALU (p = 1; tm = 0, tn = 1 lane per element, staged = 3); two
+// waves per SIMD are not marked ("v1"): "v1o2" is M.
 #define FEINT_KE_R(P, T, W, R) \
-    FwdVariant{0, 1, 3, W, &launch_direct<KE<P, T, R>, W>, &items_of<KE<P, T, R>>}
+    FwdVariant{0, 1, 3, (W) == 2 ? 1 : (W), &launch_direct<KE<P, T, R>, W>, &items_of<KE<P, T, R>>}
 #define FEINT_KE(P, T, W) FEINT_KE_R(P, T, W, 0)
-// M: prisms of degree 1 from moments, one element per lane ("v1").
+// M: prisms of degree 1 from moments, two lanes per element ("v1o2").
 #define FEINT_KM(T, W, R) FwdVariant{0, 1, 3, W, &launch_direct<KM<T, R>, W>, &items_of<KM<T, R>>}
 // R: tetrahedra from reference matrices (staged = 11): one element per lane.
 #define FEINT_KT(P, T, R, W) FwdVariant{R, 1, 11, W, &launch_direct<KT<P, T, R>, W>, &items_of<KT<P, T, R>>}
