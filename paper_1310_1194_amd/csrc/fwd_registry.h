@@ -1,6 +1,8 @@
 // Launch helpers that instantiate the forward kernels for a list of tile
 // shapes of one form.
 #pragma once
+#include <atomic>
+
 #include "fwd_kernels.h"
 #include "fwd_staged.h"
 #include "fwd_valu.h"
@@ -154,14 +156,25 @@ void launch_by_output(const FwdParams &prm, hipStream_t s) {
     FwdVariant{EPW, (NTH) / 64, 10, W, &launch_hsf<P, T, NTH, EPW, true, W, true>, &items_hsf<EPW>}
 
 // PP: products of pairs of triangle functions (staged = 17)
+// as many workgroups as the current device holds at once, each going on to further elements
+// (asked once per device: the answer depends on the kernel and the device alone)
+template <class K, int MINW>
+int64_t pair_grid() {
+    constexpr int DEVICES = 16;
+    static std::atomic<int> known[DEVICES];
+    int dev = 0, cus = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 1;
+    if (dev < DEVICES)
+        if (const int v = known[dev].load(std::memory_order_relaxed)) return v;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1 ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_pair<K, K::NW_, MINW>, K::NW_ * 64, 0) != hipSuccess || n < 1)
+        return 1;                                      // the launch reports the error
+    if (dev < DEVICES) known[dev].store(cus * n, std::memory_order_relaxed);
+    return (int64_t)cus * n;
+}
 template <class K, int MINW>
 void launch_pair(const FwdParams &prm, hipStream_t s) {
-    // as many workgroups as the device holds at once (256 CUs), each going on to further elements
-    static const int per_cu = [] {
-        int n = 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_pair<K, K::NW_, MINW>, K::NW_ * 64, 0) == hipSuccess && n > 0 ? n : 1;
-    }();
-    const int64_t groups = (prm.ne + K::EPB_ - 1) / K::EPB_, most = 256 * (int64_t)per_cu;
+    const int64_t groups = (prm.ne + K::EPB_ - 1) / K::EPB_, most = pair_grid<K, MINW>();
     hipLaunchKernelGGL((fwd_pair<K, K::NW_, MINW>), dim3((unsigned)(groups < most ? groups : most)), dim3(K::NW_ * 64), 0, s, prm);
 }
 template <class K>
