@@ -21,7 +21,10 @@ against the oracle and its CPU baseline.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--copy-cal]
                     [--mode suite|forward|fields|hex|tet|adjoint|mixed|assemble|laplace]
-                    [--workload NAME] [--forms LIST] [--hex-ps LIST]
+                    [--workload NAME] [--forms LIST] [--hex-ps LIST] [--record FILE]
+
+The line is a summary (`brief`) that fits the last 8000 characters of the output;
+--record writes everything measured.
 """
 from __future__ import annotations
 
@@ -212,6 +215,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the oracle (CPU baseline and errors)")
     ap.add_argument("--cpu-budget", type=float, default=10.0)
     ap.add_argument("--no-tune", action="store_true")
+    ap.add_argument("--record", default=None, help="also write the whole record, every configuration in full, to this file")
     ap.add_argument("--copy-cal", action="store_true", help="also run a 1 GiB device copy (counter calibration)")
     args = ap.parse_args()
 
@@ -236,7 +240,42 @@ def main():
     else:
         line = bench_forward(args, fields=args.mode == "fields",
                              kind=args.mode if args.mode in ("hex", "tet") else None)
-    print(json.dumps(line))
+    if args.record:
+        Path(args.record).write_text(json.dumps(line, indent=1) + "\n")
+    print(json.dumps(brief(line)))
+
+
+def brief(line):
+    """The printed line: the headline in full but for the forms' fields, and of every other
+    workload its value, roofline share, CPU baseline and per form (degree) a list of
+    kernel ms, variant and relative errors of A (the adjoint: of the gradients) and
+    b, four digits each, in about 5500 characters: readers that keep the last 8000 of
+    the output get it whole.  --record FILE holds everything."""
+    def cut(v):
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+
+    def leaves(d):
+        out = {}
+        for k, v in d.items():
+            if isinstance(v, dict) and "kernel_ms_mean" in v:
+                out[k] = [cut(v[x]) for x in ("kernel_ms_mean", "tile", "block", "rel_err_A", "rel_err_b", "rel_err") if x in v]
+            elif isinstance(v, dict):
+                out[k] = leaves(v)
+        return out
+    short = {k: v for k, v in line.items() if k not in ("configs", "forms", "degrees", "tile_sets_ms", "errors_vs_oracle")}
+    for k in ("forms", "degrees"):
+        if k in line:
+            short[k] = leaves(line[k])
+    if line.get("errors_vs_oracle"):
+        short["rel_err_A"] = [cut(e["rel_err_A"]) for e in line["errors_vs_oracle"].values()]
+    if "configs" in line:
+        short["configs"] = {}
+        for name, c in line["configs"].items():
+            c = brief(c)
+            keep = {k: cut(c[k]) for k in ("value", "ms_per_step", "graph_ms", "rel_err_A", "forms", "degrees") if k in c}
+            short["configs"][name] = {**keep, "bound": c["roofline"]["bound"], "frac": cut(c["roofline"]["frac"]),
+                                      "cpu": cut((c.get("cpu_baseline") or {}).get("value"))}
+    return short
 
 
 def bench_forward(args, fields=False, kind=None, err_idx=None, cpu_budget=None):
@@ -872,8 +911,8 @@ def bench_adjoint(args):
 
 
 def bench_mixed(args):
-    """Mixed-degree batch (p ~ U{1..6}, shuffled): bucketing + persistent
-    launch, eager and as a replayed HIP graph."""
+    """Mixed-degree batch (p ~ U{1..6}, shuffled): bucketing and the tile set's
+    launches, eager and as a replayed HIP graph."""
     import torch
     import paper_1310_1194_amd as F
     args.workload = args.workload or "mixed_262144"
@@ -941,7 +980,7 @@ def bench_mixed(args):
         cpu = {"value": rate, "unit": "elements/s", "cores": oracle.max_threads(), "kind": "oracle",
                "sample": "per degree the first elements of that degree (4096 >> 2(p-1), at least 16); "
                          "rate combined with the batch's degree mix", "cpu": cpu_model()}
-    line = {"metric": "mixed-degree elements/s (one persistent degree-bucketed launch, HIP graph)",
+    line = {"metric": "mixed-degree elements/s (degree-bucketed launches, HIP graph)",
             "value": ne / (ms_g * 1e-3), "unit": "elements/s", "n_gpus": 1, "steps": args.steps,
             "warmup": args.warmup, "ms_per_step": wall_g, "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": form, "data": "synthetic (seeded mesh, p ~ U{1..6}, shuffled)",
@@ -1008,7 +1047,7 @@ def bench_assemble(args):
         cpu = {"value": m / spent, "unit": "elements/s", "cores": 1, "kind": "oracle",
                "sample": f"assembly of the first {m} elements' matrices ({spent:.1f} s, FP64, one core)"}
     h = res[forms[0]]
-    line = {"metric": "global assembly elements/s (CSR, colour by colour)", "value": h["elements_per_s"],
+    line = {"metric": "global assembly elements/s (CSR, row by row in colour order)", "value": h["elements_per_s"],
             "unit": "elements/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": h["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
             "dtype": forms[0], "data": "synthetic (seeded mesh; element matrices from the forward pass)",
