@@ -14,13 +14,13 @@
 //      the chain rule to the 32 inputs, summed over the element's waves.
 // Collapsed rule, ms, best other kernel -> this one (131072, 65536, 16384, 8192,
 // 4001 elements at p = 3..7): 2.73 -> 1.36, 6.05 -> 2.62, 5.67 -> 1.90, 7.90 -> 2.82,
-// 8.73 -> 2.56; one element 0.039 -> 0.025 at p = 4, 0.17 -> 0.14 at p = 7.
-// At p = 7 the matrix cores are busy 55 % of the cycles.  Reading G is not what is
-// left: an orbit's entries (t, t') and (t', t) lie in different rows and 16 orbits take
-// about four lines of 128 bytes for each they fill (4.4 TB/s past L2), but passes over
-// 32 or 16 columns at a time, whose rows stay in L2, took 2.77 and 3.62 ms against 2.65.
-// Two waves per SIMD in step at the barriers are: the next chunk's table under way over
-// the barrier gave 2.81 -> 2.56.  Orbits are ordered by patches of 8 x 4 (t, t'): 3.05
+// 8.73 -> 2.54; one element 0.039 -> 0.025 at p = 4, 0.17 -> 0.14 at p = 7.
+// At p = 7 the matrix cores are busy 55 % of the cycles, and 12.4 GB pass L2 for the 2.66 GB
+// of G: an orbit's entries (t, t') and (t', t) lie in different rows and 16 orbits take
+// about four lines of 128 bytes for each they fill.  That is 4.9 TB/s, what a large copy
+// reaches, so either may be the bound: passes over 32 or 16 columns at a time, whose
+// rows of G stay in L2, took 2.77 and 3.62 ms against 2.65, but read the table again
+// per pass.  The next chunk's table under way over the barrier gave 2.81 -> 2.56.  Orbits are ordered by patches of 8 x 4 (t, t'): 3.05
 // ms row by row, 2.88 (4 x 4: 2.88, 8 x 8: 2.89, 16 x 16: 2.97).
 // Against KFA2 the matrix work is 4.6x less at p = 7 (with 16-padded tiles of
 // triangle functions, the unused three quarters of its second product) and no
