@@ -170,8 +170,12 @@ void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *v
 }
 // Lanes per row: the fewest of a power of two that hold a row of the element matrix, a
 // wave from p = 3 on; loads in flight per lane about four.  Waves take four rows where
-// these fill the device (1024 SIMDs of several waves): 32768 elements at p = 3, FP64, 0.34
-// ms with one row, 0.29 with four, 0.28 with eight; 512 elements 0.009, 0.017, 0.026.
+// these fill the device (1024 SIMDs of several waves), as the rows' first loads then
+// overlap; fewer rows need the waves.  us with one row, with four, FP64, by dofs: p = 3 8125
+// 9, 16, 34225 28, 30, 60025 45, 38, 117649 84, 64; p = 4 35937 36, 39, 55473 49, 46, 79233 66,
+// 58; p = 5 35301 51, 42, 68921 112, 92; p = 6 60025 156, 156, 117649 303, 272; p = 7 24389 80,
+// 113, 94221 316, 301.  FP32 alike to p = 5; p = 6 117649 160, 160; p = 7 94221 169, 198, 287337
+// 471, 480.
 template <typename T, typename I>
 void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
     const bool few = pl->ndof < 65536;
