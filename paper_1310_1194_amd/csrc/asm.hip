@@ -18,11 +18,14 @@
 // one after the other, values[row_ptr[dofs[e][a]] + pos[e][a][b]] += A_e[a][b],
 // and write the row; rhs[dofs[e][a]] += b_e[a] likewise.  The order of the sums is
 // that of the colours: no atomics, the same bits in every run.
-// Bound by HBM: A and pos are read once, the values written once.  A launch per
+// Near the memory's rate: 32768 elements at p = 3 in FP64 take 0.279 ms, in which 0.77 GB are
+// read and 0.32 written past L2 (3.9 TB/s; a large copy 4.7), where A, pos and the lists are 0.53
+// GB: element rows of 320 bytes, and of 80 in pos, touch 2.5 to 3.5 lines of 128 that other
+// workgroups' rows share.  Rows of more values than LDS holds (1024; 512 at p = 2, 128 at p =
+// 1) are taken in several passes that read their element rows again.  A launch per
 // colour, one wave per element, read and wrote each value once per colour that
-// meets it and took 13 to 16 launches and two fills: 32768 elements at p = 3 in
-// FP64 0.67 ms, here 0.29 (2.9 TB/s; element rows of 320 bytes touch 2.5 to 3.5 lines
-// of 128); 512 elements 0.23 and 0.010; p = 7, 768 elements, 15.4 and 0.43.
+// meets it and took 13 to 16 launches and two fills: 0.67 ms; 512 elements 0.23 and here
+// 0.009; p = 7, 768 elements, 15.4 and 0.42.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
