@@ -1026,9 +1026,9 @@ def bench_assemble(args):
         vals = torch.empty(plan.nnz, dtype=A.dtype, device=dev)
         rhs = torch.empty(ndof, dtype=A.dtype, device=dev)
         ms, mn, wall = timed(lambda: plan.assemble(A, b, form, values=vals, rhs=rhs), args.steps, args.warmup)
-        # algorithmic bytes: element matrices, vectors and position map read once, the
-        # global values and rhs cleared and written once, dof map and row starts read
-        alg = ne * n * n * (es + 2) + ne * n * (es + 4) + 2 * (plan.nnz + ndof) * es + (ndof + 1) * 8
+        # algorithmic bytes: element matrices, vectors, position map and the list of element rows
+        # read once, the row starts read, the global values and rhs written once
+        alg = ne * n * n * (es + 2) + ne * n * (es + 4) + (plan.nnz + ndof) * es + 2 * (ndof + 1) * 8
         res[form] = dict(kernel_ms_mean=ms, kernel_ms_min=mn, ms_per_step=wall, elements_per_s=ne / (ms * 1e-3),
                          alg_bytes=alg, gbs=alg / (ms * 1e-3) / 1e9)
         print(f"[bench] assembly {form}: {ms:.3f} ms, {alg / (ms * 1e-3) / 1e9:.0f} GB/s algorithmic",

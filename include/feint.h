@@ -184,14 +184,14 @@ feint_status feint_mixed_bucket(feint_mixed_plan *plan, const int8_t *p, int64_t
                                 int64_t *offA, int64_t *offb, uint32_t *dev_status,
                                 void *stream);
 
-/* The persistent degree-bucketed launch over the bucketing of the last
+/* The tile set's launch or launches over the bucketing of the last
    feint_mixed_bucket call on this plan (same ne, same p). */
 feint_status feint_integrate_mixed(feint_mixed_plan *plan, const feint_elements *el,
                                    void *A_packed, void *b_packed,
                                    const int64_t *offA, const int64_t *offb,
                                    uint32_t *dev_status, void *stream);
 
-/* Capture bucketing + persistent launch for fixed pointers into a HIP graph
+/* Capture bucketing and the integration for fixed pointers into a HIP graph
    held by the plan (replaces any previous one), then instantiate it.
    Capturing runs nothing: the captured bucketing first happens when the
    graph is launched, so until then feint_integrate_mixed and
@@ -205,16 +205,16 @@ feint_status feint_mixed_graph_capture(feint_mixed_plan *plan, const feint_eleme
                                        void *stream);
 /* Replay the captured graph on `stream`. */
 feint_status feint_mixed_graph_launch(feint_mixed_plan *plan, void *stream);
-/* Time each compiled set of per-degree tile shapes of the persistent launch
-   (`reps` launches each, after bucketing with feint_mixed_bucket) and keep
-   the fastest in the plan; *best_ms receives its mean launch time. */
+/* Time each compiled tile set
+   (`reps` repetitions each, after bucketing with feint_mixed_bucket) and keep
+   the fastest in the plan; *best_ms receives its mean time. */
 feint_status feint_mixed_autotune(feint_mixed_plan *plan, const feint_elements *el,
                                   void *A_packed, void *b_packed, const int64_t *offA,
                                   const int64_t *offb, int reps, double *best_ms, void *stream);
 /* For callers that cannot allocate device memory (code under HIP graph
    capture, tight serving loops, harnesses that forbid hipMalloc): the
    mixed-degree integration of a batch -- bucketing of p[ne] (int8, device)
-   into offA[ne+1], offb[ne+1] and the persistent launch into the packed
+   into offA[ne+1], offb[ne+1] and the integration into the packed
    A_packed, b_packed, as feint_mixed_bucket followed by
    feint_integrate_mixed with the first compiled tile set -- without a plan
    and without allocating.  Its bucketing scratch is a fixed device array of

@@ -460,7 +460,7 @@ NOALLOC_MAX_NE = 1048576     # FEINT_NOALLOC_MAX_NE
 
 def integrate_mixed_noalloc(coords, D, beta, c, f, p, A, b, offA, offb, form: str = "fp32", status=None):
     """Mixed-degree integration through the library's allocation-free entry
-    point (bucketing + persistent launch on the library's fixed scratch):
+    point (bucketing and integration on the library's fixed scratch):
     every buffer is the caller's; the tables of degrees 1..6 must have been
     prepared (`prepare(d)`); at most NOALLOC_MAX_NE elements."""
     if form not in ("fp32", "fp64"):
@@ -482,8 +482,8 @@ def integrate_mixed_noalloc(coords, D, beta, c, f, p, A, b, offA, offb, form: st
 
 
 class MixedPlan:
-    """Mixed-degree batches (degrees 1..6) through one persistent,
-    degree-bucketed launch; optionally captured once into a HIP graph."""
+    """Mixed-degree batches (degrees 1..6), bucketed by degree on the device;
+    optionally captured once into a HIP graph."""
 
     def __init__(self, ne_max: int, form: str = "fp32"):
         if form not in ("fp32", "fp64"):
@@ -530,7 +530,7 @@ class MixedPlan:
                                                                    _ptr(offA), _ptr(offb), _ptr(status), _stream()))
 
     def capture(self, coords, D, beta, c, f, p, A, b, offA, offb, status=None):
-        """Capture bucketing + persistent launch for these buffers into a HIP graph.
+        """Capture bucketing and integration for these buffers into a HIP graph.
 
         The graph holds raw device pointers, so the plan keeps references to
         every captured tensor until the next capture or close(): a replay

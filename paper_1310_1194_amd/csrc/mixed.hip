@@ -1,5 +1,5 @@
-// Mixed-degree batches: integer degree bucketing and one persistent,
-// degree-bucketed launch (optionally captured in a HIP graph).
+// Mixed-degree batches: integer degree bucketing and a launch per degree or one
+// persistent launch over the buckets (optionally captured in a HIP graph).
 //
 // The paper (Sec. 2.2) recommends grouping elements by type and degree so the
 // reference data of a group is fetched once.  Here the grouping is done on
@@ -428,7 +428,7 @@ void drop_graph(feint_mixed_plan *pl) {
     pl->graph = nullptr;
 }
 
-// Device memory one bucketing + persistent launch works in: the queue header,
+// Device memory one bucketing and integration works in: the queue header,
 // the per-block degree sums and the permutation into bucket order, plus the
 // degree tables and the launch grid of each compiled tile set.
 struct MixedWork {
