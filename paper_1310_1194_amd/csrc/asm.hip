@@ -18,14 +18,14 @@
 // one after the other, values[row_ptr[dofs[e][a]] + pos[e][a][b]] += A_e[a][b],
 // and write the row; rhs[dofs[e][a]] += b_e[a] likewise.  The order of the sums is
 // that of the colours: no atomics, the same bits in every run.
-// Near the memory's rate: 32768 elements at p = 3 in FP64 take 0.279 ms, in which 0.77 GB are
+// Near the memory's rate: 32768 elements at p = 3 in FP64 take 0.275 ms, in which 0.77 GB are
 // read and 0.32 written past L2 (3.9 TB/s; a large copy 4.7), where A, pos and the lists are 0.53
 // GB: element rows of 320 bytes, and of 80 in pos, touch 2.5 to 3.5 lines of 128 that other
 // workgroups' rows share.  Rows of more values than LDS holds (1024; 512 at p = 2, 128 at p =
-// 1) are taken in several passes that read their element rows again.  A launch per
+// 1) are taken in pieces, side by side, that each read the row's element rows.  A launch per
 // colour, one wave per element, read and wrote each value once per colour that
 // meets it and took 13 to 16 launches and two fills: 0.67 ms; 512 elements 0.23 and here
-// 0.009; p = 7, 768 elements, 15.4 and 0.42.
+// 0.009; p = 7, 512 elements, 15.2 and 0.24.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -51,6 +51,8 @@ struct feint_asm_plan {
     int64_t *inc_ptr = nullptr;   // [ndof + 1]
     void *inc = nullptr;          // [ne * n] rows e * n + a of the element matrices, dof by dof: uint32, or int64 if wide
     bool wide = false;
+    int64_t *more = nullptr;      // [nmore] pieces of long rows past the first (row, piece << 32)
+    int64_t nmore = 0;
     uint16_t *pos = nullptr;      // [ne][n][n]
 };
 
@@ -71,114 +73,127 @@ void parallel_for(int64_t n, F fn) {
     for (auto &x : th) x.join();
 }
 
-// G lanes take R rows of the global matrix, one after the other, cap values of a row in
-// LDS at a time; CH steps of G lanes cover a row of an element matrix.  The R rows'
-// element rows are one list: U of it are fetched while U are added, also across the
-// ends of rows, so that no row waits for its own first loads.
+// Values of a row of the global matrix in LDS at a time, by the lanes that take it: 8 KB per
+// wave at most (FP64).
+constexpr int asm_lanes(int n) { return n <= 8 ? 8 : n <= 32 ? 32 : 64; }
+constexpr int asm_cap(int n) { return 16 * asm_lanes(n); }
+
+// G lanes take R rows of the global matrix, one after the other, the first cap values of
+// each; longer rows have their further pieces of cap values in `more` (row, piece << 32), each
+// taken by G lanes of its own (the first blocks).  CH steps of G lanes cover a row of an
+// element matrix.  The R rows' element rows are one list: U of it are fetched while U are
+// added, also across the ends of rows, so that no row waits for its own first loads.
+// (A dof of many elements: the pieces taken one after the other by the same lanes were 157 ms
+// for a fan of 4000 elements at p = 1, where a launch per colour took 15; here 1.3.)
 template <typename T, typename I, int G, int CH, int U, int R>
 __global__ __launch_bounds__(256) void assemble_rows(const T *__restrict__ A, const T *__restrict__ b,
                                                      const int64_t *__restrict__ inc_ptr, const I *__restrict__ inc,
                                                      const int64_t *__restrict__ row_ptr, const uint16_t *__restrict__ pos,
-                                                     int n, int64_t ndof, int cap, int accumulate, T *values, T *rhs) {
+                                                     const int64_t *__restrict__ more, int64_t nmore, int n, int64_t ndof,
+                                                     int cap, int accumulate, T *values, T *rhs) {
     static_assert(R < G, "a lane per row and the end of the last");
+    constexpr int GROUPS = 256 / G;
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x % G, grp = threadIdx.x / G;
     T *row = (T *)lds + grp * cap;
-    const int64_t i0 = ((int64_t)blockIdx.x * (256 / G) + grp) * R;
-    if (i0 >= ndof) return;
-    const int nr = ndof - i0 < R ? (int)(ndof - i0) : R;
+    const int64_t pieces = (nmore + GROUPS - 1) / GROUPS;             // blocks
+    int64_t i0;
+    int c0 = 0, nr = 1;
+    if (blockIdx.x < pieces) {
+        i0 = (int64_t)blockIdx.x * GROUPS + grp;
+        if (i0 >= nmore) return;
+        const int64_t x = more[i0];
+        c0 = (int)(x >> 32) * cap;
+        i0 = x & 0xFFFFFFFF;
+    } else {
+        i0 = ((blockIdx.x - pieces) * GROUPS + grp) * R;
+        if (i0 >= ndof) return;
+        nr = ndof - i0 < R ? (int)(ndof - i0) : R;
+    }
     // lane r: where row r begins in the list and in the values
     const int64_t ip = inc_ptr[i0 + (lane < nr ? lane : nr)], rp = row_ptr[i0 + (lane < nr ? lane : nr)];
     const int64_t k0 = __shfl(ip, 0, G), v0 = __shfl(rp, 0, G);
     const int st = (int)(ip - k0), en = __shfl(st, lane < nr ? lane + 1 : nr, G), total = __shfl(st, nr, G);
     const int at0 = (int)(rp - v0);
-    int longest = 0;
-    for (int r = 0; r < nr; ++r) {
-        const int len = __shfl(at0, r + 1, G) - __shfl(at0, r, G);
-        longest = len > longest ? len : longest;
-    }
-    T sum = accumulate && lane < nr ? rhs[i0 + lane] : (T)0;
-    for (int c0 = 0; c0 < longest; c0 += cap) {
-        int r = -1, end = 0, m = 0;                           // the row at hand, its end in the list, its values in LDS
-        T *out = values;
-        auto close = [&] {
-            wave_sync();
-            for (int j = lane; j < m; j += G) out[j] = row[j];
-        };
-        auto open = [&] {
-            ++r;
-            end = __shfl(st, r + 1, G);
-            const int a = __shfl(at0, r, G), len = __shfl(at0, r + 1, G) - a - c0;
-            m = len < 0 ? 0 : len < cap ? len : cap;
-            out = values + v0 + a + c0;
-            wave_sync();
-            for (int j = lane; j < m; j += G) row[j] = accumulate ? out[j] : (T)0;
-            wave_sync();
-        };
-        for (int xb = 0; xb < total; xb += G) {
-            const int xn = total - xb < G ? total - xb : G;
-            const int64_t mine = lane < xn ? (int64_t)inc[k0 + xb + lane] : 0;
-            const T bm = c0 == 0 && lane < xn ? b[mine] : (T)0;
-            struct Rows { T v[U][CH]; int at[U][CH]; } cur, nxt;
-            auto fetch = [&](int x, Rows &f) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int64_t e = __shfl(mine, x + u < xn ? x + u : 0, G) * n;
-#pragma unroll
-                    for (int h = 0; h < CH; ++h) {
-                        const int j = h * G + lane;
-                        const bool on = x + u < xn && j < n;
-                        f.v[u][h] = on ? A[e + j] : (T)0;
-                        f.at[u][h] = on ? pos[e + j] - c0 : -1;
-                    }
-                }
-            };
-            fetch(0, cur);
-            for (int x = 0; x < xn; x += U) {
-                fetch(x + U, nxt);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (x + u >= xn) break;
-                    while (xb + x + u == end) {
-                        close();
-                        open();
-                    }
-#pragma unroll
-                    for (int h = 0; h < CH; ++h)
-                        if ((unsigned)cur.at[u][h] < (unsigned)m) row[cur.at[u][h]] += cur.v[u][h];
-                    wave_sync();                              // the next element's lanes meet other columns
-                }
-                cur = nxt;
-            }
-            if (c0 == 0)
-                for (int x = 0; x < xn; ++x) {
-                    const T v = __shfl(bm, x, G);
-                    if (xb + x >= st && xb + x < en) sum += v;
-                }
-        }
-        close();
+    T sum = accumulate && c0 == 0 && lane < nr ? rhs[i0 + lane] : (T)0;
+    int r = -1, end = 0, m = 0;                               // the row at hand, its end in the list, its values in LDS
+    T *out = values;
+    auto close = [&] {
         wave_sync();
+        for (int j = lane; j < m; j += G) out[j] = row[j];
+    };
+    auto open = [&] {
+        ++r;
+        end = __shfl(st, r + 1, G);
+        const int a = __shfl(at0, r, G), len = __shfl(at0, r + 1, G) - a - c0;
+        m = len < cap ? len : cap;
+        out = values + v0 + a + c0;
+        wave_sync();
+        for (int j = lane; j < m; j += G) row[j] = accumulate ? out[j] : (T)0;
+        wave_sync();
+    };
+    for (int xb = 0; xb < total; xb += G) {
+        const int xn = total - xb < G ? total - xb : G;
+        const int64_t mine = lane < xn ? (int64_t)inc[k0 + xb + lane] : 0;
+        const T bm = c0 == 0 && lane < xn ? b[mine] : (T)0;
+        struct Rows { T v[U][CH]; int at[U][CH]; } cur, nxt;
+        auto fetch = [&](int x, Rows &f) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t e = __shfl(mine, x + u < xn ? x + u : 0, G) * n;
+#pragma unroll
+                for (int h = 0; h < CH; ++h) {
+                    const int j = h * G + lane;
+                    const bool on = x + u < xn && j < n;
+                    f.v[u][h] = on ? A[e + j] : (T)0;
+                    f.at[u][h] = on ? pos[e + j] - c0 : -1;
+                }
+            }
+        };
+        fetch(0, cur);
+        for (int x = 0; x < xn; x += U) {
+            fetch(x + U, nxt);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (x + u >= xn) break;
+                while (xb + x + u == end) {
+                    close();
+                    open();
+                }
+#pragma unroll
+                for (int h = 0; h < CH; ++h)
+                    if ((unsigned)cur.at[u][h] < (unsigned)m) row[cur.at[u][h]] += cur.v[u][h];
+                wave_sync();                                  // the next element's lanes meet other columns
+            }
+            cur = nxt;
+        }
+        if (c0 == 0)
+            for (int x = 0; x < xn; ++x) {
+                const T v = __shfl(bm, x, G);
+                if (xb + x >= st && xb + x < en) sum += v;
+            }
     }
-    if (lane < nr && (en > st || !accumulate)) rhs[i0 + lane] = sum;
+    close();
+    if (c0 == 0 && lane < nr && (en > st || !accumulate)) rhs[i0 + lane] = sum;
 }
 
 template <typename T, typename I, int G, int CH, int U, int R>
 void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
-    // 8 KB of LDS per wave at most (FP64): rows of more values are taken in several passes
     constexpr int CAP = 16 * G, GROUPS = 256 / G;
     const int cap = pl->max_row < CAP ? pl->max_row : CAP;
-    hipLaunchKernelGGL((assemble_rows<T, I, G, CH, U, R>), dim3((unsigned)((pl->ndof + GROUPS * R - 1) / (GROUPS * R))), dim3(256), GROUPS * cap * sizeof(T), st,
-                       (const T *)A, (const T *)b, pl->inc_ptr, (const I *)pl->inc, pl->row_ptr, pl->pos, pl->n, pl->ndof, cap, accumulate,
-                       (T *)values, (T *)rhs);
+    const int64_t blocks = (pl->ndof + GROUPS * R - 1) / (GROUPS * R) + (pl->nmore + GROUPS - 1) / GROUPS;
+    hipLaunchKernelGGL((assemble_rows<T, I, G, CH, U, R>), dim3((unsigned)blocks), dim3(256), GROUPS * cap * sizeof(T), st,
+                       (const T *)A, (const T *)b, pl->inc_ptr, (const I *)pl->inc, pl->row_ptr, pl->pos, pl->more, pl->nmore, pl->n,
+                       pl->ndof, cap, accumulate, (T *)values, (T *)rhs);
 }
 // Lanes per row: the fewest of a power of two that hold a row of the element matrix, a
 // wave from p = 3 on; loads in flight per lane about four.  Waves take four rows where
 // these fill the device (1024 SIMDs of several waves), as the rows' first loads then
 // overlap; fewer rows need the waves.  us with one row, with four, FP64, by dofs: p = 3 8125
-// 9, 16, 34225 28, 30, 60025 45, 38, 117649 84, 64; p = 4 35937 36, 39, 55473 49, 46, 79233 66,
-// 58; p = 5 35301 51, 42, 68921 112, 92; p = 6 60025 156, 156, 117649 303, 272; p = 7 24389 80,
-// 113, 94221 316, 301.  FP32 alike to p = 5; p = 6 117649 160, 160; p = 7 94221 169, 198, 287337
-// 471, 480.
+// 9, 15, 34225 26, 30, 60025 42, 37, 117649 77, 62; p = 4 35937 35, 37, 55473 47, 45, 79233 63,
+// 57; p = 5 35301 49, 41, 68921 116, 95; p = 6 60025 149, 131, 117649 289, 242; p = 7 24389 56,
+// 68, 94221 289, 240.  FP32 alike to p = 5; p = 6 60025 56, 60, 117649 146, 138; p = 7 94221
+// 152, 152, 287337 460, 401.
 template <typename T, typename I>
 void launch_rows(const feint_asm_plan *pl, const void *A, const void *b, void *values, void *rhs, int accumulate, hipStream_t st) {
     const bool few = pl->ndof < 65536;
@@ -310,13 +325,18 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
         }
     });
 
+    // long rows, in pieces of what LDS holds at a time
+    std::vector<int64_t> more;
+    for (int64_t i = 0; i < ndof; ++i)
+        for (int64_t c = 1; c * asm_cap(n) < row_ptr[i + 1] - row_ptr[i]; ++c) more.push_back(i | c << 32);
+
     // upload
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t s_rp = al((ndof + 1) * 8), s_ci = al(nnz * 4), s_in = al(ne * n * (wide ? 8 : 4)),
-                 s_pos = al(ne * nn * 2);
+                 s_mo = al(more.size() * 8), s_pos = al(ne * nn * 2);
     feint_asm_plan *pl = new feint_asm_plan;
     if (hipGetDevice(&pl->dev) != hipSuccess) { delete pl; return FEINT_ERR_HIP; }
-    hipError_t err = hipMalloc(&pl->base, 2 * s_rp + s_ci + s_in + s_pos);
+    hipError_t err = hipMalloc(&pl->base, 2 * s_rp + s_ci + s_in + s_mo + s_pos);
     if (err != hipSuccess) { set_error("asm plan allocation", err); delete pl; return FEINT_ERR_HIP; }
     char *p = (char *)pl->base;
     pl->row_ptr = (int64_t *)p; p += s_rp;
@@ -324,11 +344,14 @@ feint_status feint_asm_plan_create(const int32_t *dofs, int64_t ne, int n, int64
     pl->inc_ptr = (int64_t *)p; p += s_rp;
     pl->inc = p; p += s_in;
     pl->wide = wide;
+    pl->more = (int64_t *)p; p += s_mo;
+    pl->nmore = (int64_t)more.size();
     pl->pos = (uint16_t *)p;
     const bool ok = hipMemcpy(pl->row_ptr, row_ptr.data(), (ndof + 1) * 8, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->col_idx, col_idx.data(), nnz * 4, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->inc_ptr, inc_ptr.data(), (ndof + 1) * 8, hipMemcpyHostToDevice) == hipSuccess &&
                     hipMemcpy(pl->inc, wide ? (const void *)rows.data() : inc.data(), ne * n * (wide ? 8 : 4), hipMemcpyHostToDevice) == hipSuccess &&
+                    (more.empty() || hipMemcpy(pl->more, more.data(), more.size() * 8, hipMemcpyHostToDevice) == hipSuccess) &&
                     hipMemcpy(pl->pos, pos.data(), ne * nn * 2, hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) {
         set_error("asm plan upload", hipGetLastError());
